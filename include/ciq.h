@@ -68,9 +68,10 @@ extern "C" {
                            With a resident K, K^{-1/2}B solves of at most 32
                            columns contract the FP32 entries on the FP64 MFMA
                            (no FP32 sums: the result is the rounded matrix's),
-                           wider ones keep FP32 sums of 16 columns; K^{1/2}B
-                           solves keep FP32 sums of 16 (<= 32 columns) or 64
-                           columns, which its final product with K damps      */
+                           K^{1/2}B solves of at most 32 columns keep FP32 sums
+                           of 16 columns; wider solves contract exact three-part
+                           FP16 splits of the FP32 entries and of the vectors on
+                           the FP16 MFMA with FP32 sums of 64 columns           */
 #define CIQ_BF16X3  2   /* as CIQ_F32, but the entries and V are split into BF16
                            hi + scaled lo parts: K V ~ Kh Vh + 2^-8 (Kh Vl + Kl Vh)
                            on bf16 MFMA, FP32 accumulation (~1e-5 per product)   */
@@ -280,8 +281,8 @@ int ciq_kernel_mvm_noalloc(const ciq_problem* p, int dtype, const void* v, int s
  * entries are written once into a buffer allocated for this call, then the
  * product kernel runs once with the launch configuration a solve of this n
  * and s uses, and the buffer is freed. dtype: CIQ_F64 (FP64 entries, FP64
- * MFMA), CIQ_F32 (FP64 entries rounded once to FP32, FP32 MFMA, FP32 sums
- * of 16 or 64 columns as a K^{1/2}B solve runs them, FP64 beyond), CIQ_F16X3
+ * MFMA), CIQ_F32 (FP64 entries rounded once to FP32, contracted as a
+ * K^{1/2}B solve of s columns does, see CIQ_F32), CIQ_F16X3
  * (FP64 entries split into FP16
  * hi + 2^-11 lo, V split likewise after a per-column power-of-two scale,
  * three part products on FP16 MFMA); CIQ_BF16X3 is CIQ_ENOTSUP.

@@ -90,15 +90,32 @@ __host__ __device__ inline size_t op16_index(int i, int c, int nsbt) {
     const int lane = (c & 15) + 16 * (r >> 3);
     return ((((size_t)ks * nsbt + (c >> 4)) * 2) * 64 + lane) * 8 + (r & 7);
 }
-inline size_t op16_halfs(size_t rows_pad, int nsbt) { return rows_pad * (size_t)nsbt * 32; }
 constexpr float kOp16Scale = 256.0f;   // scale of unit-norm Lanczos vectors (entries <= 1)
 
+// Three-part FP16 operand of the wide resident FP32 product (mvm_kx.hip): the
+// scaled element is hi + mid + lo, each the FP16 rounding of what the earlier
+// ones leave. Per k-step and column block 64 lanes x 8 halfs of each part;
+// row r of the k-step is lane (c % 16) + 16 (r % 4), half r / 4 (the order in
+// which the FP32 matrix holds its columns).
+__host__ __device__ inline size_t op3_index(int i, int c, int nsbt) {
+    const int ks = i >> 5, r = i & 31;
+    const int lane = (c & 15) + 16 * (r & 3);
+    return ((((size_t)ks * nsbt + (c >> 4)) * 3) * 64 + lane) * 8 + (r >> 2);
+}
+constexpr float kOp3Scale = 16384.0f;  // scale of unit-norm vectors there
+constexpr float kKxScale = 16384.0f;   // and of the unit-scale entries
+
+inline size_t op_halfs(size_t rows_pad, int nsbt, int parts) { return rows_pad * (size_t)nsbt * 16 * parts; }
+inline float op_scale_of(int parts) { return parts == 3 ? kOp3Scale : kOp16Scale; }
+
 // Where the update / start kernels write the split FP16 copy of the next
-// product operand (p == nullptr: none).
+// product operand (p == nullptr: none), in two (op16_index) or three
+// (op3_index) parts.
 struct Op16 {
     void* p;
     int nsbt;
     float scale;
+    int parts;
 };
 // column blocks of 16 in a split operand buffer for s columns: 1, 2, 4 or a
 // multiple of 8, so every launch's column blocks lie inside it
@@ -154,8 +171,8 @@ struct MvmArgs {
     // nullptr = evaluate entries on the fly
     const void* kt;
     long long njs;           // padded columns / 4
-    // split FP16 resident matrix (CIQ_F16X3): the operand is the tiled split
-    // copy `vt` of the FP64 vector `v` (which supplies the noise term);
+    // split operand (operand_parts > 0): the tiled split copy `vt` of the FP64
+    // vector `v` (which supplies the noise term);
     // y = o2 (K vt) * vinv (per column vcol_inv[c] when non-null)
     const void* vt;
     int nsbt;
@@ -172,6 +189,7 @@ struct KBuildArgs {
     long long njs;           // padded columns / 4
     int elem;                // 0: FP64, 1: FP32 (entries evaluated in FP64, rounded
                              // once), 2: split FP16 hi + 2^-11 lo (4 bytes per entry)
+    float mult;              // FP32: power of two the stored entries are multiplied by
     void* kt;                // kcache_rows(n) x kcache_cols(n) entries
 };
 size_t kcache_rows(int n);
@@ -181,13 +199,27 @@ hipError_t launch_kbuild(const KBuildArgs& a, hipStream_t st);
 hipError_t launch_mvm_kt(const MvmArgs& a, int nsb, hipStream_t st);
 hipError_t launch_mvm_kt32(const MvmArgs& a, int nsb, hipStream_t st);
 hipError_t launch_mvm_kt16(const MvmArgs& a, int nsb, hipStream_t st);
+// Wide resident FP32 product (mvm_kx.hip): any number of columns in one launch;
+// kx_plan picks rt and nsplit.
+hipError_t launch_mvm_kx(const MvmArgs& a, hipStream_t st);
+int kx_rows_per_block(int rt);
+void kx_plan(int n, int s, int part_bytes, int& rt, int& nsplit);
 // Blocks of the resident product (FP32 or FP64 operands, nsb column blocks of
 // 16, rt row tiles per wave) that one CU holds at once; 0 if the query fails.
 int kt_blocks_per_cu(int dtype, int nsb, int rt, int acc = 0);
-// column blocks one product launch covers: 8 x 16 for the on-the-fly FP32
-// product and the resident split FP16 one, 4 x 16 otherwise
+// columns one product launch covers: 8 x 16 for the on-the-fly FP32 product
+// and the resident split FP16 one, 4 x 16 otherwise (the three-part form takes
+// them all, launch_mvm_kx)
 inline int product_cap(int dtype, bool cached) {
     return ((dtype == CIQ_F32 && !cached) || (dtype == CIQ_F16X3 && cached)) ? 128 : 64;
+}
+// Parts of the split operand a resident product of s columns reads: two for
+// CIQ_F16X3; three for a single CIQ_F32 problem of more than 32 columns, where
+// the FP32 contraction would take longer than the stream of K (at most 32
+// columns are HBM-bound as they are, see kt32_item); 0 for the others.
+inline int operand_parts(int dtype, bool cached, int nprob, int s) {
+    if (!cached || nprob != 1) return 0;
+    return dtype == CIQ_F16X3 ? 2 : (dtype == CIQ_F32 && s > 32) ? 3 : 0;
 }
 
 // ---- launchers (kernels.hip, mvm_f32_*.hip) ---------------------------------
@@ -234,7 +266,7 @@ hipError_t launch_scalar(const Dev& d, hipStream_t st);
 template <typename T>
 hipError_t launch_update(const Dev& d, const T* y, long long ysplit, int nsplit, const T* qcur,
                          T* qprev, const T* m_prev, T* m_cur, T* acc, T* solves, float* q32,
-                         int max_n, hipStream_t st, T* pnext = nullptr, Op16 op = Op16{nullptr, 0, 1.0f});
+                         int max_n, hipStream_t st, T* pnext = nullptr, Op16 op = Op16{nullptr, 0, 1.0f, 0});
 
 // pvec (nullable): preconditioned start, pvec <- pvec / beta_1 too and q32
 // copies pvec instead of q.
@@ -256,12 +288,13 @@ hipError_t launch_basis_combine(const Dev& d, int iters, double* cq, double* c, 
 
 template <typename T>
 hipError_t launch_init_vectors(const Dev& d, T* q, T* qprev, T* acc, float* q32, int rows,
-                               hipStream_t st, T* pvec = nullptr, Op16 op = Op16{nullptr, 0, 1.0f});
+                               hipStream_t st, T* pvec = nullptr, Op16 op = Op16{nullptr, 0, 1.0f, 0});
 
-// Split FP16 operand (op16_index layout, nsbt column blocks) of the n x s FP64
-// block x (ld): per-column power-of-two scales (scale, inv: device [s]).
+// Split FP16 operand (two parts in op16_index layout or three in op3_index
+// layout, nsbt column blocks) of the n x s FP64 block x (ld): per-column
+// power-of-two scales (scale, inv: device [s]).
 hipError_t launch_op16_split(const double* x, int n, int s, int ld, double* scale, double* inv, void* vt,
-                             int nsbt, hipStream_t st);
+                             int nsbt, int parts, hipStream_t st);
 
 
 template <typename TI, typename TO>

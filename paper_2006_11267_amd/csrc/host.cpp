@@ -650,8 +650,9 @@ struct Run {
     double* t = nullptr;
     double* w = nullptr;
     const void* kt = nullptr;    // resident kernel matrix (single problem) or nullptr
+    double kt_inv = 1.0;         // its entries are k / kt_inv (a power of two)
     long long njs = 0;
-    // split FP16 resident products (CIQ_F16X3): tiled operand copy of q_j / p_j
+    // resident products with a split operand (parts() > 0): tiled copy of q_j / p_j
     void* vt16 = nullptr;
     int nsbt = 0;
     float op_scale = kOp16Scale;
@@ -687,9 +688,10 @@ struct Run {
         }
         acc = a.template take<double>(vec);
         if (keep_solves) solves = a.template take<double>(vec * Q);
-        if (f16_resident()) {
+        if (parts() > 0) {
             nsbt = op16_nsbt(s);
-            vt16 = a.template take<_Float16>(op16_halfs(kcache_cols(max_n), nsbt));
+            op_scale = op_scale_of(parts());
+            vt16 = a.template take<_Float16>(op_halfs(kcache_cols(max_n), nsbt, parts()));
             opsc = a.template take<double>(s);
             opinv = a.template take<double>(s);
         } else if (sizeof(T) == 4) {
@@ -735,11 +737,17 @@ struct Run {
         d.st = a.template take<IterState>(1);
     }
 
-    int rows_per_block() const { return cached ? 64 * rt : mvm_rows_per_block(dtype, s, rt); }
-    bool f16_resident() const { return dtype == CIQ_F16X3 && cached; }
+    int rows_per_block() const {
+        return parts() == 3 ? kx_rows_per_block(rt) : cached ? 64 * rt : mvm_rows_per_block(dtype, s, rt);
+    }
+    int parts() const { return (sp || dn) ? 0 : operand_parts(dtype, cached, nprob, s); }   // of the split operand
+    size_t op_words() const { return op_halfs(kcache_cols(max_n), nsbt, parts()) / 2; }
 
     void configure(int rt_) {
         rt = rt_;
+        const bool kx = parts() == 3;
+        int kx_split = 1;
+        if (kx) kx_plan(max_n, s, part32 ? 4 : 8, rt, kx_split);
         {   // ~8 rows per thread in the inner-product kernels, at most 512
             // blocks: their partials are summed per column by single-block
             // stages, and at N = 50,000, S = 64 a step with 512 blocks takes
@@ -779,6 +787,7 @@ struct Run {
         } else if (cached && (max_n + 63) / 64 >= 8 && nrb * 8 >= 512) {
             nsplit = 8;   // one column range per XCD
         }
+        if (kx) nsplit = kx_split;
         if (nprob > 1 && nsplit_fixed > 0) nsplit = nsplit_fixed;
         if (sp || dn) nsplit = 1;   // the sparse / dense products write one partial
         ysplit = (long long)rows_total * s;
@@ -856,7 +865,7 @@ struct Run {
         for (int k = 0; k < CIQ_MAX_D; ++k) a.scale[k] = h_scale[k];
         a.pscale = pscale;
         a.n = h_n[0];
-        a.o2 = h_o2d[0];
+        a.o2 = h_o2d[0] * kt_inv;
         a.s2 = h_s2d[0];
         a.wl = (nprob > 1) ? wl : nullptr;
         a.nrb = nrb;
@@ -885,7 +894,7 @@ struct Run {
         if (q32) return q32;
         return precond ? pbuf[(j - 1) & 1] : qbuf[(j - 1) & 1];   // (split FP16: the noise term's)
     }
-    Op16 op16() const { return Op16{vt16, nsbt, op_scale}; }
+    Op16 op16() const { return Op16{vt16, nsbt, op_scale, parts()}; }
 
     // Iteration j's kernels after the product (the buffer roles depend on the
     // parity of j only).
@@ -980,7 +989,7 @@ struct Run {
         // the state is reused scratch: clear `done` before the first kernel that reads it
         HIPCHK(launch_fill<int>(reinterpret_cast<int*>(d.st), sizeof(IterState) / sizeof(int), 0, st));
         if (vt16)      // rows past n and columns past s of the split operand stay zero
-            HIPCHK(launch_fill<int>(static_cast<int*>(vt16), op16_halfs(kcache_cols(max_n), nsbt) / 2, 0, st));
+            HIPCHK(launch_fill<int>(static_cast<int*>(vt16), op_words(), 0, st));
         if (precond) {
             // start z_1 = c / beta_1, p_1 = P^{-1} c / beta_1, beta_1^2 = c^T P^{-1} c
             STCHK(pc_apply(*pc, 1.0 / pc->s2, pc->fin, qbuf[0], rows_total, s, pbuf[0], pc->dotp, nullptr, nullptr,
@@ -1091,7 +1100,7 @@ struct Run {
 // the timed launches write only the partial buffer.
 template <typename T>
 int tune_rt(Run<T>& r, const void* operand, hipStream_t st) {
-    if (r.sp || r.dn) {
+    if (r.sp || r.dn || r.parts() == 3) {   // nothing to choose, or chosen by kx_plan
         r.configure(1);
         return CIQ_OK;
     }
@@ -1099,7 +1108,7 @@ int tune_rt(Run<T>& r, const void* operand, hipStream_t st) {
     const bool batched = r.nprob > 1;
     // one row tile per wave: the widest FP32 on-the-fly and split FP16 resident
     // launches (register budget) and the on-the-fly split forms
-    const bool rt1 = (r.dtype == CIQ_F32 && nsb >= 8) || (r.dtype == CIQ_F16X3 && r.cached && nsb > 4) ||
+    const bool rt1 = (r.dtype == CIQ_F32 && !r.cached && nsb >= 8) || (r.dtype == CIQ_F16X3 && r.cached && nsb > 4) ||
                      r.dtype == CIQ_BF16X3 || (r.dtype == CIQ_F16X3 && !r.cached);
     if (rt1 && !batched) {
         r.configure(1);
@@ -1277,6 +1286,7 @@ int kcache_build(Run<T>& r, const KCache& kc, hipStream_t st) {
             ka.nchunk = (int)(kcache_cols(ka.n) / 64);
             ka.njs = (long long)(kcache_cols(ka.n) / 4);
             ka.elem = 1;
+            ka.mult = 1.0f;
             ka.kt = static_cast<float*>(kc.ptr) + r.h_pkt[p];
             HIPCHK(launch_kbuild(ka, st));
         }
@@ -1293,9 +1303,11 @@ int kcache_build(Run<T>& r, const KCache& kc, hipStream_t st) {
     ka.nchunk = (int)(kcache_cols(ka.n) / 64);
     ka.njs = (long long)(kcache_cols(ka.n) / 4);
     ka.elem = (r.dtype == CIQ_F16X3) ? 2 : (kc.elem == 4 ? 1 : 0);
+    ka.mult = (r.parts() == 3) ? kKxScale : 1.0f;
     ka.kt = kc.ptr;
     HIPCHK(launch_kbuild(ka, st));
     r.kt = kc.ptr;
+    r.kt_inv = 1.0 / (double)ka.mult;
     r.njs = ka.njs;
     return CIQ_OK;
 }
@@ -1390,6 +1402,7 @@ int solve(int nprob, const ciq_problem* probs, const ciq_opts* o, const void* co
     if (!sparse && !dense) STCHK(setup_points(main, probs, dtype, st));
     STCHK(kcache_build(main, kc, st));
     bnd.kt = main.kt;
+    bnd.kt_inv = main.kt_inv;
     bnd.njs = main.njs;
     // the point and matrix set-up above is queued work: finish it first so
     // the factors' build time is their own
@@ -1401,10 +1414,13 @@ int solve(int nprob, const ciq_problem* probs, const ciq_opts* o, const void* co
         main.pc = &pc;
         bnd.pc = &pc;
         // the operand p_j = P^{-1} z_j has p_j^T z_j = 1 and P >= sigma^2 I, so
-        // |p_j| <= 1/sigma: scale it by the power of two at most 256 sigma
-        const float sc = (float)std::ldexp(1.0, (int)std::floor(std::log2(256.0 * std::sqrt(probs[0].noise))));
-        main.op_scale = sc;
-        bnd.op_scale = sc;
+        // |p_j| <= 1/sigma: scale it by the power of two at most sigma times
+        // the unit-norm vectors' scale
+        const auto pscale = [&](int parts) {
+            return (float)std::ldexp(1.0, (int)std::floor(std::log2(op_scale_of(parts) * std::sqrt(probs[0].noise))));
+        };
+        main.op_scale = pscale(main.parts());
+        bnd.op_scale = pscale(bnd.parts());
     }
     if (post_spec) {
         STCHK(post_build(probs[0], dtype, main.xh, main.dp, main.kernel, main.ard, main.h_scale.data(), *post_spec,
@@ -1497,8 +1513,7 @@ int solve(int nprob, const ciq_problem* probs, const ciq_opts* o, const void* co
         STCHK(tune_rt(main, main.q32, st));
     } else {
         if (main.vt16)   // the trial launches read the split operand: give them zeros
-            HIPCHK(launch_fill<int>(static_cast<int*>(main.vt16), op16_halfs(kcache_cols(main.max_n), main.nsbt) / 2,
-                                    0, st));
+            HIPCHK(launch_fill<int>(static_cast<int*>(main.vt16), main.op_words(), 0, st));
         STCHK(tune_rt(main, main.qbuf[0], st));
     }
 
@@ -1587,7 +1602,7 @@ int solve(int nprob, const ciq_problem* probs, const ciq_opts* o, const void* co
         }
         if (main.vt16)   // the combined solution is not unit-norm: per-column scales
             HIPCHK(launch_op16_split(main.acc, main.rows_total, s, s, main.opsc, main.opinv, main.vt16, main.nsbt,
-                                     st));
+                                     main.parts(), st));
         MvmArgs a = main.mvm_args(operand, main.ypart);
         a.done = nullptr;
         a.prob_done = nullptr;
@@ -1739,6 +1754,14 @@ int backward_impl(const ciq_problem* p, const ciq_opts* o, int mode, const doubl
         MvmArgs a = r.mvm_args(g, r.ypart);
         a.ldv = ldg;
         a.done = nullptr;
+        if (r.vt16) {
+            HIPCHK((launch_copy<T, double>(static_cast<const T*>(g), ldg, n, s, r.qbuf[0], s, st)));
+            HIPCHK(launch_fill<int>(static_cast<int*>(r.vt16), r.op_words(), 0, st));
+            HIPCHK(launch_op16_split(r.qbuf[0], n, s, s, r.opsc, r.opinv, r.vt16, r.nsbt, r.parts(), st));
+            a.v = r.qbuf[0];
+            a.ldv = s;
+            a.vcol_inv = r.opinv;
+        }
         HIPCHK(launch_mvm(dtype, a, st));
         HIPCHK(launch_reduce_splits<double>(r.ypart, r.ysplit, r.nsplit, s, n, s, r.qbuf[0], s, st));
     } else {
@@ -2014,8 +2037,8 @@ int ciq_kernel_mvm_resident(const ciq_problem* p, int dtype, const void* v, int 
             operand = r.q32;
         }
         if (r.vt16) {
-            HIPCHK(launch_fill<int>(static_cast<int*>(r.vt16), op16_halfs(kcache_cols(p->n), r.nsbt) / 2, 0, stream));
-            HIPCHK(launch_op16_split(r.qbuf[0], p->n, s, s, r.opsc, r.opinv, r.vt16, r.nsbt, stream));
+            HIPCHK(launch_fill<int>(static_cast<int*>(r.vt16), r.op_words(), 0, stream));
+            HIPCHK(launch_op16_split(r.qbuf[0], p->n, s, s, r.opsc, r.opinv, r.vt16, r.nsbt, r.parts(), stream));
         }
         STCHK(tune_rt(r, operand, stream));
         MvmArgs a = r.mvm_args(operand, r.ypart);

@@ -61,6 +61,8 @@ hipError_t launch_mvm(int dtype, const MvmArgs& a, hipStream_t st) {
     // FP32 partials: the resident FP32 and split-FP16 products only
     if (a.y32 != nullptr && !((dtype == CIQ_F32 || dtype == CIQ_F16X3) && a.kt != nullptr && a.wl == nullptr))
         return hipErrorInvalidValue;
+    if (dtype == CIQ_F32 && a.vt != nullptr)
+        return a.kt != nullptr ? launch_mvm_kx(a, st) : hipErrorInvalidValue;
     const int cap = product_cap(dtype, a.kt != nullptr);
     for (int c0 = 0; c0 < a.s; c0 += cap) {
         MvmArgs g = a;
@@ -718,6 +720,29 @@ __device__ inline void put_op16(_Float16* vt, int nsbt, int i, int c, double x, 
     vt[k + 512] = lo;
 }
 
+// Element (i, c) of the three-part operand copy (op3_index layout).
+__device__ __forceinline__ void split3_f16(double x, float scale, _Float16& h, _Float16& m, _Float16& l) {
+    const double xs = x * (double)scale;
+    h = (_Float16)(float)xs;
+    const double r = xs - (double)h;
+    m = (_Float16)(float)r;
+    l = (_Float16)(float)(r - (double)m);
+}
+
+__device__ inline void put_op(const Op16& op, int i, int c, double x) {
+    _Float16* vt = static_cast<_Float16*>(op.p);
+    if (op.parts == 2) {
+        put_op16(vt, op.nsbt, i, c, x, op.scale);
+        return;
+    }
+    _Float16 h, m, l;
+    split3_f16(x, op.scale, h, m, l);
+    const size_t k = op3_index(i, c, op.nsbt);
+    vt[k] = h;
+    vt[k + 512] = m;
+    vt[k + 1024] = l;
+}
+
 template <typename T>
 __global__ __launch_bounds__(256) void update_kernel(Dev d, const T* y, long long ysplit, int nsplit,
                                                      const T* qcur, T* qprev, const T* m_prev,
@@ -785,7 +810,7 @@ __global__ __launch_bounds__(256) void update_kernel(Dev d, const T* y, long lon
                 const T pn = pnext[idx] * ib;
                 pnext[idx] = pn;
                 if (q32) q32[idx] = (float)pn;
-                else if (op.p) put_op16(static_cast<_Float16*>(op.p), op.nsbt, i, c, (double)pn, op.scale);
+                else if (op.p) put_op(op, i, c, (double)pn);
                 continue;
             }
             double ys = (double)y[idx];
@@ -796,9 +821,72 @@ __global__ __launch_bounds__(256) void update_kernel(Dev d, const T* y, long lon
             qprev[idx] = qn;
             if (bq) bq[idx] = (double)qn;
             if (q32) q32[idx] = (float)qn;      // operand copy for the FP32 kernel product
-            else if (op.p) put_op16(static_cast<_Float16*>(op.p), op.nsbt, i, c, (double)qn, op.scale);
+            else if (op.p) put_op(op, i, c, (double)qn);
         }
     }
+}
+
+// The update of a run with the resident basis and a split operand (the
+// products of CIQ_F16X3 and of wide CIQ_F32 solves): q_{j+1} into the Lanczos
+// slot, the basis slot and the operand copy, nothing else. A thread owns the
+// eight rows that make one 16-byte lane of the operand in one column, so the
+// parts are written with 16-byte stores (256 contiguous bytes per 16 columns)
+// instead of two bytes at a time, and its 24 loads are in flight together.
+template <int PARTS>
+__global__ __launch_bounds__(256) void update_split_kernel(Dev d, const double* __restrict__ y,
+                                                           const double* __restrict__ qcur, double* __restrict__ qprev,
+                                                           Op16 op) {
+    typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+    if (!d.st->live) return;
+    const int s = d.s, n = d.n[0];
+    const int slot = d.st->iter;
+    double* const bq = (slot < d.basis_slots) ? d.basis[slot] : nullptr;
+    const long long units = (long long)((n + 31) / 32) * 4 * s;
+    const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (e >= units) return;
+    const int u = (int)(e / s), c = (int)(e - (long long)u * s);
+    if (d.colflag[c] != 2) return;
+    const int ks = u >> 2, g = u & 3;
+    constexpr int RS = (PARTS == 3) ? 4 : 1;       // row stride and first row of the lane (op3 / op16 order)
+    const int i0 = ks * 32 + (PARTS == 3 ? g : 8 * g);
+    const double al = d.alpha[c], bj = d.beta_used[c], ib = d.inv_beta_next[c];
+    double yv[8], qv[8], pv[8];
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+        const int i = i0 + RS * m;
+        const long long idx = (long long)i * s + c;
+        yv[m] = (i < n) ? y[idx] : 0.0;
+        qv[m] = (i < n) ? qcur[idx] : 0.0;
+        pv[m] = (i < n) ? qprev[idx] : 0.0;
+    }
+    half8 part[PARTS];
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+        const int i = i0 + RS * m;
+        const long long idx = (long long)i * s + c;
+        const double vT = yv[m] - bj * pv[m];     // same arithmetic as the inner products
+        const double v = vT - al * qv[m];
+        const double qn = v * ib;
+        if (i < n) {
+            qprev[idx] = qn;
+            if (bq) bq[idx] = qn;
+        }
+        if constexpr (PARTS == 3) {
+            _Float16 h, mm, l;
+            split3_f16(qn, op.scale, h, mm, l);
+            part[0][m] = h;
+            part[1][m] = mm;
+            part[2][m] = l;
+        } else {
+            const double xs = qn * (double)op.scale;
+            const _Float16 hi = (_Float16)(float)xs;
+            part[0][m] = hi;
+            part[1][m] = (_Float16)(float)((xs - (double)hi) * 2048.0);
+        }
+    }
+    half8* out = static_cast<half8*>(op.p) + ((size_t)ks * op.nsbt + (c >> 4)) * 64 * PARTS + (c & 15) + 16 * g;
+#pragma unroll
+    for (int k = 0; k < PARTS; ++k) out[64 * k] = part[k];
 }
 
 // Blocks of update_kernel<T> with shm bytes of coefficient tile that the
@@ -832,6 +920,16 @@ template <typename T>
 hipError_t launch_update(const Dev& d, const T* y, long long ysplit, int nsplit, const T* qcur, T* qprev,
                          const T* m_prev, T* m_cur, T* acc, T* solves, float* q32, int max_n, hipStream_t st,
                          T* pnext, Op16 op) {
+    if (sizeof(T) == 8 && d.basis != nullptr && op.p != nullptr && pnext == nullptr && d.nprob == 1 && nsplit == 1) {
+        const long long units = (long long)((max_n + 31) / 32) * 4 * d.s;
+        const dim3 g((unsigned)((units + 255) / 256)), b(256);
+        const double* yd = reinterpret_cast<const double*>(y);
+        const double* qc = reinterpret_cast<const double*>(qcur);
+        double* qp = reinterpret_cast<double*>(qprev);
+        if (op.parts == 3) hipLaunchKernelGGL(update_split_kernel<3>, g, b, 0, st, d, yd, qc, qp, op);
+        else hipLaunchKernelGGL(update_split_kernel<2>, g, b, 0, st, d, yd, qc, qp, op);
+        return hipGetLastError();
+    }
     const size_t per = 5 * sizeof(T) + sizeof(int);   // LDS bytes per (shift, column)
     int TS = col_tile(d.s);
     while (TS > 1 && (size_t)d.Q * TS * per > 49152) TS >>= 1;   // coefficient tile <= 48 KB LDS
@@ -978,11 +1076,11 @@ __global__ void init_vectors_kernel(Dev d, T* q, T* qprev, T* acc, float* q32, T
         const T pv = pvec[e] * inv;
         pvec[e] = pv;
         if (q32) q32[e] = (float)pv;
-        else if (op.p) put_op16(static_cast<_Float16*>(op.p), op.nsbt, row, c, (double)pv, op.scale);
+        else if (op.p) put_op(op, row, c, (double)pv);
     } else if (q32) {
         q32[e] = (float)qv;
     } else if (op.p) {
-        put_op16(static_cast<_Float16*>(op.p), op.nsbt, row, c, (double)qv, op.scale);
+        put_op(op, row, c, (double)qv);
     }
     qprev[e] = (T)0;
     acc[e] = (T)0;
@@ -1001,12 +1099,13 @@ template hipError_t launch_init_vectors<double>(const Dev&, double*, double*, do
 
 // ----------------------------------------------------------------------------
 // Split FP16 operand of an arbitrary FP64 block vector: per column a power of
-// two 2^e with max_i |x[i][c]| 2^e in [128, 256) (1 for a zero column), then
-// the op16 split of x[i][c] 2^e. inv[c] = 2^-e undoes it in the product.
+// two 2^e with max_i |x[i][c]| 2^e in [half, full) of the parts' scale (256 or
+// 16384; 1 for a zero column), then the split of x[i][c] 2^e. inv[c] = 2^-e
+// undoes it in the product.
 // Block: 64 columns x 16 row lanes, fixed combination order.
 // ----------------------------------------------------------------------------
-__global__ __launch_bounds__(1024) void op16_scale_kernel(const double* x, int n, int s, int ld, double* scale,
-                                                          double* inv) {
+__global__ __launch_bounds__(1024) void op16_scale_kernel(const double* x, int n, int s, int ld, int full_log2,
+                                                          double* scale, double* inv) {
     __shared__ double sh[1024];
     const int cl = threadIdx.x & 63, lane = threadIdx.x >> 6;
     const int c = blockIdx.x * 64 + cl;
@@ -1021,27 +1120,28 @@ __global__ __launch_bounds__(1024) void op16_scale_kernel(const double* x, int n
         if (m > 0.0 && isfinite(m)) {
             int e = 0;
             (void)frexp(m, &e);          // m in [2^(e-1), 2^e)
-            sc = ldexp(1.0, 8 - e);      // m sc in [128, 256)
+            sc = ldexp(1.0, full_log2 - e);
         }
         scale[c] = sc;
         inv[c] = 1.0 / sc;
     }
 }
 
-__global__ void op16_split_kernel(const double* x, int n, int s, int ld, const double* scale, _Float16* vt,
-                                  int nsbt) {
+__global__ void op16_split_kernel(const double* x, int n, int s, int ld, const double* scale, Op16 op) {
     const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= (long long)n * s) return;
     const int i = (int)(e / s), c = (int)(e - (long long)i * s);
-    put_op16(vt, nsbt, i, c, x[(long long)i * ld + c], (float)scale[c]);
+    op.scale = (float)scale[c];
+    put_op(op, i, c, x[(long long)i * ld + c]);
 }
 
 hipError_t launch_op16_split(const double* x, int n, int s, int ld, double* scale, double* inv, void* vt,
-                             int nsbt, hipStream_t st) {
-    hipLaunchKernelGGL(op16_scale_kernel, dim3((s + 63) / 64), dim3(1024), 0, st, x, n, s, ld, scale, inv);
+                             int nsbt, int parts, hipStream_t st) {
+    hipLaunchKernelGGL(op16_scale_kernel, dim3((s + 63) / 64), dim3(1024), 0, st, x, n, s, ld, parts == 3 ? 14 : 8,
+                       scale, inv);
     const long long total = (long long)n * s;
     hipLaunchKernelGGL(op16_split_kernel, dim3((int)((total + 255) / 256)), dim3(256), 0, st, x, n, s, ld, scale,
-                       static_cast<_Float16*>(vt), nsbt);
+                       Op16{vt, nsbt, 1.0f, parts});
     return hipGetLastError();
 }
 

@@ -119,7 +119,7 @@ __global__ __launch_bounds__(256) void kbuild_kernel(KBuildArgs a) {
             for (int p = 0; p < 4; ++p) {
                 floatx4 kv;
 #pragma unroll
-                for (int h = 0; h < 4; ++h) kv[h] = (float)entry(16 * p + 4 * h + (lane >> 4));
+                for (int h = 0; h < 4; ++h) kv[h] = (float)entry(16 * p + 4 * h + (lane >> 4)) * a.mult;
                 __builtin_nontemporal_store(kv, out32 + (size_t)(c * 4 + p) * 64);
             }
         } else {
@@ -308,15 +308,15 @@ __global__ __launch_bounds__(64 * WAVES) void mvm_kt_kernel(MvmArgs a) {
 // in the noise-level eigendirections that the inverse root amplifies, and
 // it grows as the square root of the MFMA steps B one FP32 sum spans.
 // NACC picks B: NACC accumulators take the chunk's 16 steps in rotation
-// (B = 16 / NACC, NACC = 1 or 4), and NACC = 0 takes each MFMA's output
-// into FP64 at once (B = 1, four converts and adds per MFMA). NACC = -1
+// (B = 16 / NACC, NACC = 4). NACC = -1
 // contracts on the FP64 MFMA instead, the FP32 operands converted as they
 // are used (two converts per MFMA, no FP32 sums at all): at half the FP32
 // MFMA rate, which launches of at most 32 columns can afford, since they
 // stream K at HBM speed with the matrix cores less than half busy. Those
-// launches use B = 4, or the FP64 MFMA for the inverse root (a.acc); the
-// 64-column launch is MFMA-bound and uses B = 16, or B = 4 for the inverse
-// root.
+// launches use B = 4, or the FP64 MFMA for the inverse root (a.acc); a
+// batched 64-column launch uses B = 4. A single problem of more than 32
+// columns would be MFMA-bound here and runs on the FP16 matrix cores
+// (mvm_kx.hip).
 // Batched runs (a.wl set) keep one such matrix per problem (a.pkt: its
 // element offset, a.pnjs: its padded columns / 4) and run persistently: a
 // grid of the resident blocks takes (problem, row block, column range) items
@@ -350,9 +350,9 @@ __device__ __forceinline__ void kt32_item(const MvmArgs& a, int p, int rb, int s
     const int c0 = (int)(((long long)split * nchunk) / nsplit);
     const int c1 = (int)(((long long)(split + 1) * nchunk) / nsplit);
 
-    // FP32 sums of B = 16 / NACC steps (NACC = 0: one step), FP64 beyond;
+    // FP32 sums of B = 16 / NACC steps, FP64 beyond;
     // NACC = -1: FP64 MFMA, in two chains when the wave has one output tile
-    static_assert(NACC >= -1 && NACC <= 4 && NACC != 3, "accumulator rotation");
+    static_assert(NACC == -1 || NACC == 4, "accumulator rotation");
     constexpr bool F64M = NACC < 0;
     constexpr int NA = NACC > 0 ? NACC : 1;
     constexpr int NC = (F64M && RT * NSB == 1) ? 2 : 1;
@@ -449,16 +449,6 @@ __device__ __forceinline__ void kt32_item(const MvmArgs& a, int p, int rb, int s
                     for (int rt = 0; rt < RT; ++rt)
                         acc64[st % NC][rt][sb] = __builtin_amdgcn_mfma_f64_16x16x4f64(
                             (double)cur[rt][st], (double)bcur[sb], acc64[st % NC][rt][sb], 0, 0, 0);
-            } else if constexpr (NACC == 0) {
-#pragma unroll
-                for (int sb = 0; sb < NSB; ++sb)
-#pragma unroll
-                    for (int rt = 0; rt < RT; ++rt) {
-                        const floatx4 t = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                            cur[rt][st], bcur[sb], floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) accd[rt][sb][r] += (double)t[r];
-                    }
             } else {
 #pragma unroll
                 for (int sb = 0; sb < NSB; ++sb)
@@ -719,7 +709,7 @@ static int occupancy_of(K kernel, int threads = 256) {
 }
 
 // accumulator rotation of a launch (see kt32_item)
-constexpr int kt32_nacc(int nsb, int acc) { return nsb <= 2 ? (acc ? -1 : 4) : (acc ? 4 : 1); }
+constexpr int kt32_nacc(int nsb, int acc) { return nsb <= 2 && acc ? -1 : 4; }
 
 template <int NSB, int RT, int NACC>
 hipError_t launch_kt32_variant(const MvmArgs& a, int grid, hipStream_t st) {

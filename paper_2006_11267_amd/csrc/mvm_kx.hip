@@ -1,0 +1,272 @@
+// Resident FP32 kernel matrix times more than 32 columns (CIQ_F32) on the FP16
+// matrix cores.
+//
+// v_mfma_f32_16x16x4_f32 runs at 157 TFLOP/s, so at 64 columns the FP32
+// contraction, not the stream of K, bounds a product (2.84 ms at N = 50,000,
+// S = 64, where reading the 10 GB matrix takes 1.6 ms). Here every FP32 entry
+// is split in registers into three FP16 parts, 11 + 11 + 2 significant bits,
+// whose sum is the entry exactly, and the operand vector (written split by
+// the update kernel, op3_index layout) likewise carries 33 bits, so that
+//     K V ~ Kh Vh + (Kh Vm + Km Vh + Km Vm + Kh Vl + Kl Vh)
+// drops only terms below 2^-33 of Kh Vh: six v_mfma_f32_16x16x32_f16 cost 0.9
+// ms of matrix time at that size and the stream of K becomes the bound. Both
+// operands are kept scaled by 2^14 (K in [0, 1] by the build pass, |V| <= 1 by
+// the kernels that write it), which keeps the low
+// parts above FP16's subnormal quantum; the matrix cores take subnormal FP16
+// inputs as they are (checked on gfx950 with an in-bounds probe).
+//
+// Kh Vh is summed in FP32 over one 64-column chunk (two MFMAs) and then taken
+// to FP64; the five cross terms are 2^-11 of it and stay in one FP32
+// accumulator over the block's column range.
+//
+// K is read in the layout of the FP32 form (mvm_cache.hip): lane l of a
+// 16-row tile holds K[l % 16][4 st + l / 16], st = 0..15 of the chunk. The
+// 16x16x32 MFMA lets the eight columns of lane group g = l / 16 be any eight,
+// as long as both operands agree, so k-step ks takes the group's columns
+// 32 ks + 4 m + g (m = 0..7) and the split operand is stored in that order.
+//
+// Block: WAVES waves of one 16-row tile each; per chunk the block stages the
+// split operand (NSB column blocks x 2 k-steps x three parts, 1 KB each) in one
+// of two LDS buffers, one barrier per chunk (see kt32_item). Sixteen waves
+// halve the operand's L2 reads (24 KB per block and chunk against 64 KB of K)
+// and fit 128 registers a wave. Measured at N = 50,000, S = 64: 2.13 ms with
+// sixteen waves, 2.20 with eight (the FP32 MFMA form: 2.86 with FP32 sums of
+// 64 columns, 3.72 with sums of 16); 12 waves with two chunks of K in flight
+// 2.23, two tiles a wave 2.31, 128 columns a launch 4.35 (no better than two
+// groups of 64). More than 64 columns run as groups of one launch, the groups
+// of a row block next to each other on one XCD so that its L2 serves K to the
+// later ones. Relative error of one product against 64 bits: 7e-8 (FP32 MFMA:
+// 1.5e-7), half of it the rounding of the entries.
+#include <algorithm>
+#include <cmath>
+
+#include "ciq_internal.h"
+
+namespace ciq {
+namespace {
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
+
+// eight (scaled) entries as three FP16 parts, rounded towards zero so that
+// every remainder is exact. minus1 is -1 in a register the compiler cannot see
+// through: it keeps each remainder one v_fma_mix_f32 (an FP16 operand read as
+// FP32) instead of a conversion and a subtraction.
+__device__ __forceinline__ void split3(const float* k, float minus1, f16x8& h, f16x8& m, f16x8& l) {
+    uintx4 hb, mb, lb;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        const float x0 = k[2 * p], x1 = k[2 * p + 1];
+        const auto hp = __builtin_amdgcn_cvt_pkrtz(x0, x1);
+        const float r0 = __builtin_fmaf((float)hp[0], minus1, x0), r1 = __builtin_fmaf((float)hp[1], minus1, x1);
+        const auto mp = __builtin_amdgcn_cvt_pkrtz(r0, r1);
+        const auto lp = __builtin_amdgcn_cvt_pkrtz(__builtin_fmaf((float)mp[0], minus1, r0),
+                                                   __builtin_fmaf((float)mp[1], minus1, r1));
+        hb[p] = __builtin_bit_cast(unsigned int, hp);
+        mb[p] = __builtin_bit_cast(unsigned int, mp);
+        lb[p] = __builtin_bit_cast(unsigned int, lp);
+    }
+    h = __builtin_bit_cast(f16x8, hb);
+    m = __builtin_bit_cast(f16x8, mb);
+    l = __builtin_bit_cast(f16x8, lb);
+}
+
+template <int NSB, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, 4) void mvm_kx_kernel(MvmArgs a, int groups) {
+    constexpr int NT = 64 * WAVES;
+    constexpr int VB = NSB * 192;                // 16-byte operand units per k-step
+    constexpr int VU = 2 * VB;                   // per chunk
+    constexpr int UPT = (VU + NT - 1) / NT;
+    __shared__ f16x8 vs[2 * VU];
+
+    if (a.done != nullptr && *a.done != 0) return;
+    const int nsplit = a.nsplit;
+    const int split = (int)(blockIdx.x % (unsigned)nsplit);
+    const int x = (int)(blockIdx.x / (unsigned)nsplit);
+    const int rb = x / groups, grp = x - rb * groups;
+    const int n = a.n;
+    const f16x8* __restrict__ vt = static_cast<const f16x8*>(a.vt) + grp * VB;
+    const int kstride = a.nsbt * 192;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tile = rb * WAVES + wave;
+    const int tmax = (int)(((n + 127) / 128) * 8) - 1;   // last tile of the padded matrix
+
+    const int nchunk = (n + 63) / 64;
+    const int c0 = (int)(((long long)split * nchunk) / nsplit);
+    const int c1 = (int)(((long long)(split + 1) * nchunk) / nsplit);
+
+    floatx4 ah[NSB], ax[NSB];
+    double accd[NSB][4];
+#pragma unroll
+    for (int sb = 0; sb < NSB; ++sb) {
+        ax[sb] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int r = 0; r < 4; ++r) accd[sb][r] = 0.0;
+    }
+
+    // operand staging: thread offsets within a chunk are fixed, the chunk's
+    // base is uniform
+    f16x8 vreg[UPT];
+    int voff[UPT];
+#pragma unroll
+    for (int u = 0; u < UPT; ++u) {
+        const int e = tid + NT * u;
+        voff[u] = e + (e >= VB ? kstride - VB : 0);
+    }
+    auto fetch_v = [&](int c) {
+        const f16x8* base = vt + (long long)c * 2 * kstride;
+#pragma unroll
+        for (int u = 0; u < UPT; ++u) {
+            if (VU % NT != 0 && tid + NT * u >= VU) break;
+            vreg[u] = base[(unsigned)voff[u]];
+        }
+    };
+    float minus1 = -1.0f;
+    asm volatile("" : "+s"(minus1));
+    const float* kb = static_cast<const float*>(a.kt) + (size_t)min(tile, tmax) * a.njs * 64;
+    // one chunk of K in flight per wave; half a chunk (k-step kk) of the next
+    // one is requested as soon as the registers of this one's half are free
+    float kq[16];
+    auto fetch_k = [&](int c, int kk) {
+        const floatx4* base = reinterpret_cast<const floatx4*>(kb + (size_t)c * 1024);
+#pragma unroll
+        for (int p = 2 * kk; p < 2 * kk + 2; ++p) {
+            const floatx4 x = __builtin_nontemporal_load(base + (unsigned)(lane + 64 * p));
+#pragma unroll
+            for (int h = 0; h < 4; ++h) kq[4 * p + h] = x[h];
+        }
+    };
+    auto chunk = [&](int c) {
+        f16x8* vb = vs + (c & 1) * VU;
+#pragma unroll
+        for (int u = 0; u < UPT; ++u) {
+            const int e = tid + NT * u;
+            if (VU % NT != 0 && e >= VU) break;
+            vb[e] = vreg[u];
+        }
+        __syncthreads();
+        if (c + 1 < c1) fetch_v(c + 1);
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+            f16x8 kh, km, kl;
+            split3(kq + 8 * kk, minus1, kh, km, kl);
+            if (c + 1 < c1) fetch_k(c + 1, kk);
+            const f16x8* bp = vb + kk * VB + lane;
+#pragma unroll
+            for (int sb = 0; sb < NSB; ++sb) {
+                const f16x8 bh = bp[sb * 192], bm = bp[sb * 192 + 64], bl = bp[sb * 192 + 128];
+                ah[sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                    kh, bh, kk == 0 ? floatx4{0.f, 0.f, 0.f, 0.f} : ah[sb], 0, 0, 0);
+                ax[sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(km, bh, ax[sb], 0, 0, 0);
+                ax[sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kl, bh, ax[sb], 0, 0, 0);
+                ax[sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kh, bm, ax[sb], 0, 0, 0);
+                ax[sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(km, bm, ax[sb], 0, 0, 0);
+                ax[sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kh, bl, ax[sb], 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int sb = 0; sb < NSB; ++sb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) accd[sb][r] += (double)ah[sb][r];
+    };
+    if (c0 < c1) {
+        fetch_v(c0);
+        fetch_k(c0, 0);
+        fetch_k(c0, 1);
+    }
+    for (int c = c0; c < c1; ++c) chunk(c);
+
+    const double o2 = a.o2, s2 = a.s2;
+    const double* __restrict__ v = static_cast<const double*>(a.v);
+    double* __restrict__ y = static_cast<double*>(a.y) + (long long)split * a.ysplit;
+    float* __restrict__ y32 = a.y32 ? a.y32 + (long long)split * a.ysplit : nullptr;
+    const int s = a.s, ldv = a.ldv, ldy = a.ldy;
+#pragma unroll
+    for (int sb = 0; sb < NSB; ++sb) {
+        const int cc = (grp * NSB + sb) * 16 + (lane & 15);
+        if (cc >= s) continue;
+        const double vi = a.vcol_inv ? a.vcol_inv[cc] : a.vinv;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = tile * 16 + 4 * (lane >> 4) + r;   // 16x16 accumulator layout
+            if (i < n) {
+                double val = o2 * ((accd[sb][r] + (double)ax[sb][r]) * vi);
+                if (split == 0) val = fma(s2, v[(long long)i * ldv + cc], val);
+                if (y32) y32[(long long)i * ldy + cc] = (float)val;
+                else y[(long long)i * ldy + cc] = val;
+            }
+        }
+    }
+}
+
+template <int NSB>
+hipError_t launch_kx_nsb(const MvmArgs& a, int groups, hipStream_t st) {
+    const int rows = kx_rows_per_block(a.rt);
+    const dim3 grid((unsigned)((a.n + rows - 1) / rows) * groups * a.nsplit);
+    if (a.rt == 1) hipLaunchKernelGGL((mvm_kx_kernel<NSB, 8>), grid, dim3(512), 0, st, a, groups);
+    else hipLaunchKernelGGL((mvm_kx_kernel<NSB, 16>), grid, dim3(1024), 0, st, a, groups);
+    return hipGetLastError();
+}
+
+// Column groups of a launch: blocks of 16 columns, at most four a group, as
+// even as they come; the operand buffer (op16_nsbt) has room for groups * nsb.
+void kx_groups(int s, int& groups, int& nsb) {
+    const int nb = (s + 15) / 16;
+    groups = (nb + 3) / 4;
+    nsb = std::max(3, (nb + groups - 1) / groups);
+}
+
+}  // namespace
+
+int kx_rows_per_block(int rt) { return rt == 1 ? 128 : 256; }
+
+hipError_t launch_mvm_kx(const MvmArgs& a, hipStream_t st) {
+    int groups, nsb;
+    kx_groups(a.s, groups, nsb);
+    if (a.rt < 1 || a.rt > 2 || a.njs * 4 != (long long)kcache_cols(a.n) || a.vt == nullptr ||
+        a.nsbt < groups * nsb || a.nsplit < 1)
+        return hipErrorInvalidValue;
+    return nsb == 3 ? launch_kx_nsb<3>(a, groups, st) : launch_kx_nsb<4>(a, groups, st);
+}
+
+// Block form and column ranges of an n x n product with s columns whose
+// partials have part_bytes per element. Modelled from the times measured at n
+// = 50,000 (a CU with all its blocks resident takes 3.6 us for 256 rows x 64
+// columns of K x 64 columns of V; two 128-row blocks about 4 % more, as they
+// read the operand twice) and at n = 5,000 (a lone 128-row block: 2.4 us a
+// chunk, bound by its loads' latency): rounds of blocks over the chip's 256
+// (16 waves) or 512 (8 waves) slots, each as long as its chunks, plus writing
+// and summing the partials at 4.5 TB/s. Where the operand is several times an
+// XCD's 4 MB L2 the ranges are 8 or 16, so that every XCD (block index mod 8)
+// streams one or two of them (at N = 10,000, S = 64, where it is as large as
+// the L2, six ranges in one round of blocks beat sixteen: 101 against 117 us).
+void kx_plan(int n, int s, int part_bytes, int& rt, int& nsplit) {
+    int groups, nsb;
+    kx_groups(s, groups, nsb);
+    const int chunks = (n + 63) / 64;
+    const bool big = (double)n * s * 6.0 > 1.2e7;
+    double best = 1e300;
+    rt = 2;
+    nsplit = 1;
+    for (int r = 1; r <= 2; ++r) {
+        const int rows = kx_rows_per_block(r), per_cu = r == 1 ? 2 : 1;
+        const double blocks = (double)((n + rows - 1) / rows) * groups;
+        for (int ns = 1; ns <= 16 && ns <= chunks; ++ns) {
+            if (big && ns != 8 && ns != 16) continue;
+            const double load = blocks * ns / (256.0 * per_cu);          // rounds
+            const double chunk_us = (r == 1 ? (load <= 0.5 ? 2.4 : 3.7) : 3.6) * nsb / 4.0;
+            const double us = std::ceil(load) * std::ceil((double)chunks / ns) * chunk_us +
+                              (double)ns * n * s * 2.0 * part_bytes / 4.5e6;
+            if (us < best) {
+                best = us;
+                rt = r;
+                nsplit = ns;
+            }
+        }
+    }
+}
+
+}  // namespace ciq
