@@ -24,6 +24,7 @@ struct IterState {
     int done;       // 1 once every column stopped or iter reached the cap
     int live;       // 1 if the current iteration's scalar stage ran
     int numeric;    // 1 if a NaN/Inf Lanczos scalar was seen
+    unsigned long long tick;   // problems settled this iteration (low half), columns left (high half)
 };
 
 struct ShiftCoef {          // per (shift, column), written by the scalar stage
@@ -45,10 +46,10 @@ struct Dev {
     int bounds_mode;        // 1: plain Lanczos (no shifts), record T
     // dots
     int dots_blocks;        // partial blocks per problem
-    int fuse_sums;          // consumers sum the dots partials themselves, the whole
-                            // block cooperating in a fixed order: bit 1 the scalar
-                            // stage (both sums), bit 2 inner-product phase 1
-                            // (alpha); each saves a column-sum launch
+    int fuse_sums;          // consumers sum the dots partials themselves: bit 1 the
+                            // scalar stage (beta^2), bit 2 inner-product phase 1 and
+                            // the scalar stage (alpha, in one fixed order); each
+                            // saves a column-sum launch
     double* dots;           // [nprob][dots_blocks][s][2] (alpha, beta^2 partials)
     double* colsum;         // [2][ncol]: block-summed alpha, beta^2
     // column state
@@ -62,6 +63,8 @@ struct Dev {
     int* colactive;         // column still iterating
     int* col_iters;         // iterations per column
     int* prob_done;         // [nprob]
+    unsigned long long* ptick;   // [nprob] blocks settled this iteration (low half), columns left (high half)
+    int* queue;             // persistent product's work counter, cleared for the next one (or nullptr)
     double* T;              // bounds mode: [max_iter][ncol][2] (alpha, beta_next)
     // shift state [Q * ncol]
     double *c1, *s1, *c2, *s2, *phibar, *relres;
@@ -163,6 +166,7 @@ struct MvmArgs {
     const int* prob_done;    // [nprob] or nullptr
     const int* done;         // global done flag or nullptr
     int* queue;              // batched FP32 products: persistent work counter (nullptr: one block per item)
+    int queue_clean;         // 1: the counter is already zero for the first launch
     int nitems;              // work items = nrb * nsplit
     const long long* pkt;    // batched resident FP32: per-problem element offset of its matrix in kt
     const long long* pnjs;   // per-problem padded columns / 4
@@ -235,6 +239,12 @@ hipError_t launch_mvm_x3_rbf(const MvmArgs& a, int nsb, int grid_x, bool half, h
 hipError_t launch_mvm_x3_m52(const MvmArgs& a, int nsb, int grid_x, bool half, hipStream_t st);
 int mvm_rows_per_block(int dtype, int s, int rt);
 int mvm_pick_nsplit(int dtype, int nrb, int n_max, int s);
+struct SplitModel {
+    double t_blk, lat;       // us per 64-column chunk of a block (see model_nsplit)
+    int per_cu;              // blocks a CU holds
+};
+int model_nsplit(double blocks, int chunks, const SplitModel& m, double part_us, int max_split, double* us = nullptr);
+SplitModel mvm_split_model(int dtype, bool cached, int n, int nsb, int rt);
 hipError_t launch_mvm(int dtype, const MvmArgs& a, hipStream_t st);
 
 template <typename TI>
@@ -257,6 +267,11 @@ hipError_t launch_dots(const Dev& d, T* y, long long ysplit, int nsplit, const T
 hipError_t launch_colsum(const Dev& d, int k, hipStream_t st);
 hipError_t launch_scalar_init(const Dev& d, hipStream_t st);
 hipError_t launch_scalar(const Dev& d, hipStream_t st);
+
+// Small problems: everything after the product in one launch (kernels.hip).
+bool step_owner_ok(const Dev& d, int max_n);
+hipError_t launch_step_owner(const Dev& d, const double* y, long long ysplit, int nsplit, const double* q, double* qp,
+                             float* q32, int max_n, hipStream_t st, const float* y32, Op16 op);
 
 // q32 (nullable): FP32 copy of the next Lanczos vector, the FP32 product's operand
 // pnext (nullable): preconditioned form. Then y holds the finished direction
@@ -300,6 +315,10 @@ hipError_t launch_op16_split(const double* x, int n, int s, int ld, double* scal
 template <typename TI, typename TO>
 hipError_t launch_copy(const TI* src, int ld_src, int n, int s, TO* dst, int ld_dst,
                        hipStream_t st);
+
+// dst (n x sd doubles, contiguous) from src (n x s, ld_src): columns past s zero
+template <typename TI>
+hipError_t launch_copy_pad(const TI* src, int ld_src, int n, int s, double* dst, int sd, hipStream_t st);
 
 template <typename T>
 hipError_t launch_fill(T* p, size_t count, T value, hipStream_t st);
@@ -414,7 +433,7 @@ int grad_k_pad(int k);
 // U/V rows: [w_q g_q(i,:) | -G(i,:)] and [a_q(i,:) | A(i,:)], zero padded to
 // grad_rows_pad(n) x grad_k_pad((Q + sqrt_mode) * s)
 template <typename T>
-hipError_t launch_build_uv(const double* gq, const T* aq, const T* g, int ldg, const double* w_dev, int n,
+hipError_t launch_build_uv(const double* gq, int sg, const T* aq, const T* g, int ldg, const double* w_dev, int n,
                            int Q, int s, int sqrt_mode, double* U, double* V, hipStream_t st);
 // partial[block][0..dp) = sum W_ij h (u_id - u_jd)^2, [dp] = sum W_ij k, [dp+1] = sum W_ii
 hipError_t launch_grad_pass(int kernel, const double* U, const double* V, int kpad, const double* pts,

@@ -30,9 +30,10 @@ constexpr int TN = 64;      // columns (j) per block
 constexpr double kSqrt5d = 2.23606797749978969640917366873;
 
 // U[i][k], V[i][k] with k = q*s + c (+ Q*s + c for the square-root block),
-// rows padded to rows_pad and k padded to kpad with zeros.
+// rows padded to rows_pad and k padded to kpad with zeros (gq: sg columns per
+// shift, aq: s).
 template <typename T>
-__global__ void build_uv_kernel(const double* gq, const T* aq, const T* g, int ldg, const double* w, int n,
+__global__ void build_uv_kernel(const double* gq, int sg, const T* aq, const T* g, int ldg, const double* w, int n,
                                 int Q, int s, int sqrt_mode, int kpad, int rows_pad, double* U, double* V) {
     const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= (long long)rows_pad * kpad) return;
@@ -41,7 +42,7 @@ __global__ void build_uv_kernel(const double* gq, const T* aq, const T* g, int l
     if (i < n) {
         if (k < Q * s) {
             const int q = k / s, c = k - q * s;
-            u = w[q] * gq[((long long)i * Q + q) * s + c];
+            u = w[q] * gq[((long long)i * Q + q) * sg + c];
             v = (double)aq[((long long)i * Q + q) * s + c];
         } else if (sqrt_mode && k < (Q + 1) * s) {
             const int c = k - Q * s;
@@ -194,18 +195,18 @@ int grad_rows_pad(int n) { return ((n + 63) / 64) * 64; }
 int grad_k_pad(int k) { return ((k + KC - 1) / KC) * KC; }
 
 template <typename T>
-hipError_t launch_build_uv(const double* gq, const T* aq, const T* g, int ldg, const double* w_dev, int n, int Q,
+hipError_t launch_build_uv(const double* gq, int sg, const T* aq, const T* g, int ldg, const double* w_dev, int n, int Q,
                            int s, int sqrt_mode, double* U, double* V, hipStream_t st) {
     const int kpad = grad_k_pad((Q + (sqrt_mode ? 1 : 0)) * s);
     const int rows = grad_rows_pad(n);
     const long long total = (long long)rows * kpad;
-    hipLaunchKernelGGL(build_uv_kernel<T>, dim3((int)((total + 255) / 256)), dim3(256), 0, st, gq, aq, g, ldg,
+    hipLaunchKernelGGL(build_uv_kernel<T>, dim3((int)((total + 255) / 256)), dim3(256), 0, st, gq, sg, aq, g, ldg,
                        w_dev, n, Q, s, sqrt_mode, kpad, rows, U, V);
     return hipGetLastError();
 }
-template hipError_t launch_build_uv<float>(const double*, const float*, const float*, int, const double*, int, int,
+template hipError_t launch_build_uv<float>(const double*, int, const float*, const float*, int, const double*, int, int,
                                            int, int, double*, double*, hipStream_t);
-template hipError_t launch_build_uv<double>(const double*, const double*, const double*, int, const double*, int,
+template hipError_t launch_build_uv<double>(const double*, int, const double*, const double*, int, const double*, int,
                                             int, int, int, double*, double*, hipStream_t);
 
 hipError_t launch_grad_pass(int kernel, const double* U, const double* V, int kpad, const double* pts, int n,

@@ -314,6 +314,8 @@ void tune_cache_store(const TuneKey& k, const TuneVal& v) {
     std::fclose(f);
 }
 
+// "model": the column ranges of single problems follow model_nsplit (winners
+// timed with other ranges have another key).
 std::string device_arch() {
     int dev = 0;
     hipDeviceProp_t prop;
@@ -322,7 +324,7 @@ std::string device_arch() {
         return "unknown";
     }
     char b[160];
-    std::snprintf(b, sizeof(b), "%s/%dcu", prop.gcnArchName, prop.multiProcessorCount);
+    std::snprintf(b, sizeof(b), "%s/%dcu/model", prop.gcnArchName, prop.multiProcessorCount);
     for (char* c = b; *c; ++c)
         if (*c == ' ' || *c == '=') *c = '_';
     return b;
@@ -724,6 +726,7 @@ struct Run {
         d.colactive = a.template take<int>(ncol);
         d.col_iters = a.template take<int>(ncol);
         d.prob_done = a.template take<int>(nprob);
+        d.ptick = a.template take<unsigned long long>(nprob);
         d.T = bounds_mode ? a.template take<double>((size_t)std::max(max_iter, 1) * ncol * 2) : nullptr;
         const size_t qn = (size_t)std::max(Q, 1) * ncol;
         d.c1 = a.template take<double>(qn);
@@ -748,44 +751,55 @@ struct Run {
         const bool kx = parts() == 3;
         int kx_split = 1;
         if (kx) kx_plan(max_n, s, part32 ? 4 : 8, rt, kx_split);
-        {   // ~8 rows per thread in the inner-product kernels, at most 512
-            // blocks: their partials are summed per column by single-block
-            // stages, and at N = 50,000, S = 64 a step with 512 blocks takes
+        {   // One row per thread in the inner-product kernels up to 128 blocks,
+            // then ~8 rows, at most 512 blocks: their partials are summed per
+            // column, and at N = 50,000, S = 64 a step with 512 blocks takes
             // 12-14 us less than with 1024 (256 leave the passes short of
-            // loads in flight; measured). The scalar stage sums both inner
-            // products' block partials itself; with few blocks phase 1 sums
-            // the alpha partials itself too. The preconditioned step reads
+            // loads in flight; measured). Where the partials are few phase 1
+            // sums the alpha partials itself. The preconditioned step reads
             // the block-summed alpha (colsum) and writes beta^2 there itself.
             int ts = 1;
             while (ts < s && ts < 64) ts <<= 1;
             const int rows_per_pass = 256 / ts;
-            d.dots_blocks = std::min(512, std::max(1, (max_n + rows_per_pass * 8 - 1) / (rows_per_pass * 8)));
-            d.fuse_sums = precond ? 0 : (d.dots_blocks <= 32 ? 3 : 1);
+            const int passes = (max_n + rows_per_pass - 1) / rows_per_pass;
+            d.dots_blocks = std::max(1, std::min(512, std::max(std::min(passes, 128), (passes + 7) / 8)));
+            d.fuse_sums = precond ? 0 : (d.dots_blocks * std::min(s, 64) <= 4096 ? 3 : 1);
         }
         const int rpb = rows_per_block();
         nrb = 0;
         for (int p = 0; p < nprob; ++p) nrb += (h_n[p] + rpb - 1) / rpb;
         nsplit = mvm_pick_nsplit(dtype, nrb, max_n, s);
-        if (cached && (max_n + 63) / 64 >= 16 && nrb * 8 >= 512) {
-            // m column ranges per XCD (split = block index mod 8 picks the XCD):
-            // m = 2 when it fills the last round of equal-cost blocks on the
-            // XCD's 32 CUs enough to pay for 8 more partial products (each
-            // one more N x S FP64 write and read, ~0.2 % of a product); at
-            // most 2, so the V slices an XCD streams stay within its L2
-            const int nsb = (std::min(s, product_cap(dtype, true)) + 15) / 16;
-            const int bpc = kt_blocks_per_cu(dtype, nsb, rt, fine_acc);
-            int m = 1;
-            if (bpc > 0) {
-                const double slots = 32.0 * bpc;
-                auto fill = [&](int mm) {
-                    const double work = (double)nrb * mm;
-                    return work / (std::ceil(work / slots) * slots) - 0.002 * 8 * (mm - 1);
-                };
-                if (fill(2) > fill(1) + 0.01) m = 2;
+        const int chunks = (max_n + 63) / 64;
+        if (nprob == 1 && !kx) {
+            const int cap = product_cap(dtype, cached);
+            const int nsb = (std::min(s, cap) + 15) / 16;
+            SplitModel m = mvm_split_model(dtype, cached, max_n, nsb, rt);
+            const int bpc = cached ? kt_blocks_per_cu(dtype, nsb, rt, fine_acc) : 0;
+            if (bpc > 0) m.per_cu = bpc;
+            if (cached && (double)max_n * s * 8.0 > 1.2e7 && chunks >= 16 && nrb * 8 >= 512) {
+                // V is several times an XCD's L2: m column ranges per XCD
+                // (split = block index mod 8 picks the XCD); m = 2 when it
+                // fills the last round of equal-cost blocks on the XCD's 32
+                // CUs enough to pay for 8 more partial products (each one
+                // more N x S FP64 write and read, ~0.2 % of a product); at
+                // most 2, so the V slices an XCD streams stay within its L2
+                int mm = 1;
+                if (bpc > 0) {
+                    const double slots = 32.0 * bpc;
+                    auto fill = [&](int k) {
+                        const double work = (double)nrb * k;
+                        return work / (std::ceil(work / slots) * slots) - 0.002 * 8 * (k - 1);
+                    };
+                    if (fill(2) > fill(1) + 0.01) mm = 2;
+                }
+                nsplit = 8 * mm;
+            } else {
+                // a range costs the step 0.3 us beside its bytes (a line a
+                // cycle of one CU in the one-launch step)
+                const double part_us = std::max(0.3, s >= 4 && max_n <= 1024 ? max_n / 2200.0 : 0.0) +
+                                       (double)max_n * s * 2.0 * (part32 ? 4 : 8) / 3e6;
+                nsplit = model_nsplit((double)nrb * ((s + cap - 1) / cap), chunks, m, part_us, 16);
             }
-            nsplit = 8 * m;
-        } else if (cached && (max_n + 63) / 64 >= 8 && nrb * 8 >= 512) {
-            nsplit = 8;   // one column range per XCD
         }
         if (kx) nsplit = kx_split;
         if (nprob > 1 && nsplit_fixed > 0) nsplit = nsplit_fixed;
@@ -820,6 +834,7 @@ struct Run {
         d.tol = tol;
         d.bd_rtol = (dtype == CIQ_F64) ? 1e-13 : 1e-6;
         d.bounds_mode = bounds_mode;
+        d.queue = (nprob > 1) ? queue : nullptr;
     }
 
     // Work list: every problem's row blocks, largest problem first (its items
@@ -920,8 +935,15 @@ struct Run {
                                          pnxt, op16()));
             return CIQ_OK;
         }
-        HIPCHK(launch_dots<double>(d, ypart, ysplit, nsplit, qcur, qprv, 0, st,   // also reduces the splits
-                                   (part32 && nsplit > 1) ? ypart32 : nullptr));
+        const float* y32 = (part32 && nsplit > 1) ? ypart32 : nullptr;
+        if (step_owner_ok(d, max_n)) {
+            HIPCHK(launch_step_owner(d, ypart, ysplit, nsplit, qcur, qprv, q32, max_n, st, y32, op16()));
+            if (Q > 0 && d.basis == nullptr)   // the direction recurrence's vectors
+                HIPCHK(launch_update<double>(d, nullptr, 0, 1, qcur, qprv, mprv, mcur, acc, solves, nullptr, max_n,
+                                             st));
+            return CIQ_OK;
+        }
+        HIPCHK(launch_dots<double>(d, ypart, ysplit, nsplit, qcur, qprv, 0, st, y32));   // also reduces the splits
         HIPCHK(launch_colsum(d, 0, st));
         HIPCHK(launch_dots<double>(d, ypart, ysplit, 1, qcur, qprv, 1, st));
         HIPCHK(launch_colsum(d, 1, st));
@@ -955,6 +977,7 @@ struct Run {
             return CIQ_OK;
         }
         MvmArgs a = mvm_args(operand(j), ypart);
+        a.queue_clean = 1;       // cleared by the scalar stage before
         if (part32 && nsplit > 1) a.y32 = ypart32;
         HIPCHK(launch_mvm(dtype, a, st));
         return CIQ_OK;
@@ -1312,6 +1335,13 @@ int kcache_build(Run<T>& r, const KCache& kc, hipStream_t st) {
     return CIQ_OK;
 }
 
+// Columns a Krylov run works on for s right-hand sides: three or more are
+// padded with zero columns (which never start: a zero column of B has a zero
+// result) to a multiple of four, so the vector passes move 16 bytes a lane
+// whatever s is; the padding is within the 16-column blocks that the products
+// compute anyway.
+int run_cols(int s) { return s <= 2 ? s : (s + 3) / 4 * 4; }
+
 struct ScratchLock {
     std::unique_lock<std::mutex> lk;
     explicit ScratchLock(int dev) : lk(g_scratch[dev].mu) {}
@@ -1348,7 +1378,8 @@ int solve(int nprob, const ciq_problem* probs, const ciq_opts* o, const void* co
     main.sp = sparse;
     main.dn = dense;
     main.dtype = dtype;
-    main.s = s;
+    const int sr = run_cols(s);
+    main.s = sr;
     main.Q = o->q;
     main.max_iter = o->max_iter;
     main.tol = o->tol;
@@ -1409,7 +1440,7 @@ int solve(int nprob, const ciq_problem* probs, const ciq_opts* o, const void* co
     if (precond || post_spec) HIPCHK(hipStreamSynchronize(st));
     const auto setup_t0 = std::chrono::steady_clock::now();
     if (precond) {
-        STCHK(pc_build(probs[0], main.xh, main.dp, main.kernel, main.ard, main.h_scale.data(), o->precond_rank, s,
+        STCHK(pc_build(probs[0], main.xh, main.dp, main.kernel, main.ard, main.h_scale.data(), o->precond_rank, sr,
                        pc, st));
         main.pc = &pc;
         bnd.pc = &pc;
@@ -1424,7 +1455,7 @@ int solve(int nprob, const ciq_problem* probs, const ciq_opts* o, const void* co
     }
     if (post_spec) {
         STCHK(post_build(probs[0], dtype, main.xh, main.dp, main.kernel, main.ard, main.h_scale.data(), *post_spec,
-                         s, po, st));
+                         sr, po, st));
         main.post = &po;
         bnd.post = &po;
     }
@@ -1502,14 +1533,14 @@ int solve(int nprob, const ciq_problem* probs, const ciq_opts* o, const void* co
 
     // ---- right-hand sides --------------------------------------------------
     for (int p = 0; p < nprob; ++p)
-        HIPCHK((launch_copy<T, double>(static_cast<const T*>(b_ptrs[p]), ldb, main.h_n[p], s,
-                                       main.qbuf[0] + (size_t)main.h_off[p] * s, s, st)));
+        HIPCHK(launch_copy_pad<T>(static_cast<const T*>(b_ptrs[p]), ldb, main.h_n[p], s,
+                                  main.qbuf[0] + (size_t)main.h_off[p] * sr, sr, st));
     HIPCHK(hipStreamSynchronize(st));  // th/wh are pageable host vectors
     if (precond)   // start vectors C = P^{1/2} B (Appendix D), in place
-        STCHK(pc_apply(pc, std::sqrt(pc.s2), pc.fsq, main.qbuf[0], main.rows_total, s, main.qbuf[0], nullptr, nullptr,
+        STCHK(pc_apply(pc, std::sqrt(pc.s2), pc.fsq, main.qbuf[0], main.rows_total, sr, main.qbuf[0], nullptr, nullptr,
                        nullptr, st));
     if (main.q32) {
-        HIPCHK((launch_copy<double, float>(main.qbuf[0], s, main.rows_total, s, main.q32, s, st)));
+        HIPCHK((launch_copy<double, float>(main.qbuf[0], sr, main.rows_total, sr, main.q32, sr, st)));
         STCHK(tune_rt(main, main.q32, st));
     } else {
         if (main.vt16)   // the trial launches read the split operand: give them zeros
@@ -1524,7 +1555,7 @@ int solve(int nprob, const ciq_problem* probs, const ciq_opts* o, const void* co
     if (o->krylov_basis == CIQ_BASIS_AUTO && !precond && solves_out == nullptr && main.Q > 0) {
         BasisPool& bp = g_basis[dev];
         const size_t slots = (size_t)main.max_iter + 1;
-        const size_t stride = ((size_t)main.rows_total * s * sizeof(double) + 255) & ~size_t(255);
+        const size_t stride = ((size_t)main.rows_total * sr * sizeof(double) + 255) & ~size_t(255);
         const size_t chunk = basis_chunk_bytes(stride);
         if (bp.chunk_bytes != chunk) {   // another chunk size: start the pool over
             STCHK(basis_pool_release(dev));
@@ -1597,40 +1628,40 @@ int solve(int nprob, const ciq_problem* probs, const ciq_opts* o, const void* co
     if (mode == CIQ_SQRT) {
         const void* operand = main.acc;
         if (main.q32) {
-            HIPCHK((launch_copy<double, float>(main.acc, s, main.rows_total, s, main.q32, s, st)));
+            HIPCHK((launch_copy<double, float>(main.acc, sr, main.rows_total, sr, main.q32, sr, st)));
             operand = main.q32;
         }
         if (main.vt16)   // the combined solution is not unit-norm: per-column scales
-            HIPCHK(launch_op16_split(main.acc, main.rows_total, s, s, main.opsc, main.opinv, main.vt16, main.nsbt,
+            HIPCHK(launch_op16_split(main.acc, main.rows_total, sr, sr, main.opsc, main.opinv, main.vt16, main.nsbt,
                                      main.parts(), st));
         MvmArgs a = main.mvm_args(operand, main.ypart);
         a.done = nullptr;
         a.prob_done = nullptr;
         if (main.vt16) a.vcol_inv = main.opinv;
         if (sparse)
-            HIPCHK(launch_spmv(*sparse, main.acc, s, s, main.ypart, s, nullptr, st));
+            HIPCHK(launch_spmv(*sparse, main.acc, sr, sr, main.ypart, sr, nullptr, st));
         else if (dense)
-            HIPCHK(launch_lr_apply(0.0, nullptr, 0, dense->A, dense->n, main.acc, s, main.rows_total, dense->n, s,
-                                   main.ypart, s, nullptr, nullptr, nullptr, st));
+            HIPCHK(launch_lr_apply(0.0, nullptr, 0, dense->A, dense->n, main.acc, sr, main.rows_total, dense->n, sr,
+                                   main.ypart, sr, nullptr, nullptr, nullptr, st));
         else
             HIPCHK(launch_mvm(dtype, a, st));
         STCHK(main.post_correct(main.acc, nullptr, st));
         mvm_count += 1;
         for (int p = 0; p < nprob; ++p)
-            HIPCHK(launch_reduce_splits<T>(main.ypart + (size_t)main.h_off[p] * s, main.ysplit, main.nsplit, s,
+            HIPCHK(launch_reduce_splits<T>(main.ypart + (size_t)main.h_off[p] * sr, main.ysplit, main.nsplit, sr,
                                            main.h_n[p], s, static_cast<T*>(out_ptrs[p]), ldo, st));
     } else {
         for (int p = 0; p < nprob; ++p)
-            HIPCHK((launch_copy<double, T>(main.acc + (size_t)main.h_off[p] * s, s, main.h_n[p], s,
+            HIPCHK((launch_copy<double, T>(main.acc + (size_t)main.h_off[p] * sr, sr, main.h_n[p], s,
                                            static_cast<T*>(out_ptrs[p]), ldo, st)));
     }
     if (solves_out) {
-        HIPCHK((launch_copy<double, T>(main.solves, s, main.rows_total * main.Q, s, static_cast<T*>(solves_out),
+        HIPCHK((launch_copy<double, T>(main.solves, sr, main.rows_total * main.Q, s, static_cast<T*>(solves_out),
                                        s, st)));
     }
 
     // ---- report ------------------------------------------------------------
-    const int ncol = nprob * s;
+    const int ncol = nprob * sr;
     const size_t qn = (size_t)main.Q * ncol;
     std::vector<int> frozen(qn), citers(ncol);
     std::vector<double> relres(qn);
@@ -1646,7 +1677,7 @@ int solve(int nprob, const ciq_problem* probs, const ciq_opts* o, const void* co
         int it = 0, conv = 1;
         double mr = 0.0;
         for (int c = 0; c < s; ++c) {
-            const int g = p * s + c;
+            const int g = p * sr + c;
             it = std::max(it, citers[g]);
             for (int q = 0; q < main.Q; ++q) {
                 const size_t idx = (size_t)q * ncol + g;
@@ -1712,7 +1743,8 @@ int backward_impl(const ciq_problem* p, const ciq_opts* o, int mode, const doubl
     Run<T> r;
     fill_problem_tables(r, p, 1, dtype);
     r.dtype = dtype;
-    r.s = s;
+    const int sr = run_cols(s);
+    r.s = sr;
     r.Q = Q;
     r.max_iter = o->max_iter;
     r.tol = o->tol;
@@ -1750,22 +1782,21 @@ int backward_impl(const ciq_problem* p, const ciq_opts* o, int mode, const doubl
     HIPCHK(hipMemcpyAsync(r.w, w, Q * sizeof(double), hipMemcpyHostToDevice, st));
 
     // G' into the first Lanczos buffer (FP64)
+    HIPCHK(launch_copy_pad<T>(static_cast<const T*>(g), ldg, n, s, r.qbuf[0], sr, st));
     if (sqrt_mode) {
-        MvmArgs a = r.mvm_args(g, r.ypart);
-        a.ldv = ldg;
-        a.done = nullptr;
+        const void* operand = r.qbuf[0];
         if (r.vt16) {
-            HIPCHK((launch_copy<T, double>(static_cast<const T*>(g), ldg, n, s, r.qbuf[0], s, st)));
             HIPCHK(launch_fill<int>(static_cast<int*>(r.vt16), r.op_words(), 0, st));
-            HIPCHK(launch_op16_split(r.qbuf[0], n, s, s, r.opsc, r.opinv, r.vt16, r.nsbt, r.parts(), st));
-            a.v = r.qbuf[0];
-            a.ldv = s;
-            a.vcol_inv = r.opinv;
+            HIPCHK(launch_op16_split(r.qbuf[0], n, sr, sr, r.opsc, r.opinv, r.vt16, r.nsbt, r.parts(), st));
+        } else if (r.q32) {
+            HIPCHK((launch_copy<double, float>(r.qbuf[0], sr, n, sr, r.q32, sr, st)));
+            operand = r.q32;
         }
+        MvmArgs a = r.mvm_args(operand, r.ypart);
+        a.done = nullptr;
+        if (r.vt16) a.vcol_inv = r.opinv;
         HIPCHK(launch_mvm(dtype, a, st));
-        HIPCHK(launch_reduce_splits<double>(r.ypart, r.ysplit, r.nsplit, s, n, s, r.qbuf[0], s, st));
-    } else {
-        HIPCHK((launch_copy<T, double>(static_cast<const T*>(g), ldg, n, s, r.qbuf[0], s, st)));
+        HIPCHK(launch_reduce_splits<double>(r.ypart, r.ysplit, r.nsplit, sr, n, sr, r.qbuf[0], sr, st));
     }
     HIPCHK(hipStreamSynchronize(st));   // t/w came from caller-owned host memory
     int mvm_count = sqrt_mode ? 1 : 0, dummy_n = 0;
@@ -1773,7 +1804,7 @@ int backward_impl(const ciq_problem* p, const ciq_opts* o, int mode, const doubl
     STCHK(r.iterate(st, o->check_every > 0 ? o->check_every : 16, pinned, &mvm_count, nullptr, 0, &dummy,
                     &dummy_n));
     const int iters = pinned->iter;
-    if (db) HIPCHK((launch_copy<double, T>(r.acc, s, n, s, static_cast<T*>(db), lddb, st)));
+    if (db) HIPCHK((launch_copy<double, T>(r.acc, sr, n, s, static_cast<T*>(db), lddb, st)));
 
     double acc_h[CIQ_MAX_D + 2] = {0};
     if (want_hyper) {
@@ -1782,7 +1813,7 @@ int backward_impl(const ciq_problem* p, const ciq_opts* o, int mode, const doubl
         double scale[CIQ_MAX_D];
         for (int k = 0; k < p->d; ++k) scale[k] = 1.0 / p->lengthscale[p->n_lengthscale == 1 ? 0 : k];
         HIPCHK(launch_prep<double>(xd, n, p->d, dpg, scale, pts, st));
-        HIPCHK(launch_build_uv<T>(r.solves, static_cast<const T*>(solves), static_cast<const T*>(g), ldg, r.w, n,
+        HIPCHK(launch_build_uv<T>(r.solves, sr, static_cast<const T*>(solves), static_cast<const T*>(g), ldg, r.w, n,
                                   Q, s, sqrt_mode ? 1 : 0, U, V, st));
         int nblocks = 0;
         HIPCHK(launch_grad_pass(p->kernel, U, V, kpad, pts, n, dpg, part, &nblocks, st));
@@ -1793,14 +1824,14 @@ int backward_impl(const ciq_problem* p, const ciq_opts* o, int mode, const doubl
             for (int k = 0; k < dpg + 2; ++k) acc_h[k] += hp[(size_t)b * (dpg + 2) + k];
     }
     // report of the backward msMINRES run
-    const size_t qn = (size_t)Q * s;
+    const size_t qn = (size_t)Q * sr;
     std::vector<double> relres(qn);
     HIPCHK(hipMemcpyAsync(relres.data(), r.d.relres, qn * sizeof(double), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     std::memset(info, 0, sizeof(*info));
     double mr = 0.0;
     int conv = 1;
-    for (double v : relres) {
+    for (double v : relres) {   // the padding columns' are zero
         mr = std::max(mr, v);
         if (!(v <= o->tol)) conv = 0;
     }
@@ -1833,20 +1864,45 @@ int backward_impl(const ciq_problem* p, const ciq_opts* o, int mode, const doubl
 
 // ---- on-the-fly kernel product (ciq_kernel_mvm and its allocation-free form)
 struct KmvmPlan {
-    int dp, nrb, nsplit;
+    int dp, nrb, nsplit, rt;
     bool direct;            // FP64 into y directly (one split, <= 64 columns)
     size_t xbytes, ybytes;  // scaled points (256-byte rounded), FP64 split partials
+    size_t bound;           // bytes that ciq_kernel_mvm_noalloc's documented limit counts
 };
 
+// Row tiles and column ranges by the model of mvm_split_model. The partials
+// stay within the allocation-free form's scratch wherever its documented bound
+// (the ranges of mvm_pick_nsplit) is met, so both forms run the same launch.
 KmvmPlan kmvm_plan(const ciq_problem* p, int dtype, int s) {
     KmvmPlan pl{};
     pl.dp = pad_dims(p->d, dtype);
-    const int rpb = mvm_rows_per_block(dtype, s, 2);
-    pl.nrb = (p->n + rpb - 1) / rpb;
-    pl.nsplit = mvm_pick_nsplit(dtype, pl.nrb, p->n, s);
     pl.xbytes = ((size_t)p->n * pl.dp * sizeof(double) + 255) & ~size_t(255);
+    const size_t one = (size_t)p->n * s * sizeof(double);
+    const int rpb2 = mvm_rows_per_block(dtype, s, 2);
+    const int ns2 = mvm_pick_nsplit(dtype, (p->n + rpb2 - 1) / rpb2, p->n, s);
+    pl.bound = pl.xbytes + ((dtype == CIQ_F64 && ns2 == 1 && s <= 64) ? 0 : ns2 * one);
+    const size_t room = std::max(pl.bound, (size_t)CIQ_NOALLOC_SCRATCH_BYTES) - pl.xbytes;
+    const int cap = product_cap(dtype, false);
+    const int nsb = (std::min(s, cap) + 15) / 16, groups = (s + cap - 1) / cap;
+    const int chunks = (p->n + 63) / 64;
+    double best = 1e300;
+    for (int rt = 1; rt <= 2; ++rt) {
+        const int rpb = mvm_rows_per_block(dtype, s, rt);
+        if (rt == 2 && rpb == mvm_rows_per_block(dtype, s, 1)) break;   // no two-tile form
+        const int nrb = (p->n + rpb - 1) / rpb;
+        const int max_split = (int)std::min<size_t>(16, std::max<size_t>(1, room / one));
+        double us = 0.0;
+        const int ns = model_nsplit((double)nrb * groups, chunks, mvm_split_model(dtype, false, p->n, nsb, rpb / 64),
+                                    one * 2.0 / 4.5e6, max_split, &us);
+        if (us < best) {
+            best = us;
+            pl.rt = rt;
+            pl.nrb = nrb;
+            pl.nsplit = ns;
+        }
+    }
     pl.direct = (dtype == CIQ_F64 && pl.nsplit == 1 && s <= 64);
-    pl.ybytes = pl.direct ? 0 : (size_t)pl.nsplit * p->n * s * sizeof(double);
+    pl.ybytes = pl.direct ? 0 : (size_t)pl.nsplit * one;
     return pl;
 }
 
@@ -1877,7 +1933,7 @@ int kmvm_run(const ciq_problem* p, int dtype, const void* v, int s, int ldv, voi
     a.kernel = p->kernel;
     a.dp = pl.dp;
     a.nsplit = pl.nsplit;
-    a.rt = 2;
+    a.rt = pl.rt;
     a.ard = 0;
     for (int k = 0; k < CIQ_MAX_D; ++k) {
         a.scale[k] = (k < p->d) ? scale[k] : 0.0;
@@ -1990,7 +2046,7 @@ int ciq_kernel_mvm_noalloc(const ciq_problem* p, int dtype, const void* v, int s
                            hipStream_t stream) {
     if (!valid_problem(p) || !valid_dtype(dtype) || !v || !y || s < 1 || ldv < s || ldy < s) return CIQ_EINVAL;
     const KmvmPlan pl = kmvm_plan(p, dtype, s);
-    if (pl.xbytes + pl.ybytes > (size_t)CIQ_NOALLOC_SCRATCH_BYTES) return CIQ_EINVAL;
+    if (pl.bound > (size_t)CIQ_NOALLOC_SCRATCH_BYTES) return CIQ_EINVAL;
     int dev;
     STCHK(get_device(&dev));
     void* buf = nullptr;

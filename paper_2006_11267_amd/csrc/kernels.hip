@@ -10,16 +10,13 @@
 //    quadrature-weighted solution accumulation).
 #include "ciq_internal.h"
 
+#include <algorithm>
 #include <cmath>
 #include <map>
 #include <mutex>
 #include <utility>
 
 namespace ciq {
-
-namespace {
-
-}  // namespace
 
 int mvm_rows_per_block(int dtype, int s, int rt) {
     if (dtype == CIQ_F64) return 64 * rt;            // FP64 MFMA: column groups of <= 64
@@ -28,9 +25,62 @@ int mvm_rows_per_block(int dtype, int s, int rt) {
     return (nsb <= 4 && rt == 2) ? 128 : 64;
 }
 
+// Column ranges of a product from a model of its time. A block of a launch
+// takes t_blk per 64-column chunk when the CU works on per_cu of them at its
+// full rate, and at least lat when it is alone (the latency of its loads and
+// of its chain of instructions); equal blocks go round by round over 256 CUs;
+// every range costs its partials (part_us: written once, read once). All in
+// microseconds; *us (nullable): the modelled time.
+int model_nsplit(double blocks, int chunks, const SplitModel& m, double part_us, int max_split, double* us) {
+    double best = 1e300;
+    int pick = 1;
+    for (int ns = 1; ns <= max_split && ns <= chunks; ++ns) {
+        const double load = blocks * ns / 256.0;
+        const int per = (int)std::min((double)m.per_cu, std::ceil(load));
+        const double r = load / m.per_cu;
+        const double rounds = r > 4.0 ? r + 0.5 : std::ceil(r);
+        const double t = rounds * std::ceil((double)chunks / ns) * std::max(m.lat, per * m.t_blk) + ns * part_us;
+        if (t < best) {
+            best = t;
+            pick = ns;
+        }
+    }
+    if (us) *us = best;
+    return pick;
+}
+
+// Model constants of the kernel products, fitted to the times measured at N =
+// 50,000 (all slots busy: matrix instructions per 16-column block of V, entry
+// evaluation or the stream of K per 64 rows) and at N = 1,024 (one block per
+// CU). A resident matrix of at most 200 MB is served by the last-level cache,
+// about twice as fast as HBM.
+SplitModel mvm_split_model(int dtype, bool cached, int n, int nsb, int rt) {
+    SplitModel m{};
+    m.per_cu = nsb <= 2 ? 4 : 2;
+    const double rows = rt;      // in units of 64
+    if (cached) {
+        const double bytes = kcache_bytes(n, dtype == CIQ_F64 ? 8 : 4);
+        const double k = rows * (dtype == CIQ_F64 ? 1.4 : 0.7) * (bytes <= 2e8 ? 0.55 : 1.0);
+        const double mfma = rows * nsb * (dtype == CIQ_F64 ? 0.47 : dtype == CIQ_F32 ? 0.4 : 0.1);
+        m.t_blk = std::max(k, mfma) + 0.1 * rows;
+        m.lat = 1.2;
+    } else if (dtype == CIQ_F64) {
+        m.t_blk = rows * (1.3 + 0.47 * nsb);
+        m.lat = 1.6 + 0.7 * rows;
+    } else if (dtype == CIQ_F32) {
+        m.t_blk = rows * (0.85 + 0.27 * nsb);
+        m.lat = 1.0 + 0.5 * rows;
+    } else {
+        m.t_blk = 1.6;
+        m.lat = 2.0;
+    }
+    return m;
+}
+
 // Split the j range so the number of equal-cost blocks fills the chip's
 // resident slots (256 CUs x blocks resident per CU, set by the kernel's
-// register use) with the least idle tail.
+// register use) with the least idle tail: batched runs before their tuner, and
+// the scratch bound of ciq_kernel_mvm_noalloc.
 int mvm_pick_nsplit(int dtype, int nrb, int n_max, int s) {
     const int cap = (dtype == CIQ_F32) ? 128 : 64;
     const int nsb = (s > cap ? cap : s + 15) / 16;
@@ -63,13 +113,21 @@ hipError_t launch_mvm(int dtype, const MvmArgs& a, hipStream_t st) {
         return hipErrorInvalidValue;
     if (dtype == CIQ_F32 && a.vt != nullptr)
         return a.kt != nullptr ? launch_mvm_kx(a, st) : hipErrorInvalidValue;
+    // The FP64 forms take several groups of 64 columns in one launch (more
+    // blocks to fill the chip: N = 3,000, S = 256 resident 137 -> 100 us); a
+    // remainder of at most 32 columns stays a launch of its own, which has a
+    // kernel of its width.
     const int cap = product_cap(dtype, a.kt != nullptr);
-    for (int c0 = 0; c0 < a.s; c0 += cap) {
+    const int rem = a.s % 64;
+    const int wide = (dtype == CIQ_F64) ? ((rem > 0 && rem <= 32) ? a.s - rem : a.s) : 0;
+    for (int c0 = 0; c0 < a.s;) {
         MvmArgs g = a;
-        g.s = (a.s - c0 < cap) ? a.s - c0 : cap;
+        const int take = (c0 < wide) ? wide : std::min(cap, a.s - c0);
+        g.s = take;
+        g.queue_clean = a.queue_clean && c0 == 0;
         g.y = static_cast<double*>(a.y) + c0;
         if (a.y32) g.y32 = a.y32 + c0;
-        const int nsb = (g.s + 15) / 16;
+        const int nsb = (std::min(take, cap) + 15) / 16;
         hipError_t e;
         if (dtype == CIQ_F16X3 && a.kt != nullptr) {
             g.v = static_cast<const double*>(a.v) + c0;
@@ -101,6 +159,7 @@ hipError_t launch_mvm(int dtype, const MvmArgs& a, hipStream_t st) {
                 e = a.ard ? launch_mvm_f32_m52_ard(g, nsb, a.nrb, st) : launch_mvm_f32_m52_iso(g, nsb, a.nrb, st);
         }
         if (e != hipSuccess) return e;
+        c0 += take;
     }
     return hipSuccess;
 }
@@ -176,12 +235,9 @@ __host__ __device__ inline int col_tile(int s) {
     return ts;
 }
 
-// Column sum k of the dots partials for global column g, in one fixed order
-// everywhere (colsum_kernel, and the consumers when fuse_sums is set): lane r
-// of 16 sums blocks r, r + 16, ...; then the 16 lane sums are added in lane
-// order. Fused and separate column sums are therefore bitwise equal.
-// Lane sum r (of 16): partials of blocks r, r + 16, ... added in that order
-// (eight loads issued before their adds).
+// Lane sum r (of 16) of column g's dots partials k: the partials of blocks r,
+// r + 16, ... added in that order (eight loads issued before their adds). The
+// 16 lane sums of a column are added in lane order.
 __device__ inline double colsum_lane(const Dev& d, int k, int g, int r) {
     const int p = g / d.s, c = g - p * d.s;
     const double* base = d.dots + ((long long)p * d.dots_blocks * d.s + c) * 2 + k;
@@ -200,29 +256,6 @@ __device__ inline double colsum_lane(const Dev& d, int k, int g, int r) {
     }
     return acc;
 }
-
-// colsum[k * ncol + g] (the fixed order above) for every column, by the whole
-// block (nt threads, nt a multiple of 64; sh: nt doubles of LDS): 64 columns
-// x nt/64 lanes, each lane computes lane sums r, r + nt/64, ...; the 16 lane
-// sums of a column are added in order. The results are
-// read by this block after a barrier.
-__device__ void block_colsums(const Dev& d, int k, int tid, int nt, double* sh) {
-    const int lanes = nt >> 6, cl = tid & 63, ln = tid >> 6;
-    for (int g0 = 0; g0 < d.ncol; g0 += 64) {
-        const int g = g0 + cl;
-        __syncthreads();
-        for (int r = ln; r < 16; r += lanes) sh[r * 64 + cl] = (g < d.ncol) ? colsum_lane(d, k, g, r) : 0.0;
-        __syncthreads();
-        if (ln == 0 && g < d.ncol) {
-            double t = 0.0;
-            for (int r = 0; r < 16; ++r) t += sh[r * 64 + cl];
-            d.colsum[(long long)k * d.ncol + g] = t;
-        }
-    }
-    __syncthreads();
-}
-
-__device__ void scalar_stage(const Dev& d, int tid, int nt, int* active_cnt, int& any);
 
 template <typename T>
 __global__ __launch_bounds__(256) void dots_kernel(Dev d, T* y, long long ysplit, int nsplit,
@@ -320,12 +353,14 @@ __global__ __launch_bounds__(256) void dots_kernel(Dev d, T* y, long long ysplit
     }
 }
 
-// The same two passes for s in {4, 8, 16, 32, 64} with 16-byte loads: lane
-// (cg, rl) owns columns 4 cg .. 4 cg + 3 of rows rl, rl + RL, ... (RL = 1024 / s
-// rows per block pass), so one load instruction moves 1 KB per wave instead of
-// 256 or 512 bytes (the passes are bound by the bytes in flight). Per element
-// the arithmetic and the order over the split partials are those of
-// dots_kernel; the block partials sum the rows in another order.
+// The same two passes for s a multiple of 4 with 16-byte loads: lane (cg, rl)
+// owns columns 4 cg .. 4 cg + 3 of its column tile (grid.y) in rows rl, rl +
+// RL, ..., so one load instruction moves 1 KB per wave instead of 256 or 512
+// bytes (the passes are bound by the bytes in flight). Per element the
+// arithmetic and the order over the split partials are those of dots_kernel;
+// the block partials sum the rows in another order. Wider right-hand sides
+// than 64 columns, and widths that are no power of two, used to take
+// dots_kernel: 18 us a pass at N = 5,000, S = 256 against 9 here.
 typedef double dvec2 __attribute__((ext_vector_type(2)));
 typedef float fvec4 __attribute__((ext_vector_type(4)));
 
@@ -344,6 +379,8 @@ __device__ __forceinline__ void load4_nt(const float* p, float (&v)[4]) {
     v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
 }
 
+constexpr int kVecCols = 64;   // columns of a tile
+
 // PT: element type of the split partials (phase 0); U: rows per trip
 template <typename PT, int U, int phase>
 __global__ __launch_bounds__(256) void dots_vec_kernel(Dev d, double* y, const PT* yp, long long ysplit,
@@ -351,22 +388,24 @@ __global__ __launch_bounds__(256) void dots_vec_kernel(Dev d, double* y, const P
     __shared__ double sh[256 * 4];
     __shared__ double lsum[16 * 64];
     if (d.st->done) return;
-    const int s = d.s, CG = s >> 2, RL = 256 / CG;
+    const int s = d.s, c0 = blockIdx.y * kVecCols, sw = min(s - c0, kVecCols);   // this tile's columns
+    const int CG = sw >> 2, RL = 256 / CG;
     const int p = blockIdx.z;
+    if (d.prob_done[p]) return;                   // a batched problem that has stopped
     const int n = d.n[p], off = d.row_off[p];
     const int cg = threadIdx.x % CG, rl = threadIdx.x / CG;
-    const int c = 4 * cg, g = p * s + c;
+    const int c = c0 + 4 * cg, g = p * s + c;
     double al[4] = {0.0, 0.0, 0.0, 0.0};
     if constexpr (phase == 1) {
         if (d.fuse_sums & 2) {   // alpha_j from the phase-0 partials, colsum_lane's fixed order
-            for (int e = threadIdx.x; e < 16 * s; e += 256) {
-                const int r = e / s, col = e - r * s;
-                lsum[r * 64 + col] = colsum_lane(d, 0, p * s + col, r);
+            for (int e = threadIdx.x; e < 16 * sw; e += 256) {
+                const int r = e / sw, col = e - r * sw;
+                lsum[r * kVecCols + col] = colsum_lane(d, 0, p * s + c0 + col, r);
             }
             __syncthreads();
 #pragma unroll
             for (int k = 0; k < 4; ++k)
-                for (int r = 0; r < 16; ++r) al[k] += lsum[r * 64 + c + k];
+                for (int r = 0; r < 16; ++r) al[k] += lsum[r * kVecCols + 4 * cg + k];
         } else {
 #pragma unroll
             for (int k = 0; k < 4; ++k) al[k] = d.colsum[g + k];
@@ -376,7 +415,7 @@ __global__ __launch_bounds__(256) void dots_vec_kernel(Dev d, double* y, const P
 #pragma unroll
     for (int k = 0; k < 4; ++k) bj[k] = d.beta_cur[g + k];
     const int G = gridDim.x * RL;
-    for (int i0 = blockIdx.x * RL + rl; i0 < n; i0 += U * G) {
+    for (int i0 = (rl < RL) ? blockIdx.x * RL + rl : n; i0 < n; i0 += U * G) {
         double yv[U][4];
         if constexpr (phase == 0) {
             PT part[U][16][4];   // all of a trip's partials requested before they are added
@@ -437,11 +476,11 @@ __global__ __launch_bounds__(256) void dots_vec_kernel(Dev d, double* y, const P
 #pragma unroll
     for (int e = 0; e < 4; ++e) sh[threadIdx.x * 4 + e] = acc[e];
     __syncthreads();
-    if (threadIdx.x < s) {
+    if (threadIdx.x < sw) {
         const int col = threadIdx.x, cgc = col >> 2, e = col & 3;
         double sum = 0.0;
         for (int r = 0; r < RL; ++r) sum += sh[(r * CG + cgc) * 4 + e];
-        d.dots[(((long long)p * d.dots_blocks + blockIdx.x) * s + col) * 2 + phase] = sum;
+        d.dots[(((long long)p * d.dots_blocks + blockIdx.x) * s + c0 + col) * 2 + phase] = sum;
     }
 }
 
@@ -484,9 +523,8 @@ template <typename T>
 hipError_t launch_dots(const Dev& d, T* y, long long ysplit, int nsplit, const T* q, const T* qp,
                        int phase, hipStream_t st, const float* y32) {
     if (y32 != nullptr && (phase != 0 || nsplit > 16)) return hipErrorInvalidValue;
-    const bool vec_s = d.s == 4 || d.s == 8 || d.s == 16 || d.s == 32 || d.s == 64;
-    if (sizeof(T) == 8 && q != nullptr && qp != nullptr && vec_s && nsplit <= 16 && (phase == 0 || nsplit == 1)) {
-        dim3 grid(d.dots_blocks, 1, d.nprob);
+    if (sizeof(T) == 8 && q != nullptr && qp != nullptr && d.s % 4 == 0 && nsplit <= 16 && (phase == 0 || nsplit == 1)) {
+        dim3 grid(d.dots_blocks, (d.s + kVecCols - 1) / kVecCols, d.nprob);
         double* yd = reinterpret_cast<double*>(y);
         const double* qd = reinterpret_cast<const double*>(q);
         const double* qpd = reinterpret_cast<const double*>(qp);
@@ -510,15 +548,28 @@ template hipError_t launch_dots<double>(const Dev&, double*, long long, int, con
                                         const float*);
 
 // ----------------------------------------------------------------------------
-// Scalar stage (single block, FP64). Initial form: beta_1 = ||b||.
+// Scalar stage (FP64). Initial form (single block): beta_1 = ||b||.
 // ----------------------------------------------------------------------------
 __global__ __launch_bounds__(1024) void scalar_init_kernel(Dev d) {
     __shared__ int any;
     __shared__ double sh[1024];
-    if (d.fuse_sums & 1) block_colsums(d, 1, threadIdx.x, blockDim.x, sh);
     if (threadIdx.x == 0) any = 0;
-    __syncthreads();
     const int ncol = d.ncol, Q = d.Q;
+    if (d.fuse_sums & 1) {   // sums of the block partials: 64 columns x 16 lanes at a time
+        const int cl = threadIdx.x & 63, r = threadIdx.x >> 6;
+        for (int g0 = 0; g0 < ncol; g0 += 64) {
+            const int g = g0 + cl;
+            __syncthreads();
+            sh[r * 64 + cl] = (g < ncol) ? colsum_lane(d, 1, g, r) : 0.0;
+            __syncthreads();
+            if (r == 0 && g < ncol) {
+                double t = 0.0;
+                for (int k = 0; k < 16; ++k) t += sh[k * 64 + cl];
+                d.colsum[ncol + g] = t;
+            }
+        }
+    }
+    __syncthreads();
     for (int g = threadIdx.x; g < ncol; g += blockDim.x) {
         const double b1 = sqrt(d.colsum[ncol + g]);
         const bool ok = (b1 > 0.0) && isfinite(b1);
@@ -542,12 +593,15 @@ __global__ __launch_bounds__(1024) void scalar_init_kernel(Dev d) {
         int act = 0;
         for (int c = 0; c < d.s; ++c) act |= d.colactive[p * d.s + c];
         d.prob_done[p] = act ? 0 : 1;
+        d.ptick[p] = 0;
     }
     if (threadIdx.x == 0) {
         d.st->iter = 0;
         d.st->live = 0;
         d.st->numeric = 0;
+        d.st->tick = 0;
         d.st->done = (any && d.max_iter > 0) ? 0 : 1;
+        if (d.queue) *d.queue = 0;
     }
 }
 
@@ -565,137 +619,202 @@ hipError_t launch_scalar_init(const Dev& d, hipStream_t st) {
 //           tau = c phibar, phibar <- -s phibar
 // Stopping: shift frozen at |phibar|/||b|| <= tol; column stops when all its
 // shifts are frozen or beta_{j+1} breaks down; run stops at max_iter.
-// The body, run by all `nt` threads of one block (active_cnt: nprob ints and
-// `any` in that block's LDS); the caller has checked that the run is live and
-// colsum holds the column sums of both inner products.
-__device__ void scalar_stage(const Dev& d, int tid, int nt, int* active_cnt, int& any) {
-    IterState* st = d.st;
-    const int ncol = d.ncol, Q = d.Q, s = d.s;
-    for (int p = tid; p < d.nprob; p += nt) active_cnt[p] = 0;
-    if (tid == 0) any = 0;
-    __syncthreads();
-    const int iter = st->iter;
+//
+// A column's stage needs nothing of the other columns, so blocks take CW
+// columns each (SlabStage: their state in LDS); what the whole run needs (is
+// any column left, the iteration count) is settled by the last block to take
+// a ticket, counted per problem and then over the problems in one 64-bit
+// atomic that also carries the number of columns still running.
+template <int CW>
+struct SlabStage {
+    double al[CW], bj[CW], bn[CW], ib[CW];
+    int act[CW], moving[CW], cont[CW];   // moving: shifts not frozen after this iteration
+    int active;                          // columns that go on
+};
 
-    for (int g = tid; g < ncol; g += nt) {
-        if (!d.colactive[g]) continue;
-        const double bj = d.beta_cur[g];
-        double al = d.colsum[g];
-        double bn = sqrt(fmax(d.colsum[ncol + g], 0.0));
-        // ||K q_j|| ~ sqrt(alpha^2 + beta_j^2 + beta_{j+1}^2) scales the breakdown test
-        bool broke = !(bn > d.bd_rtol * sqrt(al * al + bj * bj + bn * bn));
-        if (!isfinite(al) || !isfinite(bn)) {
-            st->numeric = 1;
-            broke = true;
-            al = 0.0;
-        }
-        if (d.bounds_mode) {
-            double* tr = d.T + ((long long)iter * ncol + g) * 2;
-            tr[0] = al;
-            tr[1] = bn;
-        }
-        d.alpha[g] = al;
-        d.beta_next[g] = broke ? 0.0 : bn;
-        d.beta_used[g] = bj;
-        d.col_iters[g] += 1;
+// Column slot c of the slab (one thread per slot): Lanczos scalars.
+template <int CW>
+__device__ __forceinline__ void slab_column(const Dev& d, SlabStage<CW>& sl, int c, int g, bool ok, int iter,
+                                            double al, double b2) {
+    const bool act = ok && d.colactive[g] != 0;
+    sl.act[c] = act;
+    sl.moving[c] = 0;
+    sl.cont[c] = 0;
+    sl.bn[c] = 0.0;
+    if (c == 0) sl.active = 0;
+    if (!act) return;
+    const double bj = d.beta_cur[g];
+    double bn = sqrt(fmax(b2, 0.0));
+    // ||K q_j|| ~ sqrt(alpha^2 + beta_j^2 + beta_{j+1}^2) scales the breakdown test
+    bool broke = !(bn > d.bd_rtol * sqrt(al * al + bj * bj + bn * bn));
+    if (!isfinite(al) || !isfinite(bn)) {
+        d.st->numeric = 1;
+        broke = true;
+        al = 0.0;
     }
-    __syncthreads();
-
-    for (int idx = tid; idx < Q * ncol; idx += nt) {
-        const int g = idx % ncol, q = idx / ncol;
-        ShiftCoef cf;
-        cf.delta = cf.eps = cf.ginv = cf.tau = cf.tauw = 0.0;
-        cf.upd = 0;
-        cf.pad = 0;
-        if (d.colactive[g] && !d.frozen[idx]) {
-            const int p = g / s;
-            const double a = d.alpha[g] + d.t[p * Q + q];
-            const double bj = d.beta_used[g], bn = d.beta_next[g];
-            const double c1 = d.c1[idx], s1 = d.s1[idx], c2 = d.c2[idx], s2 = d.s2[idx];
-            const double eps = s2 * bj;
-            const double dhat = c2 * bj;
-            const double delta = c1 * dhat + s1 * a;
-            const double gbar = -s1 * dhat + c1 * a;
-            const double gamma = hypot(gbar, bn);
-            double cn = 1.0, sn = 0.0, ginv = 0.0;
-            if (gamma > 0.0 && isfinite(gamma)) {
-                cn = gbar / gamma;
-                sn = bn / gamma;
-                ginv = 1.0 / gamma;
-            } else {
-                st->numeric = 1;
-            }
-            const double ph = d.phibar[idx];
-            const double tau = cn * ph;
-            const double phn = -sn * ph;
-            cf.delta = delta;
-            cf.eps = eps;
-            cf.ginv = ginv;
-            cf.tau = tau;
-            cf.tauw = d.w[p * Q + q] * tau;
-            cf.upd = 1;
-            d.c2[idx] = c1; d.s2[idx] = s1; d.c1[idx] = cn; d.s1[idx] = sn;
-            d.phibar[idx] = phn;
-            const double rr = fabs(phn) / d.beta1[g];
-            d.relres[idx] = rr;
-            if (rr <= d.tol) d.frozen[idx] = 1;
-        }
-        d.coef[idx] = cf;
-        if (d.clog != nullptr) {
-            double* lg = d.clog + ((long long)iter * Q * ncol + idx) * 4;
-            lg[0] = cf.delta;
-            lg[1] = cf.eps;
-            lg[2] = cf.ginv;
-            lg[3] = cf.tauw;
-        }
+    if (d.bounds_mode) {
+        double* tr = d.T + ((long long)iter * d.ncol + g) * 2;
+        tr[0] = al;
+        tr[1] = bn;
     }
-    __syncthreads();
+    sl.al[c] = al;
+    sl.bj[c] = bj;
+    sl.bn[c] = broke ? 0.0 : bn;
+    d.col_iters[g] += 1;
+}
 
-    for (int g = tid; g < ncol; g += nt) {
-        if (!d.colactive[g]) {
-            d.colflag[g] = 0;
-            continue;
-        }
-        const bool broke = (d.beta_next[g] == 0.0);
-        bool all_frozen = (Q > 0);
-        for (int q = 0; q < Q; ++q) all_frozen = all_frozen && d.frozen[q * ncol + g];
-        const bool cont = !(broke || all_frozen);
-        d.colflag[g] = cont ? 2 : 1;
-        d.inv_beta_next[g] = cont ? 1.0 / d.beta_next[g] : 0.0;
-        if (cont) {
-            d.beta_cur[g] = d.beta_next[g];
-            atomicAdd(&active_cnt[g / s], 1);
-            any = 1;
+// Shift q of slot c (its column is active or the coefficients are zeros).
+template <int CW>
+__device__ __forceinline__ void slab_shift(const Dev& d, SlabStage<CW>& sl, int c, int g, int p, int q, int iter) {
+    const int idx = q * d.ncol + g;
+    ShiftCoef cf;
+    cf.delta = cf.eps = cf.ginv = cf.tau = cf.tauw = 0.0;
+    cf.upd = 0;
+    cf.pad = 0;
+    if (sl.act[c] && !d.frozen[idx]) {
+        const double a = sl.al[c] + d.t[p * d.Q + q];
+        const double bj = sl.bj[c], bn = sl.bn[c];
+        const double c1 = d.c1[idx], s1 = d.s1[idx], c2 = d.c2[idx], s2 = d.s2[idx];
+        const double eps = s2 * bj;
+        const double dhat = c2 * bj;
+        const double delta = c1 * dhat + s1 * a;
+        const double gbar = -s1 * dhat + c1 * a;
+        const double gamma = hypot(gbar, bn);
+        double cn = 1.0, sn = 0.0, ginv = 0.0;
+        if (gamma > 0.0 && isfinite(gamma)) {
+            cn = gbar / gamma;
+            sn = bn / gamma;
+            ginv = 1.0 / gamma;
         } else {
-            d.colactive[g] = 0;
-            for (int q = 0; q < Q; ++q) d.frozen[q * ncol + g] = 1;
+            d.st->numeric = 1;
         }
+        const double ph = d.phibar[idx];
+        const double tau = cn * ph;
+        const double phn = -sn * ph;
+        cf.delta = delta;
+        cf.eps = eps;
+        cf.ginv = ginv;
+        cf.tau = tau;
+        cf.tauw = d.w[p * d.Q + q] * tau;
+        cf.upd = 1;
+        d.c2[idx] = c1; d.s2[idx] = s1; d.c1[idx] = cn; d.s1[idx] = sn;
+        d.phibar[idx] = phn;
+        const double rr = fabs(phn) / d.beta1[g];
+        d.relres[idx] = rr;
+        if (rr <= d.tol) d.frozen[idx] = 1;
+        else atomicAdd(&sl.moving[c], 1);
     }
-    __syncthreads();
-    for (int p = tid; p < d.nprob; p += nt) d.prob_done[p] = active_cnt[p] ? 0 : 1;
-    if (tid == 0) {
-        st->iter = iter + 1;
-        st->live = 1;
-        if (!any || iter + 1 >= d.max_iter) st->done = 1;
+    if (d.basis == nullptr) d.coef[idx] = cf;
+    if (d.clog != nullptr) {
+        double* lg = d.clog + ((long long)iter * d.Q * d.ncol + idx) * 4;
+        lg[0] = cf.delta;
+        lg[1] = cf.eps;
+        lg[2] = cf.ginv;
+        lg[3] = cf.tauw;
     }
 }
 
-__global__ __launch_bounds__(1024) void scalar_kernel(Dev d) {
-    __shared__ int active_cnt[1024];
-    __shared__ int any;
-    __shared__ double sh[1024];
-    if (d.st->done) {
-        if (threadIdx.x == 0) d.st->live = 0;
+// Slot c after its shifts: does the column go on.
+template <int CW>
+__device__ __forceinline__ void slab_close(const Dev& d, SlabStage<CW>& sl, int c, int g, bool ok) {
+    sl.ib[c] = 0.0;
+    if (!ok) return;
+    if (!sl.act[c]) {
+        d.colflag[g] = 0;
         return;
     }
-    if (d.fuse_sums & 1) {  // column sums of both inner products' partials
-        block_colsums(d, 0, threadIdx.x, blockDim.x, sh);
-        block_colsums(d, 1, threadIdx.x, blockDim.x, sh);
+    const bool cont = sl.bn[c] != 0.0 && (d.Q == 0 || sl.moving[c] > 0);
+    sl.cont[c] = cont;
+    d.colflag[g] = cont ? 2 : 1;
+    if (cont) {
+        sl.ib[c] = 1.0 / sl.bn[c];
+        d.beta_cur[g] = sl.bn[c];
+        atomicAdd(&sl.active, 1);
+    } else {
+        d.colactive[g] = 0;
     }
-    scalar_stage(d, threadIdx.x, blockDim.x, active_cnt, any);
+}
+
+// One thread of a block whose columns are settled; `blocks` of them per problem.
+__device__ __forceinline__ void take_ticket(const Dev& d, int p, int active, int blocks, int iter) {
+    typedef unsigned long long u64;
+    const u64 old = atomicAdd(&d.ptick[p], ((u64)active << 32) | 1ull);
+    if ((int)(old & 0xffffffffull) + 1 != blocks) return;
+    const u64 left = (old >> 32) + (u64)active;
+    d.ptick[p] = 0;
+    d.prob_done[p] = left ? 0 : 1;
+    const u64 all = atomicAdd(&d.st->tick, (left << 32) | 1ull);
+    if ((int)(all & 0xffffffffull) + 1 != d.nprob) return;
+    d.st->tick = 0;
+    d.st->iter = iter + 1;
+    d.st->live = 1;
+    if ((all >> 32) + left == 0 || iter + 1 >= d.max_iter) d.st->done = 1;
+    if (d.queue) *d.queue = 0;           // the next product's work counter
+}
+
+// 16 columns a block: 16 columns x 64 lanes sum the partials of both inner
+// products, then 16 columns x 64 shifts. One block over all columns took 25
+// us at S = 256, Q = 15 and 29 us for 24 problems of 16 columns; this takes
+// 6 to 7.
+constexpr int kScalarCols = 16;
+__global__ __launch_bounds__(1024) void scalar_kernel(Dev d) {
+    __shared__ SlabStage<kScalarCols> sl;
+    __shared__ double sa[16][kScalarCols], sb[16][kScalarCols];
+    IterState* st = d.st;
+    const int tid = threadIdx.x;
+    if (st->done) {
+        if (tid == 0 && blockIdx.x == 0 && blockIdx.y == 0) st->live = 0;
+        return;
+    }
+    const int iter = st->iter, p = blockIdx.y;
+    const int c = tid & (kScalarCols - 1), l = tid >> 4;
+    const int col = blockIdx.x * kScalarCols + c, g = p * d.s + col;
+    const bool ok = col < d.s;
+    if (ok && (d.fuse_sums & 2) && l < 16) sa[l][c] = colsum_lane(d, 0, g, l);   // as phase 1 summed them
+    if (d.fuse_sums & 1) {
+        double vb = 0.0;
+        if (ok) {
+            const double* base = d.dots + ((long long)p * d.dots_blocks * d.s + col) * 2 + 1;
+#pragma unroll 4
+            for (int b = l; b < d.dots_blocks; b += 64) vb += base[(long long)b * d.s * 2];
+        }
+        vb += __shfl_xor(vb, 16);
+        vb += __shfl_xor(vb, 32);
+        if ((tid & 63) < kScalarCols) sb[tid >> 6][c] = vb;
+    }
+    __syncthreads();
+    if (tid < kScalarCols) {
+        double al = 0.0, b2 = 0.0;
+        if (ok) {
+            if (d.fuse_sums & 2)
+                for (int k = 0; k < 16; ++k) al += sa[k][c];
+            else
+                al = d.colsum[g];
+            if (d.fuse_sums & 1)
+                for (int k = 0; k < 16; ++k) b2 += sb[k][c];
+            else
+                b2 = d.colsum[d.ncol + g];
+        }
+        slab_column(d, sl, c, g, ok, iter, al, b2);
+        if (ok && sl.act[c]) {
+            d.alpha[g] = sl.al[c];
+            d.beta_used[g] = sl.bj[c];
+        }
+    }
+    __syncthreads();
+    if (ok && l < d.Q) slab_shift(d, sl, c, g, p, l, iter);
+    __syncthreads();
+    if (tid < kScalarCols) {
+        slab_close(d, sl, c, g, ok);
+        if (ok && sl.act[c]) d.inv_beta_next[g] = sl.ib[c];
+    }
+    __syncthreads();
+    if (ok && l < d.Q && sl.act[c] && !sl.cont[c]) d.frozen[l * d.ncol + g] = 1;
+    if (tid == 0) take_ticket(d, p, sl.active, gridDim.x, iter);
 }
 
 hipError_t launch_scalar(const Dev& d, hipStream_t st) {
-    hipLaunchKernelGGL(scalar_kernel, dim3(1), dim3(1024), 0, st, d);
+    hipLaunchKernelGGL(scalar_kernel, dim3((d.s + kScalarCols - 1) / kScalarCols, d.nprob), dim3(1024), 0, st, d);
     return hipGetLastError();
 }
 
@@ -705,7 +824,9 @@ hipError_t launch_scalar(const Dev& d, hipStream_t st) {
 //                          acc += w_q tau m_j,  x^{(q)} += tau m_j  (if kept)
 //   if the column continues: q_{j+1} = (K q_j - beta_j q_{j-1} - alpha_j q_j) / beta_{j+1}
 // (preconditioned form, Appendix D: the recurrence consumes p_j = P^{-1} z_j
-// and the continuing column scales the finished w and P^{-1} w, see launch_update)
+// and the continuing column scales the finished w and P^{-1} w, see launch_update;
+// y == nullptr: q_{j+1} has been written by the one-launch step, only the
+// directions move)
 // m_j overwrites m_{j-2}; q_{j+1} overwrites q_{j-1}.
 // Block: TS columns x RL row lanes; grid (blocks, ceil(s/TS), nprob).
 // ----------------------------------------------------------------------------
@@ -804,7 +925,7 @@ __global__ __launch_bounds__(256) void update_kernel(Dev d, const T* y, long lon
             if (solves) solves[(row * Q + q) * s + c] += stau[e] * m;
         }
         if (!basis) acc[idx] += a;
-        if (flag == 2) {
+        if (flag == 2 && y != nullptr) {
             if (pnext) {                        // preconditioned: y is w = z_{j+1} beta_{j+1}
                 qprev[idx] = y[idx] * ib;
                 const T pn = pnext[idx] * ib;
@@ -950,6 +1071,170 @@ hipError_t launch_update(const Dev& d, const T* y, long long ysplit, int nsplit,
 template hipError_t launch_update<double>(const Dev&, const double*, long long, int, const double*, double*,
                                           const double*, double*, double*, double*, float*, int, hipStream_t,
                                           double*, Op16);
+
+// ----------------------------------------------------------------------------
+// Small problems: the whole step after the product in one launch. A block owns
+// CG columns of one problem outright -- every row of them -- so both inner
+// products end inside the block and nothing waits for another kernel: it adds
+// the split partials, forms v and alpha, then ||v - alpha q||, runs its
+// columns' scalar stage and writes q_{j+1}. The step's four to five launches
+// cost about 4.5 us each however little they do (32 us a step at N = 1,024, S
+// = 1 against 11 here). A thread keeps R rows of v and q in registers. Without
+// the resident basis update_kernel moves the directions afterwards.
+// ----------------------------------------------------------------------------
+template <int CG, int R, typename PT>
+__global__ __launch_bounds__(1024) void step_owner_kernel(Dev d, const PT* __restrict__ y, long long ysplit, int nsplit,
+                                                          const double* __restrict__ q, double* __restrict__ qp,
+                                                          float* __restrict__ q32, Op16 op) {
+    constexpr int RL = 1024 / CG;
+    constexpr int KB = R < 8 ? R : 8;         // rows whose loads are in flight together
+    constexpr int SU = 8 / KB;                // ranges of them
+    __shared__ SlabStage<CG> sl;
+    __shared__ double red[16][CG];
+    const int tid = threadIdx.x, c = tid % CG, rl = tid / CG;
+    if (d.st->done) {
+        if (tid == 0 && blockIdx.x == 0 && blockIdx.y == 0) d.st->live = 0;
+        return;
+    }
+    const int p = blockIdx.y, iter = d.st->iter;
+    const int col = blockIdx.x * CG + c, s = d.s, g = p * s + col;
+    const bool ok = col < s;
+    const int n = ok && d.colactive[g] ? d.n[p] : 0;      // stopped columns have no rows to do
+    const long long base = (long long)d.row_off[p] * s;
+    y += base;
+    q += base;
+    qp += base;
+    const double bj = ok ? d.beta_cur[g] : 0.0;
+    // rows past the end load row 0 and count as zero: straight-line loads with
+    // 32-bit offsets (a problem of this size has under 2^29 elements)
+    auto at = [&](int k) { return (unsigned)(rl + k * RL < n ? rl + k * RL : 0) * (unsigned)s + (unsigned)(ok ? col : 0); };
+    double v[R];
+    double acc = 0.0;
+#pragma unroll
+    for (int k0 = 0; k0 < R; k0 += KB) {
+        double t[KB];
+        unsigned o[KB];
+#pragma unroll
+        for (int k = 0; k < KB; ++k) {
+            t[k] = 0.0;
+            o[k] = at(k0 + k);
+        }
+        for (int sp = 0; sp < nsplit; sp += SU) {
+            PT part[SU][KB];
+#pragma unroll
+            for (int u = 0; u < SU; ++u) {
+                const PT* yp = y + (long long)min(sp + u, nsplit - 1) * ysplit;
+#pragma unroll
+                for (int k = 0; k < KB; ++k) part[u][k] = yp[o[k]];
+            }
+#pragma unroll
+            for (int u = 0; u < SU; ++u)
+#pragma unroll
+                for (int k = 0; k < KB; ++k)
+                    if (sp + u < nsplit) t[k] += (double)part[u][k];
+        }
+#pragma unroll
+        for (int k = 0; k < KB; ++k) {
+            const double vT = t[k] - bj * qp[o[k]];
+            const double vk = (rl + (k0 + k) * RL < n) ? vT : 0.0;
+            acc = fma(q[o[k]], vk, acc);
+            v[k0 + k] = vk;
+        }
+    }
+    // sum over the block's rows for each column: lanes of a wave, then waves
+    auto total = [&](double x) {
+#pragma unroll
+        for (int m = CG; m < 64; m <<= 1) x += __shfl_xor(x, m);
+        __syncthreads();
+        if ((tid & 63) < CG) red[tid >> 6][c] = x;
+        __syncthreads();
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) t += red[w][c];
+        return t;
+    };
+    const double al = total(acc);
+    acc = 0.0;
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        const double vk = v[k] - al * q[at(k)];
+        v[k] = (rl + k * RL < n) ? vk : 0.0;
+        acc = fma(v[k], v[k], acc);
+    }
+    const double b2 = total(acc);
+    if (tid < CG) slab_column(d, sl, c, g, ok, iter, al, b2);
+    __syncthreads();
+    for (int e = tid; e < d.Q * CG; e += 1024) {
+        const int cc = e % CG;
+        if (blockIdx.x * CG + cc < s) slab_shift(d, sl, cc, p * s + (int)blockIdx.x * CG + cc, p, e / CG, iter);
+    }
+    __syncthreads();
+    if (tid < CG) slab_close(d, sl, c, g, ok);
+    __syncthreads();
+    for (int e = tid; e < d.Q * CG; e += 1024) {
+        const int cc = e % CG;
+        if (sl.act[cc] && !sl.cont[cc]) d.frozen[(e / CG) * d.ncol + p * s + blockIdx.x * CG + cc] = 1;
+    }
+    if (sl.cont[c]) {
+        const double ib = sl.ib[c];
+        double* const bq = (d.basis != nullptr && iter + 1 < d.basis_slots) ? d.basis[iter + 1] + base : nullptr;
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            const int i = rl + k * RL;
+            if (i >= n) break;
+            const unsigned idx = (unsigned)i * (unsigned)s + (unsigned)col;
+            const double qn = v[k] * ib;
+            qp[idx] = qn;
+            if (bq) bq[idx] = qn;
+            if (q32) q32[base + idx] = (float)qn;
+            else if (op.p) put_op(op, i, col, qn);
+        }
+    }
+    if (tid == 0) take_ticket(d, p, sl.active, gridDim.x, iter);
+}
+
+static int owner_cols(int s) { return s >= 4 ? 4 : s; }
+
+// Whether a step takes the one-launch form: at most eight rows a thread (one
+// or two columns) or four. One block keeps only that much in flight; longer
+// columns are faster over many blocks (N = 25,600, S = 1: 41 us in one block
+// against 21 in four launches; N = 2,000, S = 10: 31 against 22).
+bool step_owner_ok(const Dev& d, int max_n) {
+    if (d.s == 3) return false;
+    return d.s >= 4 ? max_n <= 1024 : (long long)max_n * d.s <= 8192;
+}
+
+template <int CG, typename PT>
+static hipError_t launch_owner_r(const Dev& d, const PT* y, long long ysplit, int nsplit, const double* q, double* qp,
+                                 float* q32, Op16 op, int max_n, hipStream_t st) {
+    const int rows = (max_n + 1024 / CG - 1) / (1024 / CG);
+    const dim3 grid((d.s + CG - 1) / CG, d.nprob), block(1024);
+    if (rows <= 1)
+        hipLaunchKernelGGL((step_owner_kernel<CG, 1, PT>), grid, block, 0, st, d, y, ysplit, nsplit, q, qp, q32, op);
+    else if (rows <= 2)
+        hipLaunchKernelGGL((step_owner_kernel<CG, 2, PT>), grid, block, 0, st, d, y, ysplit, nsplit, q, qp, q32, op);
+    else if (rows <= 4)
+        hipLaunchKernelGGL((step_owner_kernel<CG, 4, PT>), grid, block, 0, st, d, y, ysplit, nsplit, q, qp, q32, op);
+    else if (rows <= 8)
+        hipLaunchKernelGGL((step_owner_kernel<CG, 8, PT>), grid, block, 0, st, d, y, ysplit, nsplit, q, qp, q32, op);
+    else
+        return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+hipError_t launch_step_owner(const Dev& d, const double* y, long long ysplit, int nsplit, const double* q, double* qp,
+                             float* q32, int max_n, hipStream_t st, const float* y32, Op16 op) {
+    if (!step_owner_ok(d, max_n)) return hipErrorInvalidValue;
+    const int cg = owner_cols(d.s);
+    if (y32 != nullptr) {
+        if (cg == 1) return launch_owner_r<1, float>(d, y32, ysplit, nsplit, q, qp, q32, op, max_n, st);
+        if (cg == 2) return launch_owner_r<2, float>(d, y32, ysplit, nsplit, q, qp, q32, op, max_n, st);
+        return launch_owner_r<4, float>(d, y32, ysplit, nsplit, q, qp, q32, op, max_n, st);
+    }
+    if (cg == 1) return launch_owner_r<1, double>(d, y, ysplit, nsplit, q, qp, q32, op, max_n, st);
+    if (cg == 2) return launch_owner_r<2, double>(d, y, ysplit, nsplit, q, qp, q32, op, max_n, st);
+    return launch_owner_r<4, double>(d, y, ysplit, nsplit, q, qp, q32, op, max_n, st);
+}
 
 // ----------------------------------------------------------------------------
 // Resident-basis combine. Per shift and column the logged coefficients give
@@ -1168,6 +1453,26 @@ template hipError_t launch_copy<float, float>(const float*, int, int, int, float
 template hipError_t launch_copy<double, double>(const double*, int, int, int, double*, int, hipStream_t);
 template hipError_t launch_copy<float, double>(const float*, int, int, int, double*, int, hipStream_t);
 template hipError_t launch_copy<double, float>(const double*, int, int, int, float*, int, hipStream_t);
+
+// dst (n x sd, contiguous) from src (n x s), the columns past s zero
+template <typename TI>
+__global__ void copy_pad_kernel(const TI* src, int ld_src, int n, int s, double* dst, int sd) {
+    const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= (long long)n * sd) return;
+    const int i = (int)(e / sd), c = (int)(e - (long long)i * sd);
+    dst[e] = (c < s) ? (double)src[(long long)i * ld_src + c] : 0.0;
+}
+
+template <typename TI>
+hipError_t launch_copy_pad(const TI* src, int ld_src, int n, int s, double* dst, int sd, hipStream_t st) {
+    const long long total = (long long)n * sd;
+    if (total == 0) return hipSuccess;
+    hipLaunchKernelGGL(copy_pad_kernel<TI>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, src, ld_src, n, s,
+                       dst, sd);
+    return hipGetLastError();
+}
+template hipError_t launch_copy_pad<float>(const float*, int, int, int, double*, int, hipStream_t);
+template hipError_t launch_copy_pad<double>(const double*, int, int, int, double*, int, hipStream_t);
 
 template <typename T>
 __global__ void fill_kernel(T* p, size_t count, T value) {

@@ -168,7 +168,13 @@ __global__ __launch_bounds__(64 * WAVES) void mvm_kt_kernel(MvmArgs a) {
     constexpr int BN = 64;
     constexpr int S16 = NSB * 16;
     constexpr int VST = (NSB & 1) ? S16 : S16 + 16;
-    __shared__ __attribute__((aligned(16))) double vs[BN * VST];
+    // two chunk buffers and one barrier per chunk (as in kt32_item) where the
+    // registers allow two blocks a CU at most (two tiles a wave: 5.64 against
+    // 5.77 ms at N = 50,000, S = 64); one buffer and two barriers where the
+    // smaller LDS lets a third block in (one tile: 89 against 99 us at N =
+    // 3,000, S = 256)
+    constexpr int NBUF = (RT == 2) ? 2 : 1;
+    __shared__ __attribute__((aligned(16))) double vs[NBUF * BN * VST];
 
     if (mfma::done_now(a.done)) return;
     const int nsplit = a.nsplit;
@@ -176,9 +182,10 @@ __global__ __launch_bounds__(64 * WAVES) void mvm_kt_kernel(MvmArgs a) {
     const int rb = (int)(blockIdx.x / (unsigned)nsplit);
     const int n = a.n;
     const double o2 = a.o2, s2 = a.s2;
-    const double* __restrict__ v = static_cast<const double*>(a.v);
-    double* __restrict__ y = static_cast<double*>(a.y) + (long long)split * a.ysplit;
-    const int s = a.s, ldv = a.ldv, ldy = a.ldy;
+    const int g0 = (int)blockIdx.y * 64;         // column group of a wide launch
+    const double* __restrict__ v = static_cast<const double*>(a.v) + g0;
+    double* __restrict__ y = static_cast<double*>(a.y) + (long long)split * a.ysplit + g0;
+    const int s = min(a.s - g0, 64), ldv = a.ldv, ldy = a.ldy;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: keeps bases in SGPRs
@@ -245,23 +252,24 @@ __global__ __launch_bounds__(64 * WAVES) void mvm_kt_kernel(MvmArgs a) {
         }
     };
     // one chunk: publish its V rows, start later loads, contract; the B
-    // operands of step st + 1 are read from LDS before step st's MFMAs
+    // operands of step st + 1 are read from LDS before step st's MFMAs.
     auto chunk = [&](int c, double (&cur)[RT][16], double (&far)[RT][16]) {
-        __syncthreads();
+        double* vb = vs + (c & (NBUF - 1)) * (BN * VST);
+        if constexpr (NBUF == 1) __syncthreads();
 #pragma unroll
-        for (int k = 0; k < VPV; ++k) *reinterpret_cast<VecT*>(&vs[(vr + k * VR) * VST + VW * vc]) = vreg[k];
+        for (int k = 0; k < VPV; ++k) *reinterpret_cast<VecT*>(&vb[(vr + k * VR) * VST + VW * vc]) = vreg[k];
         __syncthreads();
         if (c + 1 < c1) fetch_v(c + 1);
         if (c + KD - 1 < c1) fetch_k(c + KD - 1, far);
         double bcur[NSB], bnxt[NSB];
 #pragma unroll
-        for (int sb = 0; sb < NSB; ++sb) bcur[sb] = vs[(lane >> 4) * VST + sb * 16 + (lane & 15)];
+        for (int sb = 0; sb < NSB; ++sb) bcur[sb] = vb[(lane >> 4) * VST + sb * 16 + (lane & 15)];
 #pragma unroll
         for (int st = 0; st < 16; ++st) {
             if (st + 1 < 16) {
                 const int jn = 4 * (st + 1) + (lane >> 4);
 #pragma unroll
-                for (int sb = 0; sb < NSB; ++sb) bnxt[sb] = vs[jn * VST + sb * 16 + (lane & 15)];
+                for (int sb = 0; sb < NSB; ++sb) bnxt[sb] = vb[jn * VST + sb * 16 + (lane & 15)];
             }
 #pragma unroll
             for (int sb = 0; sb < NSB; ++sb)
@@ -671,11 +679,11 @@ __global__ __launch_bounds__(64 * WAVES) void mvm_kt16_kernel(MvmArgs a) {
 }
 
 template <int NSB>
-hipError_t launch_kt_nsb(const MvmArgs& a, int grid, hipStream_t st) {
+hipError_t launch_kt_nsb(const MvmArgs& a, dim3 grid, hipStream_t st) {
     if (a.rt == 1)
-        hipLaunchKernelGGL((mvm_kt_kernel<NSB, 1, 4, 2>), dim3(grid), dim3(256), 0, st, a);
+        hipLaunchKernelGGL((mvm_kt_kernel<NSB, 1, 4, 2>), grid, dim3(256), 0, st, a);
     else
-        hipLaunchKernelGGL((mvm_kt_kernel<NSB, 2, 4, 2>), dim3(grid), dim3(256), 0, st, a);
+        hipLaunchKernelGGL((mvm_kt_kernel<NSB, 2, 4, 2>), grid, dim3(256), 0, st, a);
     return hipGetLastError();
 }
 
@@ -724,8 +732,10 @@ hipError_t launch_kt32_variant(const MvmArgs& a, int grid, hipStream_t st) {
                 slots = 1024;
             (void)hipGetLastError();
         }
-        const hipError_t e = launch_fill<int>(a.queue, 1, 0, st);
-        if (e != hipSuccess) return e;
+        if (!a.queue_clean) {
+            const hipError_t e = launch_fill<int>(a.queue, 1, 0, st);
+            if (e != hipSuccess) return e;
+        }
         grid = std::min(a.nitems, slots);
     }
     hipLaunchKernelGGL((mvm_kt32_kernel<NSB, RT, 4, 2, NACC>), dim3(grid), dim3(256), 0, st, a);
@@ -754,7 +764,7 @@ static bool kt_rows_ok(const MvmArgs& a) {
 
 hipError_t launch_mvm_kt(const MvmArgs& a, int nsb, hipStream_t st) {
     if (!kt_rows_ok(a)) return hipErrorInvalidValue;
-    const int grid = a.nrb * a.nsplit;
+    const dim3 grid(a.nrb * a.nsplit, (a.s + 63) / 64);
     switch (nsb) {
         case 1: return launch_kt_nsb<1>(a, grid, st);
         case 2: return launch_kt_nsb<2>(a, grid, st);

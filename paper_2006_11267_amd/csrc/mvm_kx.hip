@@ -239,7 +239,8 @@ hipError_t launch_mvm_kx(const MvmArgs& a, hipStream_t st) {
 // read the operand twice) and at n = 5,000 (a lone 128-row block: 2.4 us a
 // chunk, bound by its loads' latency): rounds of blocks over the chip's 256
 // (16 waves) or 512 (8 waves) slots, each as long as its chunks, plus writing
-// and summing the partials at 4.5 TB/s. Where the operand is several times an
+// and summing the partials at 4.5 TB/s (and 0.3 us a range, or a line a cycle
+// where one block sums a small problem's, step_owner_kernel). Where the operand is several times an
 // XCD's 4 MB L2 the ranges are 8 or 16, so that every XCD (block index mod 8)
 // streams one or two of them (at N = 10,000, S = 64, where it is as large as
 // the L2, six ranges in one round of blocks beat sixteen: 101 against 117 us).
@@ -259,7 +260,8 @@ void kx_plan(int n, int s, int part_bytes, int& rt, int& nsplit) {
             const double load = blocks * ns / (256.0 * per_cu);          // rounds
             const double chunk_us = (r == 1 ? (load <= 0.5 ? 2.4 : 3.7) : 3.6) * nsb / 4.0;
             const double us = std::ceil(load) * std::ceil((double)chunks / ns) * chunk_us +
-                              (double)ns * n * s * 2.0 * part_bytes / 4.5e6;
+                              ns * (std::max(0.3, n <= 1024 ? n / 2200.0 : 0.0) +
+                                    (double)n * s * 2.0 * part_bytes / 4.5e6);
             if (us < best) {
                 best = us;
                 rt = r;

@@ -337,8 +337,10 @@ hipError_t launch_f32_variant(const MvmArgs& a, int grid_x, hipStream_t st) {
                 slots = 1024;
             (void)hipGetLastError();
         }
-        const hipError_t e = launch_fill<int>(a.queue, 1, 0, st);
-        if (e != hipSuccess) return e;
+        if (!a.queue_clean) {
+            const hipError_t e = launch_fill<int>(a.queue, 1, 0, st);
+            if (e != hipSuccess) return e;
+        }
         hipLaunchKernelGGL((mvm_f32_kernel<KERNEL, DP, NSB, RT, ARD>), dim3(std::min(a.nitems, slots)), dim3(256), 0,
                            st, a);
         return hipGetLastError();
@@ -430,9 +432,10 @@ __global__ __launch_bounds__(256) void mvm_f64mfma_kernel(MvmArgs a) {
     const double sc0sq = sc[0] * sc[0];
     const int split = blockIdx.y;
     const double* __restrict__ xh = static_cast<const double*>(a.xh) + (long long)off * DP;
-    const double* __restrict__ v = static_cast<const double*>(a.v) + (long long)off * a.ldv;
-    double* __restrict__ y = static_cast<double*>(a.y) + (long long)split * a.ysplit + (long long)off * a.ldy;
-    const int s = a.s, ldv = a.ldv, ldy = a.ldy;
+    const int g0 = (int)blockIdx.z * 64;         // column group of a wide launch
+    const double* __restrict__ v = static_cast<const double*>(a.v) + (long long)off * a.ldv + g0;
+    double* __restrict__ y = static_cast<double*>(a.y) + (long long)split * a.ysplit + (long long)off * a.ldy + g0;
+    const int s = min(a.s - g0, 64), ldv = a.ldv, ldy = a.ldy;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -544,7 +547,7 @@ __global__ __launch_bounds__(256) void mvm_f64mfma_kernel(MvmArgs a) {
 
 template <int KERNEL, bool ARD, int DP, int NSB>
 hipError_t launch_f64m_nsb(const MvmArgs& a, int grid_x, hipStream_t st) {
-    dim3 grid(grid_x, a.nsplit);
+    dim3 grid(grid_x, a.nsplit, (a.s + 63) / 64);
     if (a.rt == 1)
         hipLaunchKernelGGL((mvm_f64mfma_kernel<KERNEL, DP, NSB, 1, ARD>), grid, dim3(256), 0, st, a);
     else
