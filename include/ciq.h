@@ -171,11 +171,11 @@ typedef struct ciq_opts {
                                   max_rel_residual refer to the preconditioned
                                   system. 0: plain CIQ. ciq_backward and the batched
                                   call return CIQ_ENOTSUP for R > 0.             */
-    int32_t krylov_basis;      /* CIQ_BASIS_AUTO: when the run has neither a
-                                  preconditioner nor kept per-shift solves and
-                                  (max_iter + 1) Lanczos vectors fit in device
+    int32_t krylov_basis;      /* CIQ_BASIS_AUTO: when the run has no preconditioner
+                                  and (max_iter + 1) Lanczos vectors fit in device
                                   memory, keep the vectors the run reaches
-                                  resident and form the solution once after the
+                                  resident and form the solution (and the
+                                  per-shift solves, if kept) once after the
                                   run from the logged direction coefficients,
                                   instead of moving Q direction vectors every
                                   iteration (the same result up to rounding).

@@ -217,13 +217,11 @@ int kt_blocks_per_cu(int dtype, int nsb, int rt, int acc = 0);
 inline int product_cap(int dtype, bool cached) {
     return ((dtype == CIQ_F32 && !cached) || (dtype == CIQ_F16X3 && cached)) ? 128 : 64;
 }
-// Parts of the split operand a resident product of s columns reads: two for
-// CIQ_F16X3; three for a single CIQ_F32 problem of more than 32 columns, where
-// the FP32 contraction would take longer than the stream of K (at most 32
-// columns are HBM-bound as they are, see kt32_item); 0 for the others.
-inline int operand_parts(int dtype, bool cached, int nprob, int s) {
-    if (!cached || nprob != 1) return 0;
-    return dtype == CIQ_F16X3 ? 2 : (dtype == CIQ_F32 && s > 32) ? 3 : 0;
+// More than 32 columns of a single resident CIQ_F32 problem can run on the
+// FP16 matrix cores (three-part operand, mvm_kx.hip); at most 32 are HBM-bound
+// as they are (see kt32_item).
+inline bool kx_columns(int dtype, bool cached, int nprob, int s) {
+    return cached && nprob == 1 && dtype == CIQ_F32 && s > 32;
 }
 
 // ---- launchers (kernels.hip, mvm_f32_*.hip) ---------------------------------
@@ -300,6 +298,12 @@ hipError_t launch_basis_table(double** tab, int first, int end, int per_chunk, s
 // of scratch; iters = the run's iteration count.
 hipError_t launch_basis_combine(const Dev& d, int iters, double* cq, double* c, double* acc, int max_n,
                                 hipStream_t st);
+
+// The same with the per-shift solutions: out[i][q][c] (leading dimension ldo,
+// c < s_out) = x^{(q)}, acc = sum_q w_q x^{(q)} (one problem).
+template <typename TO>
+hipError_t launch_basis_solves(const Dev& d, int iters, double* cq, double* acc, TO* out, int ldo, int s_out, int n,
+                               hipStream_t st);
 
 template <typename T>
 hipError_t launch_init_vectors(const Dev& d, T* q, T* qprev, T* acc, float* q32, int rows,

@@ -249,7 +249,8 @@ int pad_dims(int d, int dtype) {
 // batched runs also the number of column ranges per work item (1, 2, 4).
 // Each candidate's product is timed with HIP events on the problem itself the
 // first time a (device, dtype, kernel, dims, column blocks, log2 rows,
-// resident, problems, accumulation) key is met. Winners are kept for the
+// resident, problems, accumulation) key is met ("/model" after the device:
+// single problems whose ranges follow model_nsplit). Winners are kept for the
 // process and in a text file, one "key = rt nsplit" line each (lines that
 // do not parse are skipped): $CIQ_TUNE_CACHE if set (empty: no file), else
 // $HOME/.cache/libciq/tune.txt.
@@ -314,8 +315,6 @@ void tune_cache_store(const TuneKey& k, const TuneVal& v) {
     std::fclose(f);
 }
 
-// "model": the column ranges of single problems follow model_nsplit (winners
-// timed with other ranges have another key).
 std::string device_arch() {
     int dev = 0;
     hipDeviceProp_t prop;
@@ -324,7 +323,7 @@ std::string device_arch() {
         return "unknown";
     }
     char b[160];
-    std::snprintf(b, sizeof(b), "%s/%dcu/model", prop.gcnArchName, prop.multiProcessorCount);
+    std::snprintf(b, sizeof(b), "%s/%dcu", prop.gcnArchName, prop.multiProcessorCount);
     for (char* c = b; *c; ++c)
         if (*c == ' ' || *c == '=') *c = '_';
     return b;
@@ -626,6 +625,8 @@ struct Run {
     bool keep_solves = false;
     int fine_acc = 0;      // FP32 resident products: the finer FP64 accumulation (inverse root)
     bool cached = false;   // products stream a resident kernel matrix (kt)
+    bool wide_allowed = false;   // the wide FP32 form may be chosen
+    bool wide = false;           // and is
     bool precond = false;  // preconditioned run (single problem): Lanczos in the P^{-1} inner product
     const Precond* pc = nullptr;
     BasisSlots* bslots = nullptr;   // resident Krylov basis of this run (d.basis is its table)
@@ -690,15 +691,14 @@ struct Run {
         }
         acc = a.template take<double>(vec);
         if (keep_solves) solves = a.template take<double>(vec * Q);
-        if (parts() > 0) {
+        if (max_parts() > 0) {
             nsbt = op16_nsbt(s);
-            op_scale = op_scale_of(parts());
-            vt16 = a.template take<_Float16>(op_halfs(kcache_cols(max_n), nsbt, parts()));
+            op_scale = op_scale_of(max_parts());
+            vt16 = a.template take<_Float16>(op_halfs(kcache_cols(max_n), nsbt, max_parts()));
             opsc = a.template take<double>(s);
             opinv = a.template take<double>(s);
-        } else if (sizeof(T) == 4) {
-            q32 = a.template take<float>(vec);
         }
+        if (sizeof(T) == 4 && max_parts() != 2) q32 = a.template take<float>(vec);
         if (precond) {
             pbuf[0] = a.template take<double>(vec);
             pbuf[1] = a.template take<double>(vec);
@@ -743,8 +743,34 @@ struct Run {
     int rows_per_block() const {
         return parts() == 3 ? kx_rows_per_block(rt) : cached ? 64 * rt : mvm_rows_per_block(dtype, s, rt);
     }
-    int parts() const { return (sp || dn) ? 0 : operand_parts(dtype, cached, nprob, s); }   // of the split operand
-    size_t op_words() const { return op_halfs(kcache_cols(max_n), nsbt, parts()) / 2; }
+    // parts of the split operand the products read: two for CIQ_F16X3, three
+    // for the wide CIQ_F32 form; max_parts: what the layout has room for (the
+    // wide form is decided once the bounds are known, choose_wide)
+    int max_parts() const {
+        if (sp || dn || !cached || nprob != 1) return 0;
+        return dtype == CIQ_F16X3 ? 2 : (wide_allowed && kx_columns(dtype, cached, nprob, s)) ? 3 : 0;
+    }
+    int parts() const { return max_parts() == 3 ? (wide ? 3 : 0) : max_parts(); }
+    // The inverse root passes FP32 noise of the products on multiplied by about
+    // kappa / sqrt(N). The FP32 matrix cores with sums of 16 columns and the
+    // wide form differ in that noise (the wide form has half of it): up to
+    // kappa / sqrt(N) = 125 their results lie within 1.2e-5 of each other,
+    // beyond that they drift apart with it (1.5e-4 at 3,000; 64 problems, N =
+    // 800 to 20,000, kappa 20 to 4.5e5), although both are as far from the
+    // exact root. So the inverse root takes the wide form where results keep to
+    // what the FP32 matrix cores gave, and from 32,768 rows on, where the
+    // product is most of a solve (3.7 -> 2.2 ms). The square root's FP32 path
+    // had sums of 64 columns, whose own noise is as large as any difference.
+    void choose_wide(bool sqrt_mode, double kappa) {
+        wide = max_parts() == 3 &&
+               (sqrt_mode || max_n >= 32768 || kappa <= 125.0 * std::sqrt((double)max_n));
+        use_operand();
+    }
+    void use_operand() {      // the operand copy that is not read is not written
+        if (parts() > 0) q32 = nullptr;
+        else vt16 = nullptr;
+    }
+    size_t op_words() const { return op_halfs(kcache_cols(max_n), nsbt, max_parts()) / 2; }
 
     void configure(int rt_) {
         rt = rt_;
@@ -770,7 +796,7 @@ struct Run {
         for (int p = 0; p < nprob; ++p) nrb += (h_n[p] + rpb - 1) / rpb;
         nsplit = mvm_pick_nsplit(dtype, nrb, max_n, s);
         const int chunks = (max_n + 63) / 64;
-        if (nprob == 1 && !kx) {
+        if (nprob == 1 && !kx && !(sp || dn)) {
             const int cap = product_cap(dtype, cached);
             const int nsb = (std::min(s, cap) + 15) / 16;
             SplitModel m = mvm_split_model(dtype, cached, max_n, nsb, rt);
@@ -811,11 +837,16 @@ struct Run {
     void plan(int rt_) {
         nsplit_alloc = 1;
         nrb_alloc = 1;
-        for (int r = 1; r <= 2; ++r) {
-            configure(r);
-            nsplit_alloc = std::max(nsplit_alloc, nsplit);
-            nrb_alloc = std::max(nrb_alloc, nrb);
+        const bool w0 = wide;
+        for (int form = 0; form < 2; ++form) {   // with and without the wide form
+            wide = (form == 1);
+            for (int r = 1; r <= 2; ++r) {
+                configure(r);
+                nsplit_alloc = std::max(nsplit_alloc, nsplit);
+                nrb_alloc = std::max(nrb_alloc, nrb);
+            }
         }
+        wide = w0;
         if (nprob > 1) nsplit_alloc = std::max(nsplit_alloc, 4);   // the tuner's batched candidates
         configure(rt_);
     }
@@ -1140,7 +1171,7 @@ int tune_rt(Run<T>& r, const void* operand, hipStream_t st) {
     int nlog = 0;
     while ((1 << (nlog + 1)) <= r.rows_total) ++nlog;
     tune_cache_load();
-    const TuneKey key{device_arch(), r.dtype, r.kernel, r.dp, nsb, nlog, r.cached ? 1 : 0, batched ? 1 : 0,
+    const TuneKey key{device_arch() + (batched ? "" : "/model"), r.dtype, r.kernel, r.dp, nsb, nlog, r.cached ? 1 : 0, batched ? 1 : 0,
                       r.fine_acc};
     auto it = g_tuned.find(key);
     if (it == g_tuned.end()) {
@@ -1326,7 +1357,7 @@ int kcache_build(Run<T>& r, const KCache& kc, hipStream_t st) {
     ka.nchunk = (int)(kcache_cols(ka.n) / 64);
     ka.njs = (long long)(kcache_cols(ka.n) / 4);
     ka.elem = (r.dtype == CIQ_F16X3) ? 2 : (kc.elem == 4 ? 1 : 0);
-    ka.mult = (r.parts() == 3) ? kKxScale : 1.0f;
+    ka.mult = (r.max_parts() == 3) ? kKxScale : 1.0f;
     ka.kt = kc.ptr;
     HIPCHK(launch_kbuild(ka, st));
     r.kt = kc.ptr;
@@ -1346,6 +1377,76 @@ struct ScratchLock {
     std::unique_lock<std::mutex> lk;
     explicit ScratchLock(int dev) : lk(g_scratch[dev].mu) {}
 };
+
+// Resident Krylov basis for run r, when every slot it may reach fits: points
+// r at the slots and logs (r.bslots, r.d.basis) or leaves it on the direction
+// recurrence. cq, c: the combine's coefficients.
+template <typename T>
+int basis_acquire(Run<T>& r, int dev, BasisSlots& bslots, double** cq, double** c, hipStream_t st) {
+    BasisPool& bp = g_basis[dev];
+    const size_t slots = (size_t)r.max_iter + 1;
+    const size_t stride = ((size_t)r.rows_total * r.s * sizeof(double) + 255) & ~size_t(255);
+    const size_t chunk = basis_chunk_bytes(stride);
+    if (bp.chunk_bytes != chunk) {   // another chunk size: start the pool over
+        STCHK(basis_pool_release(dev));
+        bp.chunk_bytes = chunk;
+    }
+    const size_t per_chunk = chunk / stride;
+    const size_t chunks = (slots + per_chunk - 1) / per_chunk;
+    const size_t qn = (size_t)r.Q * r.d.ncol;
+    const size_t iters_cap = (size_t)r.max_iter;
+    auto log_layout = [&](auto& l) {   // coefficient logs and the slot table
+        r.d.clog = l.template take<double>(iters_cap * qn * 4);
+        *cq = l.template take<double>(iters_cap * qn);
+        *c = l.template take<double>(iters_cap * r.d.ncol);
+        bslots.tab = l.template take<double*>(slots);
+    };
+    Sizer lz;
+    log_layout(lz);
+    const size_t logs = lz.off;
+    const size_t more =
+        (chunks > bp.chunks.size() ? (chunks - bp.chunks.size()) * chunk : 0) + (logs > bp.logs_cap ? logs : 0);
+    bool fits = true;
+    if (more > 0) {   // leave a tenth of the free memory and 4 GiB for everything else
+        size_t free_b = 0, total_b = 0;
+        fits = hipMemGetInfo(&free_b, &total_b) == hipSuccess && more + (size_t(4) << 30) <= free_b / 10 * 9;
+        if (!fits) (void)hipGetLastError();
+    }
+    if (fits && logs > bp.logs_cap) {
+        if (bp.logs) {
+            HIPCHK(hipDeviceSynchronize());
+            HIPCHK(hipFree(bp.logs));
+            bp.logs = nullptr;
+            bp.logs_cap = 0;
+        }
+        if (hipMalloc(&bp.logs, logs) == hipSuccess) {
+            bp.logs_cap = logs;
+        } else {
+            (void)hipGetLastError();
+            bp.logs = nullptr;
+            fits = false;
+        }
+    }
+    if (!fits) {
+        r.d.clog = nullptr;
+        *cq = *c = nullptr;
+        bslots.tab = nullptr;
+        return CIQ_OK;
+    }
+    Carver lc(bp.logs);
+    log_layout(lc);
+    bslots.dev = dev;
+    bslots.stride = stride;
+    bslots.per_chunk = (int)per_chunk;
+    bslots.max_slots = (int)slots;
+    HIPCHK(launch_fill<double>(reinterpret_cast<double*>(bslots.tab), slots, 0.0, st));   // null pointers
+    // the pooled chunks at once; the run takes new ones as it reaches them
+    STCHK(bslots.ensure((int)std::min(bp.chunks.size() * per_chunk, slots), st));
+    r.d.basis = bslots.tab;
+    r.d.basis_slots = (int)slots;
+    r.bslots = &bslots;
+    return CIQ_OK;
+}
 
 // Full CIQ solve for nprob problems sharing s, Q, dtype, kernel.
 // out_ptrs[p]: n_p x s with leading dimension ldo; b_ptrs likewise with ldb.
@@ -1393,6 +1494,9 @@ int solve(int nprob, const ciq_problem* probs, const ciq_opts* o, const void* co
     // the inverse root keeps FP64 partials
     main.part32 = (mode == CIQ_SQRT) && nprob == 1 && main.cached && (dtype == CIQ_F32 || dtype == CIQ_F16X3) &&
                   !precond && post_spec == nullptr && sparse == nullptr && dense == nullptr;
+    // (inverse roots: kept solves feed gradients, whose sums cancel, and a
+    // posterior's products carry noise of the prior's size, see choose_wide)
+    main.wide_allowed = !precond && (mode == CIQ_SQRT || (post_spec == nullptr && solves_out == nullptr));
     main.plan(2);
 
     Run<T> bnd;
@@ -1445,13 +1549,11 @@ int solve(int nprob, const ciq_problem* probs, const ciq_opts* o, const void* co
         main.pc = &pc;
         bnd.pc = &pc;
         // the operand p_j = P^{-1} z_j has p_j^T z_j = 1 and P >= sigma^2 I, so
-        // |p_j| <= 1/sigma: scale it by the power of two at most sigma times
-        // the unit-norm vectors' scale
-        const auto pscale = [&](int parts) {
-            return (float)std::ldexp(1.0, (int)std::floor(std::log2(op_scale_of(parts) * std::sqrt(probs[0].noise))));
-        };
-        main.op_scale = pscale(main.parts());
-        bnd.op_scale = pscale(bnd.parts());
+        // |p_j| <= 1/sigma: scale it by the power of two at most 256 sigma
+        const float sc =
+            (float)std::ldexp(1.0, (int)std::floor(std::log2(kOp16Scale * std::sqrt(probs[0].noise))));
+        main.op_scale = sc;
+        bnd.op_scale = sc;
     }
     if (post_spec) {
         STCHK(post_build(probs[0], dtype, main.xh, main.dp, main.kernel, main.ard, main.h_scale.data(), *post_spec,
@@ -1531,6 +1633,8 @@ int solve(int nprob, const ciq_problem* probs, const ciq_opts* o, const void* co
     HIPCHK(hipMemcpyAsync(main.t, th.data(), th.size() * sizeof(double), hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(main.w, wh.data(), wh.size() * sizeof(double), hipMemcpyHostToDevice, st));
 
+    main.choose_wide(mode == CIQ_SQRT, dense ? 1.0 : lmax[0] / lmin[0]);
+
     // ---- right-hand sides --------------------------------------------------
     for (int p = 0; p < nprob; ++p)
         HIPCHK(launch_copy_pad<T>(static_cast<const T*>(b_ptrs[p]), ldb, main.h_n[p], s,
@@ -1551,78 +1655,23 @@ int solve(int nprob, const ciq_problem* probs, const ciq_opts* o, const void* co
     // ---- resident Krylov basis (when every slot the run may reach fits) -----
     BasisSlots bslots;
     double *basis_cq = nullptr, *basis_c = nullptr;
-    bool use_basis = false;
-    if (o->krylov_basis == CIQ_BASIS_AUTO && !precond && solves_out == nullptr && main.Q > 0) {
-        BasisPool& bp = g_basis[dev];
-        const size_t slots = (size_t)main.max_iter + 1;
-        const size_t stride = ((size_t)main.rows_total * sr * sizeof(double) + 255) & ~size_t(255);
-        const size_t chunk = basis_chunk_bytes(stride);
-        if (bp.chunk_bytes != chunk) {   // another chunk size: start the pool over
-            STCHK(basis_pool_release(dev));
-            bp.chunk_bytes = chunk;
-        }
-        const size_t per_chunk = chunk / stride;
-        const size_t chunks = (slots + per_chunk - 1) / per_chunk;
-        const size_t qn = (size_t)main.Q * main.d.ncol;
-        const size_t iters_cap = (size_t)main.max_iter;
-        auto log_layout = [&](auto& c) {   // coefficient logs and the slot table
-            main.d.clog = c.template take<double>(iters_cap * qn * 4);
-            basis_cq = c.template take<double>(iters_cap * qn);
-            basis_c = c.template take<double>(iters_cap * main.d.ncol);
-            bslots.tab = c.template take<double*>(slots);
-        };
-        Sizer lz;
-        log_layout(lz);
-        const size_t logs = lz.off;
-        const size_t more =
-            (chunks > bp.chunks.size() ? (chunks - bp.chunks.size()) * chunk : 0) + (logs > bp.logs_cap ? logs : 0);
-        bool fits = true;
-        if (more > 0) {   // leave a tenth of the free memory and 4 GiB for everything else
-            size_t free_b = 0, total_b = 0;
-            fits = hipMemGetInfo(&free_b, &total_b) == hipSuccess && more + (size_t(4) << 30) <= free_b / 10 * 9;
-            if (!fits) (void)hipGetLastError();
-        }
-        if (fits && logs > bp.logs_cap) {
-            if (bp.logs) {
-                HIPCHK(hipDeviceSynchronize());
-                HIPCHK(hipFree(bp.logs));
-                bp.logs = nullptr;
-                bp.logs_cap = 0;
-            }
-            if (hipMalloc(&bp.logs, logs) == hipSuccess) {
-                bp.logs_cap = logs;
-            } else {
-                (void)hipGetLastError();
-                bp.logs = nullptr;
-                fits = false;
-            }
-        }
-        if (fits) {
-            Carver lc(bp.logs);
-            log_layout(lc);
-            bslots.dev = dev;
-            bslots.stride = stride;
-            bslots.per_chunk = (int)per_chunk;
-            bslots.max_slots = (int)slots;
-            HIPCHK(launch_fill<double>(reinterpret_cast<double*>(bslots.tab), slots, 0.0, st));   // null pointers
-            // the pooled chunks at once; the run takes new ones as it reaches them
-            STCHK(bslots.ensure((int)std::min(bp.chunks.size() * per_chunk, slots), st));
-            main.d.basis = bslots.tab;
-            main.d.basis_slots = (int)slots;
-            main.bslots = &bslots;
-            use_basis = true;
-        } else {
-            main.d.clog = nullptr;
-            basis_cq = basis_c = nullptr;
-            bslots.tab = nullptr;
-        }
-    }
+    if (o->krylov_basis == CIQ_BASIS_AUTO && !precond && main.Q > 0)
+        STCHK(basis_acquire(main, dev, bslots, &basis_cq, &basis_c, st));
+    const bool use_basis = main.bslots != nullptr;
+    if (use_basis) main.solves = nullptr;   // formed after the run
 
     STCHK(main.iterate(st, check_every, pinned, &mvm_count, profile ? evs.data() : nullptr,
                        profile ? check_every : 0, &mvm_ms, &mvm_timed, o->graph == 1));
     const int iters = pinned->iter;
-    if (use_basis && iters > 0)
-        HIPCHK(launch_basis_combine(main.d, iters, basis_cq, basis_c, main.acc, main.max_n, st));
+    if (use_basis && iters > 0) {
+        if (solves_out)
+            HIPCHK(launch_basis_solves<T>(main.d, iters, basis_cq, main.acc, static_cast<T*>(solves_out), s, s,
+                                          main.max_n, st));
+        else
+            HIPCHK(launch_basis_combine(main.d, iters, basis_cq, basis_c, main.acc, main.max_n, st));
+    } else if (use_basis && solves_out) {   // every column of B is zero
+        HIPCHK(launch_fill<T>(static_cast<T*>(solves_out), (size_t)main.rows_total * main.Q * s, (T)0, st));
+    }
 
     // ---- combine -----------------------------------------------------------
     if (mode == CIQ_SQRT) {
@@ -1655,7 +1704,7 @@ int solve(int nprob, const ciq_problem* probs, const ciq_opts* o, const void* co
             HIPCHK((launch_copy<double, T>(main.acc + (size_t)main.h_off[p] * sr, sr, main.h_n[p], s,
                                            static_cast<T*>(out_ptrs[p]), ldo, st)));
     }
-    if (solves_out) {
+    if (solves_out && !use_basis) {
         HIPCHK((launch_copy<double, T>(main.solves, sr, main.rows_total * main.Q, s, static_cast<T*>(solves_out),
                                        s, st)));
     }
@@ -1751,6 +1800,7 @@ int backward_impl(const ciq_problem* p, const ciq_opts* o, int mode, const doubl
     r.keep_solves = true;
     r.fine_acc = sqrt_mode ? 0 : 1;
     r.cached = (kc.ptr != nullptr);
+    r.wide_allowed = sqrt_mode;
     r.plan(2);
 
     const int kpad = grad_k_pad((Q + (sqrt_mode ? 1 : 0)) * s);
@@ -1774,6 +1824,8 @@ int backward_impl(const ciq_problem* p, const ciq_opts* o, int mode, const doubl
     Carver c(base);
     r.layout(c, true);
     extra(c, &U, &V, &pts, &xd, &part);
+    r.choose_wide(sqrt_mode, 1.0);
+    r.configure(2);
     r.fill_dev();
     STCHK(r.upload_tables(st));
     STCHK(setup_points(r, p, dtype, st));
@@ -1799,11 +1851,23 @@ int backward_impl(const ciq_problem* p, const ciq_opts* o, int mode, const doubl
         HIPCHK(launch_reduce_splits<double>(r.ypart, r.ysplit, r.nsplit, sr, n, sr, r.qbuf[0], sr, st));
     }
     HIPCHK(hipStreamSynchronize(st));   // t/w came from caller-owned host memory
+    BasisSlots bslots;
+    double *basis_cq = nullptr, *basis_c = nullptr;
+    double* const gq = r.solves;    // [rows][Q][sr] FP64, formed after the run or during it
+    if (o->krylov_basis == CIQ_BASIS_AUTO) STCHK(basis_acquire(r, dev, bslots, &basis_cq, &basis_c, st));
+    const bool use_basis = r.bslots != nullptr;
+    if (use_basis) r.solves = nullptr;
     int mvm_count = sqrt_mode ? 1 : 0, dummy_n = 0;
     double dummy = 0.0;
     STCHK(r.iterate(st, o->check_every > 0 ? o->check_every : 16, pinned, &mvm_count, nullptr, 0, &dummy,
                     &dummy_n));
     const int iters = pinned->iter;
+    if (use_basis) {
+        if (iters > 0)
+            HIPCHK(launch_basis_solves<double>(r.d, iters, basis_cq, r.acc, gq, sr, sr, n, st));
+        else
+            HIPCHK(launch_fill<double>(gq, (size_t)n * Q * sr, 0.0, st));
+    }
     if (db) HIPCHK((launch_copy<double, T>(r.acc, sr, n, s, static_cast<T*>(db), lddb, st)));
 
     double acc_h[CIQ_MAX_D + 2] = {0};
@@ -1813,7 +1877,7 @@ int backward_impl(const ciq_problem* p, const ciq_opts* o, int mode, const doubl
         double scale[CIQ_MAX_D];
         for (int k = 0; k < p->d; ++k) scale[k] = 1.0 / p->lengthscale[p->n_lengthscale == 1 ? 0 : k];
         HIPCHK(launch_prep<double>(xd, n, p->d, dpg, scale, pts, st));
-        HIPCHK(launch_build_uv<T>(r.solves, sr, static_cast<const T*>(solves), static_cast<const T*>(g), ldg, r.w, n,
+        HIPCHK(launch_build_uv<T>(gq, sr, static_cast<const T*>(solves), static_cast<const T*>(g), ldg, r.w, n,
                                   Q, s, sqrt_mode ? 1 : 0, U, V, st));
         int nblocks = 0;
         HIPCHK(launch_grad_pass(p->kernel, U, V, kpad, pts, n, dpg, part, &nblocks, st));
@@ -1841,6 +1905,7 @@ int backward_impl(const ciq_problem* p, const ciq_opts* o, int mode, const doubl
     info->mvm_count = mvm_count;
     info->max_rel_residual = mr;
     info->kernel_cached = (kc.ptr != nullptr) ? 1 : 0;
+    info->krylov_basis = use_basis ? 1 : 0;
     for (int q = 0; q < Q; ++q) {
         info->t[q] = t[q];
         info->w[q] = w[q];
@@ -2075,6 +2140,7 @@ int ciq_kernel_mvm_resident(const ciq_problem* p, int dtype, const void* v, int 
         r.Q = 0;
         r.max_iter = 1;
         r.cached = true;
+        r.wide_allowed = true;
         r.plan(2);
         Sizer sz;
         r.layout(sz, true);
@@ -2082,6 +2148,7 @@ int ciq_kernel_mvm_resident(const ciq_problem* p, int dtype, const void* v, int 
         STCHK(scratch_reserve(dev, sz.off + 4096, &base));
         Carver c(base);
         r.layout(c, true);
+        r.choose_wide(true, 1.0);
         r.fill_dev();
         STCHK(r.upload_tables(stream));
         STCHK(setup_points(r, p, dtype, stream));

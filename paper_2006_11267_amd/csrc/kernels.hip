@@ -113,13 +113,15 @@ hipError_t launch_mvm(int dtype, const MvmArgs& a, hipStream_t st) {
         return hipErrorInvalidValue;
     if (dtype == CIQ_F32 && a.vt != nullptr)
         return a.kt != nullptr ? launch_mvm_kx(a, st) : hipErrorInvalidValue;
-    // The FP64 forms take several groups of 64 columns in one launch (more
-    // blocks to fill the chip: N = 3,000, S = 256 resident 137 -> 100 us); a
+    // The FP64 forms and the resident FP32 one take several groups of 64
+    // columns in one launch (more blocks to fill the chip: N = 3,000, S = 256
+    // resident FP64 137 -> 90 us); a
     // remainder of at most 32 columns stays a launch of its own, which has a
     // kernel of its width.
     const int cap = product_cap(dtype, a.kt != nullptr);
     const int rem = a.s % 64;
-    const int wide = (dtype == CIQ_F64) ? ((rem > 0 && rem <= 32) ? a.s - rem : a.s) : 0;
+    const bool grouped = dtype == CIQ_F64 || (dtype == CIQ_F32 && a.kt != nullptr && a.wl == nullptr);
+    const int wide = grouped ? ((rem > 0 && rem <= 32) ? a.s - rem : a.s) : 0;
     for (int c0 = 0; c0 < a.s;) {
         MvmArgs g = a;
         const int take = (c0 < wide) ? wide : std::min(cap, a.s - c0);
@@ -1307,6 +1309,77 @@ __global__ __launch_bounds__(256) void basis_gemv_kernel(Dev d, const double* __
     for (; j < J; ++j) t = fma(cg[(long long)j * cs], tab[j][idx], t);
     acc[idx] = t;
 }
+
+// The per-shift solutions as well: x^{(q)}[i][c] = (1 / w_q) sum_j cq[j][q][g]
+// q_{j+1}[i][c] (the logged weights carry w_q) for the shifts q0 .. q0 + 15, and
+// acc = sum_q w_q x^{(q)} in the launch of the first shifts (partial sums of
+// later launches add to it). A thread holds four rows x 16 shifts of one
+// column: the basis is read once per 16 shifts (1.5 GB at N = 5,000, S = 256,
+// 144 iterations: 0.4 ms), the coefficients once per four rows, from L1 for
+// three of a block's four waves. The direction recurrence moved five vectors
+// of Q columns every iteration instead (82 us each there, 12 ms in all).
+template <typename TO>
+__global__ __launch_bounds__(256) void basis_solves_kernel(Dev d, int iters, int q0, const double* __restrict__ cq,
+                                                           double* __restrict__ acc, TO* __restrict__ out, int ldo,
+                                                           int s_out) {
+    constexpr int R = 4, QT = 16;
+    const int s = d.s, n = d.n[0], Q = d.Q;
+    const int c = blockIdx.y * 64 + (threadIdx.x & 63);
+    const int i0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * R;
+    if (c >= s || i0 >= n) return;
+    const int J = min(min(d.col_iters[c], d.basis_slots), iters);
+    const int nq = min(QT, Q - q0);
+    double* const* __restrict__ tab = d.basis;
+    double x[R][QT];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int k = 0; k < QT; ++k) x[r][k] = 0.0;
+    long long idx[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) idx[r] = (long long)min(i0 + r, n - 1) * s + c;
+    const double* __restrict__ cj = cq + (long long)q0 * d.ncol + c;
+    const long long step = (long long)Q * d.ncol;
+    for (int j = 0; j < J; ++j, cj += step) {
+        const double* __restrict__ v = tab[j];
+        double vr[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) vr[r] = __builtin_nontemporal_load(v + idx[r]);
+#pragma unroll
+        for (int k = 0; k < QT; ++k) {
+            const double w = cj[(long long)min(k, nq - 1) * d.ncol];
+#pragma unroll
+            for (int r = 0; r < R; ++r) x[r][k] = fma(w, vr[r], x[r][k]);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if (i0 + r >= n) break;
+        double sum = (q0 == 0) ? 0.0 : acc[idx[r]];
+#pragma unroll
+        for (int k = 0; k < QT; ++k) {
+            if (k >= nq) break;
+            sum += x[r][k];
+            if (c < s_out) out[((long long)(i0 + r) * Q + q0 + k) * ldo + c] = (TO)(x[r][k] / d.w[q0 + k]);
+        }
+        acc[idx[r]] = sum;
+    }
+}
+
+template <typename TO>
+hipError_t launch_basis_solves(const Dev& d, int iters, double* cq, double* acc, TO* out, int ldo, int s_out, int n,
+                               hipStream_t st) {
+    if (iters <= 0 || d.basis == nullptr || d.clog == nullptr || d.nprob != 1) return hipErrorInvalidValue;
+    const int QN = d.Q * d.ncol;
+    hipLaunchKernelGGL(basis_coef_kernel, dim3((QN + 255) / 256), dim3(256), 0, st, d, iters, cq);
+    // the coefficients past a column's own run are not read (J above)
+    for (int q0 = 0; q0 < d.Q; q0 += 16)
+        hipLaunchKernelGGL(basis_solves_kernel<TO>, dim3((n + 15) / 16, (d.s + 63) / 64), dim3(256), 0, st, d, iters, q0,
+                           cq, acc, out, ldo, s_out);
+    return hipGetLastError();
+}
+template hipError_t launch_basis_solves<float>(const Dev&, int, double*, double*, float*, int, int, int, hipStream_t);
+template hipError_t launch_basis_solves<double>(const Dev&, int, double*, double*, double*, int, int, int, hipStream_t);
 
 // tab[t] for slots t in [first, end): slot t sits at byte offset
 // (t % per_chunk) * stride of chunk t / per_chunk, whose base is

@@ -316,15 +316,17 @@ __global__ __launch_bounds__(64 * WAVES) void mvm_kt_kernel(MvmArgs a) {
 // in the noise-level eigendirections that the inverse root amplifies, and
 // it grows as the square root of the MFMA steps B one FP32 sum spans.
 // NACC picks B: NACC accumulators take the chunk's 16 steps in rotation
-// (B = 16 / NACC, NACC = 4). NACC = -1
+// (B = 16 / NACC, NACC = 1 or 4). NACC = -1
 // contracts on the FP64 MFMA instead, the FP32 operands converted as they
 // are used (two converts per MFMA, no FP32 sums at all): at half the FP32
 // MFMA rate, which launches of at most 32 columns can afford, since they
 // stream K at HBM speed with the matrix cores less than half busy. Those
-// launches use B = 4, or the FP64 MFMA for the inverse root (a.acc); a
-// batched 64-column launch uses B = 4. A single problem of more than 32
-// columns would be MFMA-bound here and runs on the FP16 matrix cores
-// (mvm_kx.hip).
+// launches use B = 4, or the FP64 MFMA for the inverse root (a.acc); the
+// 64-column launch is MFMA-bound and uses B = 16, or B = 4 for the inverse
+// root (plain solves of more than 32 columns run on the FP16 matrix cores
+// where their conditioning allows, mvm_kx.hip). A single problem's column
+// groups of 64 run in one launch (grid.y): at N = 5,000, S = 256 one group
+// leaves the chip's last round of blocks mostly idle (206 against 140 us).
 // Batched runs (a.wl set) keep one such matrix per problem (a.pkt: its
 // element offset, a.pnjs: its padded columns / 4) and run persistently: a
 // grid of the resident blocks takes (problem, row block, column range) items
@@ -344,10 +346,11 @@ __device__ __forceinline__ void kt32_item(const MvmArgs& a, int p, int rb, int s
     const float* kt = static_cast<const float*>(a.kt) + ((p < 0) ? 0 : a.pkt[p]);
     const double o2 = (p < 0) ? a.o2 : (double)a.po2[p];
     const double s2 = (p < 0) ? a.s2 : (double)a.ps2[p];
-    const float* __restrict__ v = static_cast<const float*>(a.v) + off * a.ldv;
-    double* __restrict__ y = static_cast<double*>(a.y) + (long long)split * a.ysplit + off * a.ldy;
-    float* __restrict__ y32 = a.y32 ? a.y32 + (long long)split * a.ysplit + off * a.ldy : nullptr;
-    const int s = a.s, ldv = a.ldv, ldy = a.ldy;
+    const int g0 = (int)blockIdx.y * 64;         // column group of a wide launch (0 in batched ones)
+    const float* __restrict__ v = static_cast<const float*>(a.v) + off * a.ldv + g0;
+    double* __restrict__ y = static_cast<double*>(a.y) + (long long)split * a.ysplit + off * a.ldy + g0;
+    float* __restrict__ y32 = a.y32 ? a.y32 + (long long)split * a.ysplit + off * a.ldy + g0 : nullptr;
+    const int s = min(a.s - g0, 64), ldv = a.ldv, ldy = a.ldy;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: keeps bases in SGPRs
@@ -360,7 +363,7 @@ __device__ __forceinline__ void kt32_item(const MvmArgs& a, int p, int rb, int s
 
     // FP32 sums of B = 16 / NACC steps, FP64 beyond;
     // NACC = -1: FP64 MFMA, in two chains when the wave has one output tile
-    static_assert(NACC == -1 || NACC == 4, "accumulator rotation");
+    static_assert(NACC == -1 || NACC == 1 || NACC == 4, "accumulator rotation");
     constexpr bool F64M = NACC < 0;
     constexpr int NA = NACC > 0 ? NACC : 1;
     constexpr int NC = (F64M && RT * NSB == 1) ? 2 : 1;
@@ -717,7 +720,7 @@ static int occupancy_of(K kernel, int threads = 256) {
 }
 
 // accumulator rotation of a launch (see kt32_item)
-constexpr int kt32_nacc(int nsb, int acc) { return nsb <= 2 && acc ? -1 : 4; }
+constexpr int kt32_nacc(int nsb, int acc) { return nsb <= 2 ? (acc ? -1 : 4) : (acc ? 4 : 1); }
 
 template <int NSB, int RT, int NACC>
 hipError_t launch_kt32_variant(const MvmArgs& a, int grid, hipStream_t st) {
@@ -738,7 +741,8 @@ hipError_t launch_kt32_variant(const MvmArgs& a, int grid, hipStream_t st) {
         }
         grid = std::min(a.nitems, slots);
     }
-    hipLaunchKernelGGL((mvm_kt32_kernel<NSB, RT, 4, 2, NACC>), dim3(grid), dim3(256), 0, st, a);
+    const int groups = (a.wl == nullptr) ? (a.s + 63) / 64 : 1;
+    hipLaunchKernelGGL((mvm_kt32_kernel<NSB, RT, 4, 2, NACC>), dim3(grid, groups), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 

@@ -60,3 +60,39 @@ def test_batched_step_widths(s):
             ref = U @ ((U.T @ b.astype(np.float64)) / np.sqrt(lam)[:, None])
             assert i["converged"]
             assert colwise_rel(o.double().cpu().numpy(), ref).max() < 1e-4
+
+
+# rows around the four a thread and the 16 a block, shifts around the 16 a
+# launch, columns around the 64-column blocks and the padding
+@pytest.mark.parametrize("n,s,q", [(1, 1, 3), (17, 2, 16), (63, 5, 17), (130, 65, 15), (1030, 3, 33)])
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+def test_kept_solves_from_basis(n, s, q, prec):
+    """Per-shift solves formed from the resident basis against dense shifted
+    solves: FP64 run to 1e-12 relative residual (1e-9 of the solve: the
+    residual over the smallest shifted eigenvalue, 0.5, times the 25-fold
+    norm of this K), FP32 products 1e-4 (the FP32 bar). A zero column keeps
+    zero solves."""
+    torch = torch_cuda()
+    ciq = ciq_module()
+    rng = np.random.default_rng(7 * n + s)
+    dt = np.float64 if prec == "f64" else np.float32
+    x, b = rng.random((n, 3)).astype(dt), rng.standard_normal((n, s)).astype(dt)
+    if s > 2:
+        b[:, 2] = 0.0
+    K = okern.kernel_matrix("rbf", x.astype(np.float64), [0.2], 1.0, 0.5)
+    announce(f"kept solves n={n} s={s} q={q} {prec}")
+    prob = ciq.Problem(torch.from_numpy(x).cuda(), "rbf", [0.2], 1.0, 0.5)
+    out, info, solves = ciq.ciq_invsqrt_mvm(prob, torch.from_numpy(b).cuda(), q=q, max_iter=500,
+                                            tol=1e-12 if prec == "f64" else 1e-6, keep_solves=True)
+    assert info["krylov_basis"] and info["converged"]
+    live = [c for c in range(s) if np.any(b[:, c])]
+    bar = 1e-9 if prec == "f64" else 1e-4
+    acc = np.zeros((n, len(live)))
+    for k in range(q):
+        ref = np.linalg.solve(K + info["t"][k] * np.eye(n), b[:, live].astype(np.float64))
+        got = solves[:, k, :].double().cpu().numpy()
+        assert colwise_rel(got[:, live], ref).max() < bar
+        if s > 2:
+            assert np.all(got[:, 2] == 0.0)
+        acc += info["w"][k] * ref
+    assert colwise_rel(out.double().cpu().numpy()[:, live], acc).max() < bar
