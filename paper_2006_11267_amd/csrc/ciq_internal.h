@@ -373,7 +373,10 @@ int lr_apply_blocks(int n);
 hipError_t launch_lr_apply(double alpha0, const double* X, int ldx, const double* A, int lda,
                            const double* T, int ldt, int n, int R, int S, double* Y, int ldy,
                            double* dotp, const int* colmask, const int* done, hipStream_t st,
-                           int accumulate = 0);   // 1: Y += alpha0 X + A T
+                           int accumulate = 0,    // 1: Y += alpha0 X + A T
+                           int ranges = 1,        // > 1: range z of r (alpha0 X with z = 0) to Y + z zstride
+                           long long zstride = 0);
+int lr_apply_ranges(int n, int R, int S);   // ranges that fill the chip (1..4)
 // out[c] = sum_b dotp[b][c] (fixed order), b < nblk
 hipError_t launch_lr_dotsum(const double* dotp, int nblk, int S, double* out, const int* done,
                             hipStream_t st);

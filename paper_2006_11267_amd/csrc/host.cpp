@@ -625,6 +625,7 @@ struct Run {
     bool keep_solves = false;
     int fine_acc = 0;      // FP32 resident products: the finer FP64 accumulation (inverse root)
     bool cached = false;   // products stream a resident kernel matrix (kt)
+    bool with_post = false;      // products carry a posterior's correction
     bool wide_allowed = false;   // the wide FP32 form may be chosen
     bool wide = false;           // and is
     bool precond = false;  // preconditioned run (single problem): Lanczos in the P^{-1} inner product
@@ -829,7 +830,8 @@ struct Run {
         }
         if (kx) nsplit = kx_split;
         if (nprob > 1 && nsplit_fixed > 0) nsplit = nsplit_fixed;
-        if (sp || dn) nsplit = 1;   // the sparse / dense products write one partial
+        if (sp) nsplit = 1;   // the sparse product writes one partial
+        if (dn) nsplit = lr_apply_ranges(max_n, max_n, s);
         ysplit = (long long)rows_total * s;
     }
 
@@ -848,6 +850,7 @@ struct Run {
         }
         wide = w0;
         if (nprob > 1) nsplit_alloc = std::max(nsplit_alloc, 4);   // the tuner's batched candidates
+        if (with_post) nsplit_alloc += 4;                          // the correction's partials
         configure(rt_);
     }
 
@@ -967,14 +970,15 @@ struct Run {
             return CIQ_OK;
         }
         const float* y32 = (part32 && nsplit > 1) ? ypart32 : nullptr;
+        const int np = nsplit + post_ranges();   // partials to add up
         if (step_owner_ok(d, max_n)) {
-            HIPCHK(launch_step_owner(d, ypart, ysplit, nsplit, qcur, qprv, q32, max_n, st, y32, op16()));
+            HIPCHK(launch_step_owner(d, ypart, ysplit, np, qcur, qprv, q32, max_n, st, y32, op16()));
             if (Q > 0 && d.basis == nullptr)   // the direction recurrence's vectors
                 HIPCHK(launch_update<double>(d, nullptr, 0, 1, qcur, qprv, mprv, mcur, acc, solves, nullptr, max_n,
                                              st));
             return CIQ_OK;
         }
-        HIPCHK(launch_dots<double>(d, ypart, ysplit, nsplit, qcur, qprv, 0, st, y32));   // also reduces the splits
+        HIPCHK(launch_dots<double>(d, ypart, ysplit, np, qcur, qprv, 0, st, y32));   // also reduces the splits
         HIPCHK(launch_colsum(d, 0, st));
         HIPCHK(launch_dots<double>(d, ypart, ysplit, 1, qcur, qprv, 1, st));
         HIPCHK(launch_colsum(d, 1, st));
@@ -984,15 +988,23 @@ struct Run {
         return CIQ_OK;
     }
 
-    // Posterior covariance: the product's first partial += -W (W^T v) for the
-    // FP64 operand v (rows_total x s).
+    // Posterior covariance: -W (W^T v) for the FP64 operand v (rows_total x s),
+    // in ranges as further partials of the product after its own nsplit, or
+    // (one range, or no room among the 16 partials the inner products take)
+    // added to the first.
+    int post_ranges() const {
+        const int r = post ? lr_apply_ranges(rows_total, post->n, s) : 0;
+        return r > 1 && nsplit + r <= 16 ? r : 0;
+    }
     int post_correct(const double* v, const int* done, hipStream_t st) {
         if (!post) return CIQ_OK;
         const int nch = lr_part_chunks(rows_total, post->n, s);
         HIPCHK(launch_lr_part(post->W, post->ldw, v, s, rows_total, post->n, s, nch, post->part, done, st));
         HIPCHK(launch_lr_reduce(post->part, nch, post->n, s, post->fneg, post->T, s, done, st));
-        HIPCHK(launch_lr_apply(0.0, nullptr, 0, post->W, post->ldw, post->T, s, rows_total, post->n, s, ypart, s,
-                               nullptr, nullptr, done, st, 1));
+        const int r = post_ranges();
+        HIPCHK(launch_lr_apply(0.0, nullptr, 0, post->W, post->ldw, post->T, s, rows_total, post->n, s,
+                               ypart + (r ? (size_t)nsplit * ysplit : 0), s, nullptr, nullptr, done, st, r ? 0 : 1,
+                               r ? r : 1, ysplit));
         return CIQ_OK;
     }
 
@@ -1004,7 +1016,7 @@ struct Run {
         }
         if (dn) {
             HIPCHK(launch_lr_apply(0.0, nullptr, 0, dn->A, dn->n, qbuf[(j - 1) & 1], s, rows_total, dn->n, s, ypart,
-                                   s, nullptr, nullptr, &d.st->done, st));
+                                   s, nullptr, nullptr, &d.st->done, st, 0, nsplit, ysplit));
             return CIQ_OK;
         }
         MvmArgs a = mvm_args(operand(j), ypart);
@@ -1497,6 +1509,7 @@ int solve(int nprob, const ciq_problem* probs, const ciq_opts* o, const void* co
     // (inverse roots: kept solves feed gradients, whose sums cancel, and a
     // posterior's products carry noise of the prior's size, see choose_wide)
     main.wide_allowed = !precond && (mode == CIQ_SQRT || (post_spec == nullptr && solves_out == nullptr));
+    main.with_post = post_spec != nullptr;
     main.plan(2);
 
     Run<T> bnd;
@@ -1511,6 +1524,7 @@ int solve(int nprob, const ciq_problem* probs, const ciq_opts* o, const void* co
     bnd.precond = precond;
     bnd.sp = sparse;
     bnd.dn = dense;
+    bnd.with_post = main.with_post;
     bnd.plan(2);
 
     Sizer sz;
@@ -1691,13 +1705,14 @@ int solve(int nprob, const ciq_problem* probs, const ciq_opts* o, const void* co
             HIPCHK(launch_spmv(*sparse, main.acc, sr, sr, main.ypart, sr, nullptr, st));
         else if (dense)
             HIPCHK(launch_lr_apply(0.0, nullptr, 0, dense->A, dense->n, main.acc, sr, main.rows_total, dense->n, sr,
-                                   main.ypart, sr, nullptr, nullptr, nullptr, st));
+                                   main.ypart, sr, nullptr, nullptr, nullptr, st, 0, main.nsplit, main.ysplit));
         else
             HIPCHK(launch_mvm(dtype, a, st));
         STCHK(main.post_correct(main.acc, nullptr, st));
         mvm_count += 1;
         for (int p = 0; p < nprob; ++p)
-            HIPCHK(launch_reduce_splits<T>(main.ypart + (size_t)main.h_off[p] * sr, main.ysplit, main.nsplit, sr,
+            HIPCHK(launch_reduce_splits<T>(main.ypart + (size_t)main.h_off[p] * sr, main.ysplit,
+                                           main.nsplit + main.post_ranges(), sr,
                                            main.h_n[p], s, static_cast<T*>(out_ptrs[p]), ldo, st));
     } else {
         for (int p = 0; p < nprob; ++p)

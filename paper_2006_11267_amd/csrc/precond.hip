@@ -169,31 +169,35 @@ __global__ __launch_bounds__(256) void pchol_col_kernel(PcholArgs a, int m) {
 // the accumulator holds D[l/16 + 4v][l%16] in register v.
 typedef double pdx4 __attribute__((ext_vector_type(4)));
 
-// part: the block owns 128 r x 64 s of one row chunk; wave w the r-tiles
-// r0 + 32 w + {0, 16} against four 16-column s-tiles (8 accumulators).
+// part: the block owns 128 r x 16 NSB s of one row chunk; wave w the r-tiles
+// r0 + 32 w + {0, 16} against NSB 16-column s-tiles (2 NSB accumulators).
 // MFMA (i, k, j) = (r, row, s): A-operand A[row][r] (16 consecutive r per
 // row, loaded into registers one group of four k-steps ahead), B-operand
 // X[row][s] from double-buffered LDS tiles of 16 rows shared by the four
-// waves (X is read once per block instead of once per wave).
+// waves (X is read once per block instead of once per wave). Bound by its
+// loads' latency and by the partials it writes (lr_part_chunks); the narrow
+// forms spend no matrix time on columns that are not there.
 constexpr int kPartRows = 16;
+template <int NSB>
 __global__ __launch_bounds__(256) void lr_part_kernel(const double* __restrict__ A, int lda,
                                                       const double* __restrict__ X, int ldx, int n, int R, int S,
                                                       int rows_per_chunk, double* __restrict__ part,
                                                       const int* done) {
     if (done != nullptr && *done) return;
-    __shared__ double Xs[2][kPartRows][80];
+    constexpr int SW = 16 * NSB, XPT = kPartRows * SW / 256;
+    __shared__ double Xs[2][kPartRows][SW + 16];
     const int chunk = blockIdx.x, tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63, lr = lane & 15, lk = lane >> 4;
-    const int r0 = blockIdx.y * 128 + wave * 32, s0 = blockIdx.z * 64;
+    const int r0 = blockIdx.y * 128 + wave * 32, s0 = blockIdx.z * SW;
     const int i0 = chunk * rows_per_chunk;
     const int i1 = min(n, i0 + rows_per_chunk);
     const bool ra_ok[2] = {r0 + lr < R, r0 + 16 + lr < R};
-    pdx4 acc[2][4];
+    pdx4 acc[2][NSB];
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int sb = 0; sb < 4; ++sb) acc[t][sb] = pdx4{0.0, 0.0, 0.0, 0.0};
-    double ga[4][2], xn[4];
+        for (int sb = 0; sb < NSB; ++sb) acc[t][sb] = pdx4{0.0, 0.0, 0.0, 0.0};
+    double ga[4][2], xn[XPT];
     auto load_a = [&](int ib, double (&dst)[4][2]) {
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
@@ -206,17 +210,17 @@ __global__ __launch_bounds__(256) void lr_part_kernel(const double* __restrict__
     };
     auto load_x = [&](int ib) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int e = tid + 256 * k, row = e >> 6, cc = e & 63;
+        for (int k = 0; k < XPT; ++k) {
+            const int e = tid + 256 * k, row = e / SW, cc = e % SW;
             const int i = ib + row, c = s0 + cc;
             xn[k] = (i < i1 && c < S) ? X[(long long)i * ldx + c] : 0.0;
         }
     };
     auto store_x = [&](int buf) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < XPT; ++k) {
             const int e = tid + 256 * k;
-            Xs[buf][e >> 6][e & 63] = xn[k];
+            Xs[buf][e / SW][e % SW] = xn[k];
         }
     };
     if (i0 < i1) {
@@ -238,7 +242,7 @@ __global__ __launch_bounds__(256) void lr_part_kernel(const double* __restrict__
 #pragma unroll
             for (int t = 0; t < 2; ++t)
 #pragma unroll
-                for (int sb = 0; sb < 4; ++sb)
+                for (int sb = 0; sb < NSB; ++sb)
                     acc[t][sb] = __builtin_amdgcn_mfma_f64_16x16x4f64(ga[g][t], Xs[cur][4 * g + lk][sb * 16 + lr],
                                                                       acc[t][sb], 0, 0, 0);
         if (more) {
@@ -255,7 +259,7 @@ __global__ __launch_bounds__(256) void lr_part_kernel(const double* __restrict__
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int sb = 0; sb < 4; ++sb) {
+        for (int sb = 0; sb < NSB; ++sb) {
             const int sc = s0 + sb * 16 + lr;
             if (sc >= S) continue;
 #pragma unroll
@@ -294,79 +298,98 @@ __global__ __launch_bounds__(256) void lr_reduce_kernel(const double* __restrict
     }
 }
 
-// apply: the block owns 64 rows x 64 s; wave w rows i0 + 16 w against four
-// s-tiles. MFMA (i, k, j) = (row, r, s): A-operand A[row][r] (each lane walks
-// its row, loaded into registers one slab ahead), B-operand T[r][s] from
-// double-buffered LDS slabs of 32 r shared by the four waves (T is read once
-// per block instead of once per wave). The slabs (36 KB) are the block's
-// only LDS -- the column-sum scratch reuses them after the last slab -- so
-// four blocks fit on a CU and a 50,000-row launch (782 blocks) is resident
-// at once.
+// apply: the block owns 64 rows x 16 NSB s of one range of r (grid.z, whose
+// sums go to Y + z zstride); wave w rows i0 + 16 w against NSB s-tiles. MFMA
+// (i, k, j) = (row, r, s): A-operand A[row][r] (each lane walks its row, loaded
+// into registers one slab ahead), B-operand T[r][s] from double-buffered LDS
+// slabs of 32 r shared by the four waves (T is read once per block instead of
+// once per wave). Any order of r serves the MFMA as long as both operands
+// agree, so lane group l / 16 takes four consecutive r of each 16: two 16-byte
+// loads a lane, 128 contiguous bytes a row, where A's rows are 16-byte aligned
+// (VEC). The slabs (36 KB at NSB = 4) are the block's only LDS -- the
+// column-sum scratch reuses them after the last slab -- so four blocks fit on
+// a CU. Bound by its loads' latency while the chip is not full: 10,000 rows
+// are 157 blocks, which took 87 us at R = 1,000, S = 64 (18 us of matrix time).
 constexpr int kApplySlab = 32;
-constexpr int kApplyLd = 72;
+template <int NSB, bool VEC>
 __global__ __launch_bounds__(256) void lr_apply_kernel(double alpha0, const double* X, int ldx,
                                                        const double* __restrict__ A, int lda,
                                                        const double* __restrict__ T, int ldt, int n, int R, int S,
                                                        double* Y, int ldy, double* __restrict__ dotp,
                                                        const int* __restrict__ colmask, const int* done,
-                                                       int accumulate) {
+                                                       int accumulate, int rlen, long long zstride) {
+    typedef double pdx2 __attribute__((ext_vector_type(2)));
     if (done != nullptr && *done) return;
-    __shared__ double lds[2 * kApplySlab * kApplyLd];
-    static_assert(16 * 64 <= 2 * kApplySlab * kApplyLd, "column-sum scratch must fit in the slab buffers");
-    auto Ts = reinterpret_cast<double (*)[kApplySlab][kApplyLd]>(lds);
-    auto red = reinterpret_cast<double (*)[64]>(lds);   // after the slab loop only
+    constexpr int SW = 16 * NSB, LD = SW + 8, TPT = kApplySlab * SW / 256;
+    constexpr int LDSN = 2 * kApplySlab * LD > 16 * SW ? 2 * kApplySlab * LD : 16 * SW;
+    __shared__ double lds[LDSN];
+    auto Ts = reinterpret_cast<double (*)[kApplySlab][LD]>(lds);
+    auto red = reinterpret_cast<double (*)[SW]>(lds);   // after the slab loop only
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63, lr = lane & 15, lk = lane >> 4;
-    const int i0 = blockIdx.x * 64, s0 = blockIdx.y * 64;
+    const int i0 = blockIdx.x * 64, s0 = blockIdx.y * SW;
+    const int rbeg = blockIdx.z * rlen, rend = min(R, rbeg + rlen);
     const int ia = i0 + wave * 16 + lr;           // this lane's A-operand row
     const bool ia_ok = ia < n;
     const double* arow = A + (long long)(ia_ok ? ia : 0) * lda;
-    pdx4 acc[4];
+    pdx4 acc[NSB];
 #pragma unroll
-    for (int sb = 0; sb < 4; ++sb) acc[sb] = pdx4{0.0, 0.0, 0.0, 0.0};
+    for (int sb = 0; sb < NSB; ++sb) acc[sb] = pdx4{0.0, 0.0, 0.0, 0.0};
     constexpr int G = kApplySlab / 4;             // k-steps per slab
-    double ga[G], tn[8];
+    double ga[G], tn[TPT];
+    // element 4 h + e of a slab: r = rb + 16 h + 4 lk + e
     auto load_a = [&](int rb, double* dst) {
+        if (VEC && rb + kApplySlab <= rend) {
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const int r = rb + 4 * g + lk;
-            dst[g] = (ia_ok && r < R) ? arow[r] : 0.0;
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const pdx2 v = *reinterpret_cast<const pdx2*>(arow + rb + 16 * h + 4 * lk + 2 * e);
+                    dst[4 * h + 2 * e] = ia_ok ? v[0] : 0.0;
+                    dst[4 * h + 2 * e + 1] = ia_ok ? v[1] : 0.0;
+                }
+        } else {
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                const int r = rb + 16 * (g >> 2) + 4 * lk + (g & 3);
+                dst[g] = (ia_ok && r < rend) ? arow[r] : 0.0;
+            }
         }
     };
     auto load_t = [&](int rb) {
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int e = tid + 256 * k, rr = e >> 6, cc = e & 63;
+        for (int k = 0; k < TPT; ++k) {
+            const int e = tid + 256 * k, rr = e / SW, cc = e % SW;
             const int r = rb + rr, c = s0 + cc;
-            tn[k] = (r < R && c < S) ? T[(long long)r * ldt + c] : 0.0;
+            tn[k] = (r < rend && c < S) ? T[(long long)r * ldt + c] : 0.0;
         }
     };
     auto store_t = [&](int buf) {
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
+        for (int k = 0; k < TPT; ++k) {
             const int e = tid + 256 * k;
-            Ts[buf][e >> 6][e & 63] = tn[k];
+            Ts[buf][e / SW][e % SW] = tn[k];
         }
     };
-    const int nslab = (R + kApplySlab - 1) / kApplySlab;
-    load_t(0);
+    const int nslab = (rend - rbeg + kApplySlab - 1) / kApplySlab;
+    load_t(rbeg);
     store_t(0);
-    load_a(0, ga);
+    load_a(rbeg, ga);
     __syncthreads();
     for (int sl = 0; sl < nslab; ++sl) {
         const int cur = sl & 1;
         double gn[G];
         const bool more = sl + 1 < nslab;
         if (more) {
-            load_t((sl + 1) * kApplySlab);
-            load_a((sl + 1) * kApplySlab, gn);
+            load_t(rbeg + (sl + 1) * kApplySlab);
+            load_a(rbeg + (sl + 1) * kApplySlab, gn);
         }
 #pragma unroll
         for (int g = 0; g < G; ++g)
 #pragma unroll
-            for (int sb = 0; sb < 4; ++sb)
-                acc[sb] = __builtin_amdgcn_mfma_f64_16x16x4f64(ga[g], Ts[cur][4 * g + lk][sb * 16 + lr], acc[sb], 0,
-                                                               0, 0);
+            for (int sb = 0; sb < NSB; ++sb)
+                acc[sb] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                    ga[g], Ts[cur][16 * (g >> 2) + 4 * lk + (g & 3)][sb * 16 + lr], acc[sb], 0, 0, 0);
         if (more) {
             store_t(cur ^ 1);
 #pragma unroll
@@ -374,9 +397,14 @@ __global__ __launch_bounds__(256) void lr_apply_kernel(double alpha0, const doub
         }
         __syncthreads();
     }
-    double dsum[4] = {0.0, 0.0, 0.0, 0.0};
+    if (blockIdx.z > 0) {                         // later ranges: their sums alone
+        X = nullptr;
+        Y += (long long)blockIdx.z * zstride;
+    }
+    double dsum[NSB];
 #pragma unroll
-    for (int sb = 0; sb < 4; ++sb) {
+    for (int sb = 0; sb < NSB; ++sb) {
+        dsum[sb] = 0.0;
         const int c = s0 + sb * 16 + lr;
         if (c >= S) continue;
         if (colmask != nullptr && colmask[c] == 0) continue;
@@ -393,9 +421,9 @@ __global__ __launch_bounds__(256) void lr_apply_kernel(double alpha0, const doub
     }
     if (dotp == nullptr) return;
 #pragma unroll
-    for (int sb = 0; sb < 4; ++sb) red[wave * 4 + lk][sb * 16 + lr] = dsum[sb];
+    for (int sb = 0; sb < NSB; ++sb) red[wave * 4 + lk][sb * 16 + lr] = dsum[sb];
     __syncthreads();
-    if (tid < 64 && s0 + tid < S) {
+    if (tid < SW && s0 + tid < S) {
         double sum = 0.0;
 #pragma unroll
         for (int g = 0; g < 16; ++g) sum += red[g][tid];
@@ -532,21 +560,48 @@ hipError_t launch_pchol_col(const PcholArgs& a, int m, hipStream_t st) {
     return hipGetLastError();
 }
 
-// Row chunks per (r, s) tile: at most 1024 blocks in all (four per CU), so
-// that no CU holds a fifth block that would set the launch's duration.
+// 16-column blocks of a block's s-tile
+static int lr_nsb(int S) { return S <= 16 ? 1 : S <= 32 ? 2 : 4; }
+
+// Row chunks per (r, s) tile, by a model of the time: a block takes about 1.9
+// us for 16 rows (its loads' latency) as long as the matrix time of the blocks
+// that share its CU (0.95 us each at 64 columns, four to a CU) is less, and
+// every chunk's partials are written and read once (4.5 TB/s). At 10,000
+// rows, R = 1,000, S = 64 the former rule (1024 blocks) wrote 65 MB of
+// partials: 35 + 11 us.
 int lr_part_chunks(int n, int R, int S) {
-    const int tiles = ((R + 127) / 128) * ((S + 63) / 64);
-    int nchunk = 1024 / tiles;
-    nchunk = std::min(nchunk, (n + 63) / 64);
-    return std::max(nchunk, 1);
+    const int nsb = lr_nsb(S);
+    const int tiles = ((R + 127) / 128) * ((S + 16 * nsb - 1) / (16 * nsb));
+    const double mfma = 0.24 * nsb;
+    double best = 1e300;
+    int pick = 1;
+    const int top = std::max(1, std::min(1024 / tiles, (n + 15) / 16));
+    for (int nchunk = 1; nchunk <= top; nchunk += std::max(1, nchunk / 16)) {
+        const double blocks = (double)tiles * nchunk, load = std::ceil(blocks / 256.0);
+        const double steps = std::ceil(std::ceil((double)n / nchunk) / 16.0) + 2.0;
+        const double us = steps * std::max(1.9, load * mfma) + (double)nchunk * R * S * 16.0 / 4.5e6;
+        if (us < best) {
+            best = us;
+            pick = nchunk;
+        }
+    }
+    return pick;
 }
 
 hipError_t launch_lr_part(const double* A, int lda, const double* X, int ldx, int n, int R, int S, int nchunk,
                           double* part, const int* done, hipStream_t st) {
     const int rows_per_chunk = (n + nchunk - 1) / nchunk;
-    dim3 grid(nchunk, (R + 127) / 128, (S + 63) / 64);
-    hipLaunchKernelGGL(lr_part_kernel, grid, dim3(256), 0, st, A, lda, X, ldx, n, R, S, rows_per_chunk, part,
-                       done);
+    const int nsb = lr_nsb(S);
+    dim3 grid(nchunk, (R + 127) / 128, (S + 16 * nsb - 1) / (16 * nsb));
+    if (nsb == 1)
+        hipLaunchKernelGGL(lr_part_kernel<1>, grid, dim3(256), 0, st, A, lda, X, ldx, n, R, S, rows_per_chunk, part,
+                           done);
+    else if (nsb == 2)
+        hipLaunchKernelGGL(lr_part_kernel<2>, grid, dim3(256), 0, st, A, lda, X, ldx, n, R, S, rows_per_chunk, part,
+                           done);
+    else
+        hipLaunchKernelGGL(lr_part_kernel<4>, grid, dim3(256), 0, st, A, lda, X, ldx, n, R, S, rows_per_chunk, part,
+                           done);
     return hipGetLastError();
 }
 
@@ -560,13 +615,46 @@ hipError_t launch_lr_reduce(const double* part, int nchunk, int R, int S, const 
 
 int lr_apply_blocks(int n) { return (n + 63) / 64; }
 
+// Ranges of r of an apply whose consumer adds them up: enough blocks for three
+// a CU, at least four slabs a range.
+int lr_apply_ranges(int n, int R, int S) {
+    const int nsb = lr_nsb(S);
+    const int blocks = lr_apply_blocks(n) * ((S + 16 * nsb - 1) / (16 * nsb));
+    const int slabs = (R + kApplySlab - 1) / kApplySlab;
+    return std::max(1, std::min({4, 768 / std::max(blocks, 1), slabs / 4}));
+}
+
+template <int NSB>
+static hipError_t launch_apply_nsb(dim3 grid, bool vec, double alpha0, const double* X, int ldx, const double* A,
+                                   int lda, const double* T, int ldt, int n, int R, int S, double* Y, int ldy,
+                                   double* dotp, const int* colmask, const int* done, hipStream_t st, int accumulate,
+                                   int rlen, long long zstride) {
+    if (vec)
+        hipLaunchKernelGGL((lr_apply_kernel<NSB, true>), grid, dim3(256), 0, st, alpha0, X, ldx, A, lda, T, ldt, n, R,
+                           S, Y, ldy, dotp, colmask, done, accumulate, rlen, zstride);
+    else
+        hipLaunchKernelGGL((lr_apply_kernel<NSB, false>), grid, dim3(256), 0, st, alpha0, X, ldx, A, lda, T, ldt, n, R,
+                           S, Y, ldy, dotp, colmask, done, accumulate, rlen, zstride);
+    return hipGetLastError();
+}
+
 hipError_t launch_lr_apply(double alpha0, const double* X, int ldx, const double* A, int lda, const double* T,
                            int ldt, int n, int R, int S, double* Y, int ldy, double* dotp, const int* colmask,
-                           const int* done, hipStream_t st, int accumulate) {
-    dim3 grid(lr_apply_blocks(n), (S + 63) / 64);
-    hipLaunchKernelGGL(lr_apply_kernel, grid, dim3(256), 0, st, alpha0, X, ldx, A, lda, T, ldt, n, R, S, Y, ldy,
-                       dotp, colmask, done, accumulate);
-    return hipGetLastError();
+                           const int* done, hipStream_t st, int accumulate, int ranges, long long zstride) {
+    if (ranges > 1 && (dotp != nullptr || accumulate)) return hipErrorInvalidValue;
+    const int nsb = lr_nsb(S);
+    const int slabs = (R + kApplySlab - 1) / kApplySlab;
+    const int rlen = (slabs + ranges - 1) / ranges * kApplySlab;
+    const dim3 grid(lr_apply_blocks(n), (S + 16 * nsb - 1) / (16 * nsb), ranges);
+    const bool vec = lda % 2 == 0 && (reinterpret_cast<uintptr_t>(A) & 15) == 0;
+    if (nsb == 1)
+        return launch_apply_nsb<1>(grid, vec, alpha0, X, ldx, A, lda, T, ldt, n, R, S, Y, ldy, dotp, colmask, done, st,
+                                   accumulate, rlen, zstride);
+    if (nsb == 2)
+        return launch_apply_nsb<2>(grid, vec, alpha0, X, ldx, A, lda, T, ldt, n, R, S, Y, ldy, dotp, colmask, done, st,
+                                   accumulate, rlen, zstride);
+    return launch_apply_nsb<4>(grid, vec, alpha0, X, ldx, A, lda, T, ldt, n, R, S, Y, ldy, dotp, colmask, done, st,
+                               accumulate, rlen, zstride);
 }
 
 hipError_t launch_lr_dotsum(const double* dotp, int nblk, int S, double* out, const int* done, hipStream_t st) {
