@@ -19,7 +19,7 @@ BUILD = os.path.join(ROOT, "_build")
 
 # the longest compiles first (the on-the-fly FP32 products take ~90 s)
 SOURCES = ["mvm_f32.hip", "mvm_f64.hip", "mvm_x3.hip",
-           "mvm_cache.hip", "mvm_kx.hip", "kernels.hip", "precond.hip", "sparse.hip", "grad.hip", "chol.hip", "elliptic.cpp",
+           "mvm_cache.hip", "mvm_kx.hip", "mvm_fx.hip", "kernels.hip", "precond.hip", "sparse.hip", "grad.hip", "chol.hip", "elliptic.cpp",
            "host.cpp"]
 
 # Packed FP32 (v_pk_*_f32) is disabled for every device pass. MFMA results

@@ -150,6 +150,8 @@ struct MvmArgs {
     int rt;                  // FP32 product: row tiles of 16 per wave (1 or 2)
     int acc;                 // FP32 resident product: 1 = the finer FP64 accumulation
                              // (inverse root), 0 = the faster one (see mvm_cache.hip)
+    int fx;                  // FP32 product, entries on the fly: 1 = on the BF16 matrix cores from
+                             // 17 columns on (mvm_fx.hip; nrb and rt as for 128 rows a block)
     int ard;                 // FP32 product: per-dimension scales differ
     double scale[CIQ_MAX_D]; // FP32 product: per-dimension scale of coordinate differences
     const double* pscale;    // batched: [nprob][CIQ_MAX_D] scales
@@ -205,6 +207,8 @@ hipError_t launch_mvm_kt32(const MvmArgs& a, int nsb, hipStream_t st);
 hipError_t launch_mvm_kt16(const MvmArgs& a, int nsb, hipStream_t st);
 // Wide resident FP32 product (mvm_kx.hip): any number of columns in one launch;
 // kx_plan picks rt and nsplit.
+constexpr int kFxRows = 128;   // rows of a block of launch_mvm_fx
+hipError_t launch_mvm_fx(const MvmArgs& a, int nsb, hipStream_t st);
 hipError_t launch_mvm_kx(const MvmArgs& a, hipStream_t st);
 int kx_rows_per_block(int rt);
 void kx_plan(int n, int s, int part_bytes, int& rt, int& nsplit);
@@ -242,7 +246,7 @@ struct SplitModel {
     int per_cu;              // blocks a CU holds
 };
 int model_nsplit(double blocks, int chunks, const SplitModel& m, double part_us, int max_split, double* us = nullptr);
-SplitModel mvm_split_model(int dtype, bool cached, int n, int nsb, int rt);
+SplitModel mvm_split_model(int dtype, bool cached, int n, int nsb, int rt, bool fx);
 hipError_t launch_mvm(int dtype, const MvmArgs& a, hipStream_t st);
 
 template <typename TI>

@@ -742,7 +742,7 @@ struct Run {
     }
 
     int rows_per_block() const {
-        return parts() == 3 ? kx_rows_per_block(rt) : cached ? 64 * rt : mvm_rows_per_block(dtype, s, rt);
+        return parts() == 3 ? kx_rows_per_block(rt) : fx() ? kFxRows : cached ? 64 * rt : mvm_rows_per_block(dtype, s, rt);
     }
     // parts of the split operand the products read: two for CIQ_F16X3, three
     // for the wide CIQ_F32 form; max_parts: what the layout has room for (the
@@ -752,6 +752,11 @@ struct Run {
         return dtype == CIQ_F16X3 ? 2 : (wide_allowed && kx_columns(dtype, cached, nprob, s)) ? 3 : 0;
     }
     int parts() const { return max_parts() == 3 ? (wide ? 3 : 0) : max_parts(); }
+    // the same choice where entries are evaluated in the product (mvm_fx.hip)
+    bool fx_form() const {
+        return wide_allowed && !sp && !dn && !cached && nprob == 1 && dtype == CIQ_F32 && s > 16;
+    }
+    bool fx() const { return wide && fx_form(); }
     // The inverse root passes FP32 noise of the products on multiplied by about
     // kappa / sqrt(N). The FP32 matrix cores with sums of 16 columns and the
     // wide form differ in that noise (the wide form has half of it): up to
@@ -763,7 +768,7 @@ struct Run {
     // product is most of a solve (3.7 -> 2.2 ms). The square root's FP32 path
     // had sums of 64 columns, whose own noise is as large as any difference.
     void choose_wide(bool sqrt_mode, double kappa) {
-        wide = max_parts() == 3 &&
+        wide = (max_parts() == 3 || fx_form()) &&
                (sqrt_mode || max_n >= 32768 || kappa <= 125.0 * std::sqrt((double)max_n));
         use_operand();
     }
@@ -774,7 +779,7 @@ struct Run {
     size_t op_words() const { return op_halfs(kcache_cols(max_n), nsbt, max_parts()) / 2; }
 
     void configure(int rt_) {
-        rt = rt_;
+        rt = fx() ? 2 : rt_;   // (a last group of at most 16 columns: the FP32 form with 128 rows)
         const bool kx = parts() == 3;
         int kx_split = 1;
         if (kx) kx_plan(max_n, s, part32 ? 4 : 8, rt, kx_split);
@@ -800,7 +805,7 @@ struct Run {
         if (nprob == 1 && !kx && !(sp || dn)) {
             const int cap = product_cap(dtype, cached);
             const int nsb = (std::min(s, cap) + 15) / 16;
-            SplitModel m = mvm_split_model(dtype, cached, max_n, nsb, rt);
+            SplitModel m = mvm_split_model(dtype, cached, max_n, nsb, rt, fx());
             const int bpc = cached ? kt_blocks_per_cu(dtype, nsb, rt, fine_acc) : 0;
             if (bpc > 0) m.per_cu = bpc;
             if (cached && (double)max_n * s * 8.0 > 1.2e7 && chunks >= 16 && nrb * 8 >= 512) {
@@ -910,6 +915,7 @@ struct Run {
         a.nsplit = nsplit;
         a.rt = rt;
         a.acc = fine_acc;
+        a.fx = fx();
         a.ard = ard;
         for (int k = 0; k < CIQ_MAX_D; ++k) a.scale[k] = h_scale[k];
         a.pscale = pscale;
@@ -1166,7 +1172,7 @@ struct Run {
 // the timed launches write only the partial buffer.
 template <typename T>
 int tune_rt(Run<T>& r, const void* operand, hipStream_t st) {
-    if (r.sp || r.dn || r.parts() == 3) {   // nothing to choose, or chosen by kx_plan
+    if (r.sp || r.dn || r.parts() == 3 || r.fx()) {   // nothing to choose, or chosen by the plan
         r.configure(1);
         return CIQ_OK;
     }
@@ -1945,6 +1951,7 @@ int backward_impl(const ciq_problem* p, const ciq_opts* o, int mode, const doubl
 // ---- on-the-fly kernel product (ciq_kernel_mvm and its allocation-free form)
 struct KmvmPlan {
     int dp, nrb, nsplit, rt;
+    int fx;                 // FP32 from 17 columns on: the split form (mvm_fx.hip)
     bool direct;            // FP64 into y directly (one split, <= 64 columns)
     size_t xbytes, ybytes;  // scaled points (256-byte rounded), FP64 split partials
     size_t bound;           // bytes that ciq_kernel_mvm_noalloc's documented limit counts
@@ -1966,13 +1973,14 @@ KmvmPlan kmvm_plan(const ciq_problem* p, int dtype, int s) {
     const int nsb = (std::min(s, cap) + 15) / 16, groups = (s + cap - 1) / cap;
     const int chunks = (p->n + 63) / 64;
     double best = 1e300;
-    for (int rt = 1; rt <= 2; ++rt) {
-        const int rpb = mvm_rows_per_block(dtype, s, rt);
-        if (rt == 2 && rpb == mvm_rows_per_block(dtype, s, 1)) break;   // no two-tile form
+    pl.fx = dtype == CIQ_F32 && s > 16;
+    for (int rt = pl.fx ? 2 : 1; rt <= 2; ++rt) {
+        const int rpb = pl.fx ? kFxRows : mvm_rows_per_block(dtype, s, rt);
+        if (!pl.fx && rt == 2 && rpb == mvm_rows_per_block(dtype, s, 1)) break;   // no two-tile form
         const int nrb = (p->n + rpb - 1) / rpb;
         const int max_split = (int)std::min<size_t>(16, std::max<size_t>(1, room / one));
         double us = 0.0;
-        const int ns = model_nsplit((double)nrb * groups, chunks, mvm_split_model(dtype, false, p->n, nsb, rpb / 64),
+        const int ns = model_nsplit((double)nrb * groups, chunks, mvm_split_model(dtype, false, p->n, nsb, rpb / 64, pl.fx),
                                     one * 2.0 / 4.5e6, max_split, &us);
         if (us < best) {
             best = us;
@@ -2024,6 +2032,7 @@ int kmvm_run(const ciq_problem* p, int dtype, const void* v, int s, int ldv, voi
     a.o2 = p->outputscale;
     a.s2 = p->noise;
     a.nrb = pl.nrb;
+    a.fx = pl.fx;
     if (launch_mvm(dtype, a, stream) != hipSuccess) return CIQ_EHIP;
     if (!pl.direct) {
         if (dtype == CIQ_F64)

@@ -54,8 +54,14 @@ int model_nsplit(double blocks, int chunks, const SplitModel& m, double part_us,
 // evaluation or the stream of K per 64 rows) and at N = 1,024 (one block per
 // CU). A resident matrix of at most 200 MB is served by the last-level cache,
 // about twice as fast as HBM.
-SplitModel mvm_split_model(int dtype, bool cached, int n, int nsb, int rt) {
+SplitModel mvm_split_model(int dtype, bool cached, int n, int nsb, int rt, bool fx) {
     SplitModel m{};
+    if (fx) {                    // blocks of 128 rows and eight waves
+        m.per_cu = nsb <= 4 ? 2 : 1;
+        m.t_blk = nsb <= 2 ? 1.9 : nsb <= 4 ? 2.5 : 4.9;
+        m.lat = nsb <= 2 ? 2.3 : nsb <= 4 ? 3.3 : 4.4;
+        return m;
+    }
     m.per_cu = nsb <= 2 ? 4 : 2;
     const double rows = rt;      // in units of 64
     if (cached) {
@@ -155,7 +161,9 @@ hipError_t launch_mvm(int dtype, const MvmArgs& a, hipStream_t st) {
                 e = a.ard ? launch_mvm_f64_m52_ard(g, nsb, a.nrb, st) : launch_mvm_f64_m52_iso(g, nsb, a.nrb, st);
         } else {
             g.v = static_cast<const float*>(a.v) + c0;
-            if (a.kernel == CIQ_KERNEL_RBF)
+            if (a.fx && a.wl == nullptr && nsb >= 2)
+                e = launch_mvm_fx(g, nsb, st);
+            else if (a.kernel == CIQ_KERNEL_RBF)
                 e = a.ard ? launch_mvm_f32_rbf_ard(g, nsb, a.nrb, st) : launch_mvm_f32_rbf_iso(g, nsb, a.nrb, st);
             else
                 e = a.ard ? launch_mvm_f32_m52_ard(g, nsb, a.nrb, st) : launch_mvm_f32_m52_iso(g, nsb, a.nrb, st);

@@ -1,0 +1,291 @@
+// FP32 kernel product with entries evaluated on the fly (CIQ_F32), more than
+// 16 columns, on the BF16 matrix cores.
+//
+// v_mfma_f32_16x16x4_f32 and vector instructions share the SIMD: at N =
+// 50,000, d = 6, S = 64 the FP32 form (mvm_mfma.h) spends 2.2 ms on the
+// contraction and then 2.3 ms on the entries. BF16 matrix instructions run
+// beside the other waves' vector work, so here every entry and every element
+// of V is split in registers into three BF16 parts of 8 bits whose sum it is,
+// and
+//     K V ~ Kh Vh + (Kh Vm + Km Vh) + (Km Vm + Kh Vl + Kl Vh)
+// drops terms of 2^-25 of Kh Vh and less (rounding to nearest leaves 2^-9 and
+// 2^-18 in the lower parts). Six v_mfma_f32_16x16x32_bf16 take 0.8 ms of matrix
+// time there; the entries' evaluation and split (about 27 vector instructions,
+// two of them of a quarter of the rate) are the bound. Measured, same size:
+// 4.55 -> 3.00 ms; 32 columns 3.20 -> 2.21, 128 columns 9.33 -> 5.8; N = 20,000,
+// 64 columns 0.82 -> 0.57. At 16 columns the split costs what it saves.
+//
+// FP32 sums: per chunk of 64 columns the cross terms first, then the two
+// Kh Vh, then to FP64. The matrix cores cut a sum of eight products off
+// downwards (towards minus infinity), which adds up over the chunks (0.7 of
+// the whole error at N = 50,000), so V changes its sign from chunk to chunk.
+// The diagonal entry, which outweighs the rest of its chunk where lengthscales
+// are short, stays out of the matrix product: 2^-60 takes its place (an
+// infinite V[i] must still reach row i) and the epilogue adds V[i] itself.
+// The lengthscale and log2(e) are one factor, rounded once, of the exponent.
+// Error against 64 bits at d = 2 to 16, lengthscales 0.02 to 2, N = 300 to
+// 50,000: 3e-8 to 2.2e-7, in every one of 33 cases below the FP32 form's.
+//
+// Block: eight waves of one 16-row tile each; per chunk of 64 columns the block
+// splits V and stages it in the operand's order (16-byte units, the eight rows
+// of a lane group of one column) and the points, double-buffered up to 64
+// columns: one barrier a chunk. One tile a wave leaves 128 registers, two
+// blocks a CU (3.0 ms; two tiles a wave, one block of eight or two of four
+// waves: 3.2; sixteen waves 2.9 at this size, but blocks of 256 rows). The
+// 128-column form takes 250 registers and one block a CU, and still beats two
+// launches of 64 (5.8 against 6.0 ms: entries are evaluated once).
+#include <algorithm>
+
+#include "mvm_mfma.h"
+
+namespace ciq {
+namespace {
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
+
+constexpr float kBf16Max = 0x1.fep127f;
+
+__device__ __forceinline__ unsigned int pk_bf16(float a, float b) {
+    return __builtin_bit_cast(unsigned int, __builtin_convertvector((floatx2{a, b}), bf16x2));
+}
+__device__ __forceinline__ float bf_lo(unsigned int p) { return __builtin_bit_cast(float, p << 16); }
+__device__ __forceinline__ float bf_hi(unsigned int p) { return __builtin_bit_cast(float, p & 0xffff0000u); }
+
+// eight values as three BF16 parts whose sum is the value (8 bits each, the
+// remainders of a rounding to nearest are exact). CLAMP: values that round to
+// infinity, and infinities, leave a finite first part; an infinity ends up in
+// the last part alone, so that it meets only the first part of an entry, as
+// the FP32 product would have multiplied it.
+template <bool CLAMP>
+__device__ __forceinline__ void split3(const float* e, bf16x8& h, bf16x8& m, bf16x8& l) {
+    uintx4 hb, mb, lb;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        float x0 = e[2 * p], x1 = e[2 * p + 1];
+        auto cl = [](float x) { return CLAMP ? fminf(fmaxf(x, -kBf16Max), kBf16Max) : x; };
+        const unsigned int hp = pk_bf16(cl(x0), cl(x1));
+        x0 -= bf_lo(hp);
+        x1 -= bf_hi(hp);
+        const unsigned int mp = pk_bf16(cl(x0), cl(x1));
+        x0 -= bf_lo(mp);
+        x1 -= bf_hi(mp);
+        hb[p] = hp;
+        mb[p] = mp;
+        lb[p] = pk_bf16(x0, x1);
+    }
+    h = __builtin_bit_cast(bf16x8, hb);
+    m = __builtin_bit_cast(bf16x8, mb);
+    l = __builtin_bit_cast(bf16x8, lb);
+}
+
+// a value that is the same in every lane, kept in a scalar register
+__device__ __forceinline__ float uniform(float x) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x)));
+}
+
+template <int KERNEL, int DP, int NSB, bool ARD>
+__global__ __launch_bounds__(512, NSB > 4 ? 2 : 4) void mvm_fx_kernel(MvmArgs a) {
+    constexpr int NT = 512;
+    constexpr int S16 = NSB * 16;
+    constexpr int VB = NSB * 64;                   // 16-byte units of one part of one k-step of 32 columns
+    constexpr int VU = S16 * 8;                    // units of one part of a chunk of 64 columns
+    constexpr int UPT = (VU + NT - 1) / NT;
+    constexpr int NBUF = NSB <= 4 ? 2 : 1;
+    constexpr int DPP = DP == 6 ? 8 : DP == 10 ? 12 : DP;
+    constexpr int XE = 64 * DP;
+    constexpr int XPT = (XE + NT - 1) / NT;
+    __shared__ bf16x8 vs[NBUF][3 * VU];
+    __shared__ __attribute__((aligned(16))) float xs[NBUF][64 * DPP];
+
+    if (mfma::done_now(a.done)) return;
+    const int n = a.n;
+    float sc[DP];
+#pragma unroll
+    for (int k = 0; k < DP; ++k) sc[k] = uniform((float)a.scale[k]);
+    // the lengthscale (isotropic) and log2(e) are one factor of the exponent
+    const double sc0 = ARD ? 1.0 : a.scale[0];
+    const float ec = uniform((float)(KERNEL == CIQ_KERNEL_RBF ? -0.5 * 1.4426950408889634074 * sc0 * sc0
+                                                              : -1.4426950408889634074 * sc0));
+    const int split = blockIdx.y;
+    const double* __restrict__ xh = static_cast<const double*>(a.xh);
+    const float* __restrict__ v = static_cast<const float*>(a.v);
+    double* __restrict__ y = static_cast<double*>(a.y) + (long long)split * a.ysplit;
+    const int s = a.s, ldv = a.ldv, ldy = a.ldy;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int row0 = (blockIdx.x * 8 + wave) * 16;
+    float xi[DP];
+    {
+        const int i = row0 + (lane & 15);
+#pragma unroll
+        for (int k = 0; k < DP; ++k) xi[k] = (i < n) ? (float)xh[(long long)i * DP + k] : 0.0f;
+    }
+
+    floatx4 acc[NSB];
+    double accd[NSB][4];
+#pragma unroll
+    for (int sb = 0; sb < NSB; ++sb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) accd[sb][r] = 0.0;
+
+    const int nchunk = (n + 63) / 64;
+    const int c0 = (int)(((long long)split * nchunk) / a.nsplit);
+    const int c1 = (int)(((long long)(split + 1) * nchunk) / a.nsplit);
+
+    float xreg[XPT], vreg[UPT][8];
+    auto fetch = [&](int c) {
+        const int j0 = c * 64;
+#pragma unroll
+        for (int k = 0; k < XPT; ++k) {
+            const int e = tid + NT * k;
+            const int j = j0 + e / DP;
+            xreg[k] = (e < XE && j < n) ? (float)xh[(long long)j0 * DP + e] : 0.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < UPT; ++u) {
+            const int e = tid + NT * u;
+            const int cc = e % S16, j = j0 + 8 * (e / S16);
+            const bool ok = e < VU && cc < s;
+            const float* vp = v + (long long)j * ldv + cc;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) vreg[u][q] = (ok && j + q < n) ? vp[(long long)q * ldv] : 0.0f;
+        }
+    };
+    if (c0 < c1) fetch(c0);
+
+    for (int c = c0; c < c1; ++c) {
+        const int buf = NBUF == 2 ? (c & 1) : 0;
+        const float sign = (c & 1) ? -1.0f : 1.0f;
+        if (NBUF == 1) __syncthreads();
+#pragma unroll
+        for (int k = 0; k < XPT; ++k) {
+            const int e = tid + NT * k;
+            if (e < XE) xs[buf][(e / DP) * DPP + e % DP] = xreg[k];
+        }
+#pragma unroll
+        for (int u = 0; u < UPT; ++u) {
+            const int e = tid + NT * u;
+            if (VU % NT != 0 && e >= VU) break;
+            const int cc = e % S16, g = e / S16;      // column, group of eight rows of V
+            bf16x8 h, m, l;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) vreg[u][q] *= sign;
+            split3<true>(vreg[u], h, m, l);
+            const int at = (g >> 2) * VB + (cc >> 4) * 64 + (g & 3) * 16 + (cc & 15);
+            vs[buf][at] = h;
+            vs[buf][VU + at] = m;
+            vs[buf][2 * VU + at] = l;
+        }
+        __syncthreads();
+        if (c + 1 < c1) fetch(c + 1);
+        bf16x8 kh[2];
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+            const float* xj0 = &xs[buf][(kk * 32 + 8 * (lane >> 4)) * DPP];
+            float kv[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                float r2 = 0.0f;
+#pragma unroll
+                for (int k = 0; k < DP; ++k) {
+                    const float dd = xi[k] - xj0[u * DPP + k];
+                    if constexpr (ARD) {
+                        const float w = dd * sc[k];
+                        r2 = fmaf(w, w, r2);
+                    } else {
+                        r2 = fmaf(dd, dd, r2);
+                    }
+                }
+                if constexpr (KERNEL == CIQ_KERNEL_RBF) {
+                    kv[u] = __builtin_amdgcn_exp2f(r2 * ec);
+                } else {
+                    // t = -rho log2(e); 1 + rho + rho^2 / 3 in t
+                    constexpr double ln2 = 0.69314718055994530942;
+                    const float t = __builtin_amdgcn_sqrtf(r2) * ec;
+                    kv[u] = fmaf(t, fmaf(t, (float)(ln2 * ln2 / 3.0), (float)-ln2), 1.0f) *
+                            __builtin_amdgcn_exp2f(t);
+                }
+            }
+            const int j0 = c * 64 + kk * 32;
+            if (j0 <= row0 + 15 && row0 <= j0 + 31) {     // the diagonal (see above)
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    if (j0 + 8 * (lane >> 4) + u == row0 + (lane & 15)) kv[u] = (kv[u] - 1.0f) + 0x1p-60f;
+            }
+            bf16x8 km, kl;
+            split3<false>(kv, kh[kk], km, kl);
+            const bf16x8* bp = &vs[buf][kk * VB + lane];
+#pragma unroll
+            for (int sb = 0; sb < NSB; ++sb) {
+                const bf16x8 bh = bp[sb * 64], bm = bp[VU + sb * 64], bl = bp[2 * VU + sb * 64];
+                floatx4 t = kk == 0 ? floatx4{0.f, 0.f, 0.f, 0.f} : acc[sb];
+                t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kl, bh, t, 0, 0, 0);
+                t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kh[kk], bl, t, 0, 0, 0);
+                t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(km, bm, t, 0, 0, 0);
+                t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(km, bh, t, 0, 0, 0);
+                t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kh[kk], bm, t, 0, 0, 0);
+                if (kk == 1) {
+                    t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kh[0], vs[buf][lane + sb * 64], t, 0, 0, 0);
+                    t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kh[1], bh, t, 0, 0, 0);
+                }
+                acc[sb] = t;
+            }
+        }
+#pragma unroll
+        for (int sb = 0; sb < NSB; ++sb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) accd[sb][r] = fma((double)acc[sb][r], (double)sign, accd[sb][r]);
+    }
+
+    const double o2 = a.o2, s2 = a.s2;
+#pragma unroll
+    for (int sb = 0; sb < NSB; ++sb) {
+        const int cc = sb * 16 + (lane & 15);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = row0 + 4 * (lane >> 4) + r;
+            if (i < n && cc < s) {
+                double val = o2 * accd[sb][r];
+                if (split == 0) val = fma(o2 + s2, (double)v[(long long)i * ldv + cc], val);
+                y[(long long)i * ldy + cc] = val;
+            }
+        }
+    }
+}
+
+template <int KERNEL, bool ARD, int DP>
+hipError_t launch_fx_dp(const MvmArgs& a, int nsb, hipStream_t st) {
+    const dim3 grid((a.n + kFxRows - 1) / kFxRows, a.nsplit);
+    if (nsb <= 2) hipLaunchKernelGGL((mvm_fx_kernel<KERNEL, DP, 2, ARD>), grid, dim3(512), 0, st, a);
+    else if (nsb <= 4) hipLaunchKernelGGL((mvm_fx_kernel<KERNEL, DP, 4, ARD>), grid, dim3(512), 0, st, a);
+    else hipLaunchKernelGGL((mvm_fx_kernel<KERNEL, DP, 8, ARD>), grid, dim3(512), 0, st, a);
+    return hipGetLastError();
+}
+
+template <int KERNEL, bool ARD>
+hipError_t launch_fx_k(const MvmArgs& a, int nsb, hipStream_t st) {
+    switch (a.dp) {
+        case 4: return launch_fx_dp<KERNEL, ARD, 4>(a, nsb, st);
+        case 6: return launch_fx_dp<KERNEL, ARD, 6>(a, nsb, st);
+        case 8: return launch_fx_dp<KERNEL, ARD, 8>(a, nsb, st);
+        case 10: return launch_fx_dp<KERNEL, ARD, 10>(a, nsb, st);
+        case 12: return launch_fx_dp<KERNEL, ARD, 12>(a, nsb, st);
+        default: return launch_fx_dp<KERNEL, ARD, 16>(a, nsb, st);
+    }
+}
+}  // namespace
+
+hipError_t launch_mvm_fx(const MvmArgs& a, int nsb, hipStream_t st) {
+    static_assert(kFxRows == 128, "eight waves of 16 rows");
+    if (a.wl != nullptr || nsb < 2 || nsb > 8) return hipErrorInvalidValue;
+    if (a.kernel == CIQ_KERNEL_RBF)
+        return a.ard ? launch_fx_k<CIQ_KERNEL_RBF, true>(a, nsb, st) : launch_fx_k<CIQ_KERNEL_RBF, false>(a, nsb, st);
+    return a.ard ? launch_fx_k<CIQ_KERNEL_MATERN52, true>(a, nsb, st)
+                 : launch_fx_k<CIQ_KERNEL_MATERN52, false>(a, nsb, st);
+}
+}  // namespace ciq
