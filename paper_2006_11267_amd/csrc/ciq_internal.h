@@ -244,6 +244,7 @@ int mvm_pick_nsplit(int dtype, int nrb, int n_max, int s);
 struct SplitModel {
     double t_blk, lat;       // us per 64-column chunk of a block (see model_nsplit)
     int per_cu;              // blocks a CU holds
+    double tail;             // > 0: the last round counts by its blocks, at tail t_blk each
 };
 int model_nsplit(double blocks, int chunks, const SplitModel& m, double part_us, int max_split, double* us = nullptr);
 SplitModel mvm_split_model(int dtype, bool cached, int n, int nsb, int rt, bool fx);

@@ -1970,7 +1970,10 @@ KmvmPlan kmvm_plan(const ciq_problem* p, int dtype, int s) {
     pl.bound = pl.xbytes + ((dtype == CIQ_F64 && ns2 == 1 && s <= 64) ? 0 : ns2 * one);
     const size_t room = std::max(pl.bound, (size_t)CIQ_NOALLOC_SCRATCH_BYTES) - pl.xbytes;
     const int cap = product_cap(dtype, false);
-    const int nsb = (std::min(s, cap) + 15) / 16, groups = (s + cap - 1) / cap;
+    const int nsb = (std::min(s, cap) + 15) / 16;
+    // column groups of the largest launch (launch_mvm): FP64 takes its groups
+    // of 64 in one, without a last one of at most 32 columns
+    const int groups = dtype == CIQ_F64 ? std::max(1, s / cap + (s % cap > 32 ? 1 : 0)) : 1;
     const int chunks = (p->n + 63) / 64;
     double best = 1e300;
     pl.fx = dtype == CIQ_F32 && s > 16;
@@ -1981,7 +1984,7 @@ KmvmPlan kmvm_plan(const ciq_problem* p, int dtype, int s) {
         const int max_split = (int)std::min<size_t>(16, std::max<size_t>(1, room / one));
         double us = 0.0;
         const int ns = model_nsplit((double)nrb * groups, chunks, mvm_split_model(dtype, false, p->n, nsb, rpb / 64, pl.fx),
-                                    one * 2.0 / 4.5e6, max_split, &us);
+                                    one * 1.2 / 4.5e6, max_split, &us);
         if (us < best) {
             best = us;
             pl.rt = rt;

@@ -28,8 +28,10 @@ int mvm_rows_per_block(int dtype, int s, int rt) {
 // Column ranges of a product from a model of its time. A block of a launch
 // takes t_blk per 64-column chunk when the CU works on per_cu of them at its
 // full rate, and at least lat when it is alone (the latency of its loads and
-// of its chain of instructions); equal blocks go round by round over 256 CUs;
-// every range costs its partials (part_us: written once, read once). All in
+// of its chain of instructions); equal blocks go round by round over 256 CUs
+// (tail: a last round of fewer blocks a CU runs at their own rate, tail times
+// t_blk each, as measured for the products that evaluate entries: blocks that
+// start together wait for the same units together); every range costs its partials (part_us: written once, read once). All in
 // microseconds; *us (nullable): the modelled time.
 int model_nsplit(double blocks, int chunks, const SplitModel& m, double part_us, int max_split, double* us) {
     double best = 1e300;
@@ -39,7 +41,12 @@ int model_nsplit(double blocks, int chunks, const SplitModel& m, double part_us,
         const int per = (int)std::min((double)m.per_cu, std::ceil(load));
         const double r = load / m.per_cu;
         const double rounds = r > 4.0 ? r + 0.5 : std::ceil(r);
-        const double t = rounds * std::ceil((double)chunks / ns) * std::max(m.lat, per * m.t_blk) + ns * part_us;
+        double step = rounds * std::max(m.lat, per * m.t_blk);   // us per chunk of every range
+        if (m.tail > 0.0) {
+            const double full = std::floor(r), rest = std::ceil(load - full * m.per_cu - 1e-9);
+            step = full * std::max(m.lat, m.per_cu * m.t_blk) + (rest > 0.0 ? std::max(m.lat, rest * m.t_blk * m.tail) : 0.0);
+        }
+        const double t = step * std::ceil((double)chunks / ns) + ns * part_us;
         if (t < best) {
             best = t;
             pick = ns;
@@ -50,9 +57,9 @@ int model_nsplit(double blocks, int chunks, const SplitModel& m, double part_us,
 }
 
 // Model constants of the kernel products, fitted to the times measured at N =
-// 50,000 (all slots busy: matrix instructions per 16-column block of V, entry
-// evaluation or the stream of K per 64 rows) and at N = 1,024 (one block per
-// CU). A resident matrix of at most 200 MB is served by the last-level cache,
+// 15,000 to 50,000 (all slots busy: matrix instructions per 16-column block of
+// V, entry evaluation or the stream of K per 64 rows) and at N = 1,024 to 8,000
+// (one block per CU), d = 6. A resident matrix of at most 200 MB is served by the last-level cache,
 // about twice as fast as HBM.
 SplitModel mvm_split_model(int dtype, bool cached, int n, int nsb, int rt, bool fx) {
     SplitModel m{};
@@ -60,6 +67,7 @@ SplitModel mvm_split_model(int dtype, bool cached, int n, int nsb, int rt, bool 
         m.per_cu = nsb <= 4 ? 2 : 1;
         m.t_blk = nsb <= 2 ? 1.9 : nsb <= 4 ? 2.5 : 4.9;
         m.lat = nsb <= 2 ? 2.3 : nsb <= 4 ? 3.3 : 4.4;
+        m.tail = 1.06;
         return m;
     }
     m.per_cu = nsb <= 2 ? 4 : 2;
@@ -71,11 +79,13 @@ SplitModel mvm_split_model(int dtype, bool cached, int n, int nsb, int rt, bool 
         m.t_blk = std::max(k, mfma) + 0.1 * rows;
         m.lat = 1.2;
     } else if (dtype == CIQ_F64) {
-        m.t_blk = rows * (1.3 + 0.47 * nsb);
-        m.lat = 1.6 + 0.7 * rows;
+        m.t_blk = rt == 1 ? 1.45 + 0.57 * nsb : 2.85 + 1.05 * nsb;
+        m.lat = rt == 1 ? 2.1 + 0.62 * nsb : 3.4 + 1.05 * nsb;
+        m.tail = rt == 1 ? 1.15 : 1.04;
     } else if (dtype == CIQ_F32) {
-        m.t_blk = rows * (0.85 + 0.27 * nsb);
-        m.lat = 1.0 + 0.5 * rows;
+        m.t_blk = rows * (0.58 + 0.27 * nsb);
+        m.lat = 1.1 + rows * (0.57 + 0.27 * nsb);
+        m.tail = 1.15;
     } else {
         m.t_blk = 1.6;
         m.lat = 2.0;
