@@ -12,8 +12,8 @@
 // 2^-18 in the lower parts). Six v_mfma_f32_16x16x32_bf16 take 0.8 ms of matrix
 // time there; the entries' evaluation and split (about 27 vector instructions,
 // two of them of a quarter of the rate) are the bound. Measured, same size:
-// 4.55 -> 3.00 ms; 32 columns 3.20 -> 2.21, 128 columns 9.33 -> 5.8; N = 20,000,
-// 64 columns 0.82 -> 0.57. At 16 columns the split costs what it saves.
+// 4.55 -> 2.9 ms; 32 columns 3.20 -> 2.20, 128 columns 9.33 -> 5.5; N = 20,000,
+// 64 columns 0.82 -> 0.58. At 16 columns the split costs what it saves.
 //
 // FP32 sums: per chunk of 64 columns the cross terms first, then the two
 // Kh Vh, then to FP64. The matrix cores cut a sum of eight products off
@@ -28,12 +28,13 @@
 //
 // Block: eight waves of one 16-row tile each; per chunk of 64 columns the block
 // splits V and stages it in the operand's order (16-byte units, the eight rows
-// of a lane group of one column) and the points, double-buffered up to 64
-// columns: one barrier a chunk. One tile a wave leaves 128 registers, two
+// of a lane group of one column) and the points (16 bytes of padding after every
+// eight: a wave reads four groups at once), double-buffered up to 64 columns:
+// one barrier a chunk. One tile a wave leaves 128 registers, two
 // blocks a CU (3.0 ms; two tiles a wave, one block of eight or two of four
 // waves: 3.2; sixteen waves 2.9 at this size, but blocks of 256 rows). The
 // 128-column form takes 250 registers and one block a CU, and still beats two
-// launches of 64 (5.8 against 6.0 ms: entries are evaluated once).
+// launches of 64 (5.5 against 5.8 ms: entries are evaluated once).
 #include <algorithm>
 
 #include "mvm_mfma.h"
@@ -66,7 +67,7 @@ __device__ __forceinline__ void split3(const float* e, bf16x8& h, bf16x8& m, bf1
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
         float x0 = e[2 * p], x1 = e[2 * p + 1];
-        auto cl = [](float x) { return CLAMP ? fminf(fmaxf(x, -kBf16Max), kBf16Max) : x; };
+        auto cl = [](float x) { return CLAMP ? __builtin_amdgcn_fmed3f(x, -kBf16Max, kBf16Max) : x; };
         const unsigned int hp = pk_bf16(cl(x0), cl(x1));
         x0 -= bf_lo(hp);
         x1 -= bf_hi(hp);
@@ -99,7 +100,7 @@ __global__ __launch_bounds__(512, NSB > 4 ? 2 : 4) void mvm_fx_kernel(MvmArgs a)
     constexpr int XE = 64 * DP;
     constexpr int XPT = (XE + NT - 1) / NT;
     __shared__ bf16x8 vs[NBUF][3 * VU];
-    __shared__ __attribute__((aligned(16))) float xs[NBUF][64 * DPP];
+    __shared__ __attribute__((aligned(16))) float xs[NBUF][64 * DPP + 32];
 
     if (mfma::done_now(a.done)) return;
     const int n = a.n;
@@ -152,6 +153,11 @@ __global__ __launch_bounds__(512, NSB > 4 ? 2 : 4) void mvm_fx_kernel(MvmArgs a)
             const int cc = e % S16, j = j0 + 8 * (e / S16);
             const bool ok = e < VU && cc < s;
             const float* vp = v + (long long)j * ldv + cc;
+            if (j0 + 64 <= n && S16 <= s) {
+#pragma unroll
+                for (int q = 0; q < 8; ++q) vreg[u][q] = (VU % NT == 0 || e < VU) ? vp[(long long)q * ldv] : 0.0f;
+                continue;
+            }
 #pragma unroll
             for (int q = 0; q < 8; ++q) vreg[u][q] = (ok && j + q < n) ? vp[(long long)q * ldv] : 0.0f;
         }
@@ -165,7 +171,7 @@ __global__ __launch_bounds__(512, NSB > 4 ? 2 : 4) void mvm_fx_kernel(MvmArgs a)
 #pragma unroll
         for (int k = 0; k < XPT; ++k) {
             const int e = tid + NT * k;
-            if (e < XE) xs[buf][(e / DP) * DPP + e % DP] = xreg[k];
+            if (e < XE) xs[buf][(e / DP) * DPP + (e / DP / 8) * 4 + e % DP] = xreg[k];
         }
 #pragma unroll
         for (int u = 0; u < UPT; ++u) {
@@ -186,7 +192,7 @@ __global__ __launch_bounds__(512, NSB > 4 ? 2 : 4) void mvm_fx_kernel(MvmArgs a)
         bf16x8 kh[2];
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) {
-            const float* xj0 = &xs[buf][(kk * 32 + 8 * (lane >> 4)) * DPP];
+            const float* xj0 = &xs[buf][(4 * kk + (lane >> 4)) * (8 * DPP + 4)];
             float kv[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
