@@ -353,7 +353,7 @@ struct PcholArgs {
     int* piv;                // [rank + 1] pivot of step m (-1: stopped)
     double* pval;            // [rank + 1] residual diagonal of that pivot
     double* trace;           // [rank + 1] residual trace before step m
-    double* bval;            // [nblk] block candidates
+    double* bval;            // [2][nblk] block candidates
     int* bidx;
     double* bsum;
     int nblk;

@@ -413,12 +413,12 @@ void pchol_layout(int n, int R, F&& take_d, PcholScratch& w) {
     w.dres = take_d((size_t)n);
     w.pval = take_d((size_t)R + 1);
     w.trace = take_d((size_t)R + 1);
-    w.bval = take_d((size_t)nblk);
-    w.bsum = take_d((size_t)nblk);
+    w.bval = take_d((size_t)2 * nblk);   // two sets, used in turn
+    w.bsum = take_d((size_t)2 * nblk);
     // integer arrays as doubles' worth of space (8 bytes per entry)
     w.chosen = reinterpret_cast<int*>(take_d((size_t)n));
     w.piv = reinterpret_cast<int*>(take_d((size_t)R + 1));
-    w.bidx = reinterpret_cast<int*>(take_d((size_t)nblk));
+    w.bidx = reinterpret_cast<int*>(take_d((size_t)nblk));   // 2 nblk of them
 }
 
 // Rank-R factor into L (n x ldl, zero-filled here); pivots and the final
@@ -447,10 +447,7 @@ int pchol_run(const double* xh, int n, int dp, int kernel, int ard, const double
     a.nblk = pchol_blocks(n);
     HIPCHK(launch_fill<double>(L, (size_t)n * ldl, 0.0, st));
     HIPCHK(launch_pchol_init(a, st));
-    for (int m = 0; m < R; ++m) {
-        HIPCHK(launch_pchol_pick(a, m, st));
-        HIPCHK(launch_pchol_col(a, m, st));
-    }
+    for (int m = 0; m < R; ++m) HIPCHK(launch_pchol_col(a, m, st));
     HIPCHK(launch_pchol_pick(a, R, st));
     piv.assign((size_t)R, -1);
     HIPCHK(hipMemcpyAsync(piv.data(), w.piv, (size_t)R * sizeof(int), hipMemcpyDeviceToHost, st));

@@ -31,30 +31,39 @@ __device__ __forceinline__ bool better(double v, int i, double bv, int bi) {
     return v > bv || (v == bv && i < bi);
 }
 
+struct PickLds {
+    double v[256], sum[256];
+    int i[256];
+};
+
 // Block reduction of (value, index) by `better` and of a sum in a fixed tree
-// order; thread 0 writes the block's partial.
-__device__ void block_pick(double v, int i, double sum, double* bval, int* bidx, double* bsum) {
-    __shared__ double sv[256], ss[256];
-    __shared__ int si[256];
+// order, into element 0 of every array.
+__device__ void block_best(double v, int i, double sum, PickLds& l) {
     const int t = threadIdx.x;
-    sv[t] = v;
-    si[t] = i;
-    ss[t] = sum;
+    l.v[t] = v;
+    l.i[t] = i;
+    l.sum[t] = sum;
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
         if (t < w) {
-            if (better(sv[t + w], si[t + w], sv[t], si[t])) {
-                sv[t] = sv[t + w];
-                si[t] = si[t + w];
+            if (better(l.v[t + w], l.i[t + w], l.v[t], l.i[t])) {
+                l.v[t] = l.v[t + w];
+                l.i[t] = l.i[t + w];
             }
-            ss[t] += ss[t + w];
+            l.sum[t] += l.sum[t + w];
         }
         __syncthreads();
     }
-    if (t == 0) {
-        bval[blockIdx.x] = sv[0];
-        bidx[blockIdx.x] = si[0];
-        bsum[blockIdx.x] = ss[0];
+}
+
+// The block's candidate and partial sum, for step m's pivot.
+__device__ void block_pick(double v, int i, double sum, const PcholArgs& a, int m, PickLds& l) {
+    block_best(v, i, sum, l);
+    if (threadIdx.x == 0) {
+        const int at = (m & 1) * a.nblk + blockIdx.x;
+        a.bval[at] = l.v[0];
+        a.bidx[at] = l.i[0];
+        a.bsum[at] = l.sum[0];
     }
 }
 
@@ -70,44 +79,44 @@ __global__ __launch_bounds__(256) void pchol_init_kernel(PcholArgs a) {
             bi = i;
         }
     }
-    block_pick(bv, bi, sum, a.bval, a.bidx, a.bsum);
+    __shared__ PickLds lds;
+    block_pick(bv, bi, sum, a, 0, lds);
 }
 
-// Step m's pivot from the block candidates (one block).
-__global__ __launch_bounds__(256) void pchol_pick_kernel(PcholArgs a, int m) {
+// Step m's pivot from the block candidates of the step before, by every block
+// for itself (a launch of its own was a third of the step); block 0 records
+// it. Steps write their candidates into two sets in turn: a block may still
+// read one while another of its launch writes the next.
+__device__ int pick(const PcholArgs& a, int m, double* pval, PickLds& l) {
+    const int set = (m & 1) * a.nblk;
     double bv = -DBL_MAX, sum = 0.0;
     int bi = INT_MAX;
     for (int b = threadIdx.x; b < a.nblk; b += 256) {
-        sum += a.bsum[b];
-        if (better(a.bval[b], a.bidx[b], bv, bi)) {
-            bv = a.bval[b];
-            bi = a.bidx[b];
+        sum += a.bsum[set + b];
+        if (better(a.bval[set + b], a.bidx[set + b], bv, bi)) {
+            bv = a.bval[set + b];
+            bi = a.bidx[set + b];
         }
     }
-    __shared__ double sv[256], ss[256];
-    __shared__ int si[256];
-    const int t = threadIdx.x;
-    sv[t] = bv;
-    si[t] = bi;
-    ss[t] = sum;
+    block_best(bv, bi, sum, l);
+    const bool stopped = (m > 0 && a.piv[m - 1] < 0);
+    const bool take = !stopped && l.i[0] != INT_MAX && l.v[0] > a.stop_abs;
+    const int p = take ? l.i[0] : -1;
+    *pval = take ? l.v[0] : 0.0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        a.piv[m] = p;
+        a.pval[m] = *pval;
+        a.trace[m] = l.sum[0];
+    }
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (t < w) {
-            if (better(sv[t + w], si[t + w], sv[t], si[t])) {
-                sv[t] = sv[t + w];
-                si[t] = si[t + w];
-            }
-            ss[t] += ss[t + w];
-        }
-        __syncthreads();
-    }
-    if (t == 0) {
-        const bool stopped = (m > 0 && a.piv[m - 1] < 0);
-        const bool take = !stopped && si[0] != INT_MAX && sv[0] > a.stop_abs;
-        a.piv[m] = take ? si[0] : -1;
-        a.pval[m] = take ? sv[0] : 0.0;
-        a.trace[m] = ss[0];
-    }
+    return p;
+}
+
+// After the last column: the pivot that would follow and the residual trace.
+__global__ __launch_bounds__(256) void pchol_pick_kernel(PcholArgs a, int m) {
+    __shared__ PickLds lds;
+    double pval;
+    pick(a, m, &pval, lds);
 }
 
 // Column m: L[i][m] = (Ktil[i][p] - sum_{k<m} L[i][k] L[p][k]) / sqrt(d_p) for
@@ -117,13 +126,23 @@ template <int KERNEL, bool ARD>
 __global__ __launch_bounds__(256) void pchol_col_kernel(PcholArgs a, int m) {
     extern __shared__ double lrow[];          // L[p][0..m)
     __shared__ double xp[CIQ_MAX_D];
-    const int p = a.piv[m];
-    if (p < 0) return;                        // stopped: column m stays zero
+    __shared__ PickLds lds;
+    double pval;
+    const int p = pick(a, m, &pval, lds);
+    if (p < 0) {                              // stopped: column m stays zero, the residuals as they are
+        if (threadIdx.x == 0) {
+            const int from = (m & 1) * a.nblk + blockIdx.x, to = ((m + 1) & 1) * a.nblk + blockIdx.x;
+            a.bval[to] = a.bval[from];
+            a.bidx[to] = a.bidx[from];
+            a.bsum[to] = a.bsum[from];
+        }
+        return;
+    }
     const int dp = a.dp;
     for (int k = threadIdx.x; k < m; k += 256) lrow[k] = a.L[(long long)p * a.ldl + k];
     if (threadIdx.x < dp) xp[threadIdx.x] = a.xh[(long long)p * dp + threadIdx.x];
     __syncthreads();
-    const double lpp = sqrt(a.pval[m]);
+    const double lpp = sqrt(pval);
     const double sc0sq = a.scale[0] * a.scale[0];
     double bv = -DBL_MAX, sum = 0.0;
     int bi = INT_MAX;
@@ -160,7 +179,7 @@ __global__ __launch_bounds__(256) void pchol_col_kernel(PcholArgs a, int m) {
             bi = i;
         }
     }
-    block_pick(bv, bi, sum, a.bval, a.bidx, a.bsum);
+    block_pick(bv, bi, sum, a, m + 1, lds);
 }
 
 // ---- low-rank products -------------------------------------------------------
