@@ -20,9 +20,10 @@ its columns/s, accuracy and HBM roofline are reported beside the FP32 line
 ("precision_form").
 
 Default path: the kernel matrix is evaluated once per call in FP64, rounded
-to FP32 and kept resident in HBM (10 GB); every product streams it through
-FP32 MFMA with FP64 sums across 64-column chunks; Lanczos and search-direction
-vectors and all scalars are FP64 (dtype "f32" names the product arithmetic).
+to FP32 and kept resident in HBM (10 GB); every product streams it, splits each
+FP32 entry exactly into three FP16 parts and contracts them on the FP16 MFMA
+with FP64 sums across 64-column chunks; Lanczos and search-direction vectors and
+all scalars are FP64 (dtype "f32" names the product arithmetic).
 
 Prints ONE JSON line (metric, value, roofline, cpu_baseline, ...).
 """
@@ -45,8 +46,8 @@ GOLDEN = os.path.join(ROOT, "tests", "golden")
 # (N = 50,000, S = 64): FETCH_SIZE and WRITE_SIZE from two rocprofv3 counter
 # runs of `bench.py --counters [--precision f64|f16x3]`, each scaled by the
 # same counter's reading for a plain 512 MiB device copy
-# (profiles/mvm_kt*_kernel_matern52_n50000_s64_hbm_traffic.md).
-KT_TRAFFIC_BYTES = {"f64": 2.1359e10, "f32": 1.0345e10, "f16x3": 1.0352e10}
+# (profiles/mvm_k*_kernel_matern52_n50000_s64_hbm_traffic.md).
+KT_TRAFFIC_BYTES = {"f64": 2.1359e10, "f32": 1.0500e10, "f16x3": 1.0352e10}
 METRIC = "K^{±1/2}B columns/s at rel err ≤1e-4 (N=50k); kernel-MVM MFMA util %"
 HBM_PEAK_GBS = 8000.0
 
@@ -90,26 +91,28 @@ def cpu_baseline(p, iters: int, q: int, sample_rows: int = 12288) -> dict:
 
 
 def roofline(precision: str, cached: bool, n: int, s: int, avg_ms: float, launches: int) -> dict:
-    """Roofline of the kernel product from its live HIP-event timing. The FP32
-    and FP64 products are MFMA-bound: 2 N^2 S flops per launch against the
-    dense MFMA peak of their precision. The resident split FP16 product is
-    HBM-bound: its algorithmic bytes per launch are the matrix (4 bytes per
-    entry, N^2 entries), the split operand (4 N S) and the FP64 result (8 N S),
-    against 8 TB/s."""
-    if precision == "f16x3" and cached:
-        bytes_ = 4.0 * n * n + 12.0 * n * s
+    """Roofline of the kernel product from its live HIP-event timing. The FP64
+    products and the narrow FP32 ones are reported against the dense MFMA peak
+    of their precision: 2 N^2 S flops per launch. The resident split FP16
+    product and the resident FP32 one of more than 32 columns (exact FP16 parts)
+    are HBM-bound: their algorithmic bytes per launch are the matrix (4 bytes
+    per entry, N^2 entries), the split operand (4 or 6 N S) and the FP64 result
+    (8 N S), against 8 TB/s."""
+    if cached and (precision == "f16x3" or (precision == "f32" and s > 32)):
+        f32 = precision == "f32"
+        bytes_ = 4.0 * n * n + (14.0 if f32 else 12.0) * n * s
         achieved = bytes_ / (avg_ms * 1e-3) / 1e9
         return {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": achieved / HBM_PEAK_GBS,
-                "traffic": KT_TRAFFIC_BYTES.get("f16x3") if (n, s) == (50000, 64) else None,
-                "kernel": "mvm_kt16_kernel", "avg_ms": avg_ms, "launches": launches,
+                "traffic": KT_TRAFFIC_BYTES.get(precision) if (n, s) == (50000, 64) else None,
+                "kernel": "mvm_kx_kernel" if f32 else "mvm_kt16_kernel", "avg_ms": avg_ms, "launches": launches,
                 "algorithmic_bytes": bytes_,
-                "mfma_tflops": 3 * 2.0 * n * n * s / (avg_ms * 1e-3) / 1e12}
+                "mfma_tflops": (6 if f32 else 3) * 2.0 * n * n * s / (avg_ms * 1e-3) / 1e12}
     flops = 2.0 * n * n * s * (3 if precision in ("bf16x3", "f16x3") else 1)
     achieved = flops / (avg_ms * 1e-3) / 1e12
     peak = MFMA_PEAK_TFLOPS[precision]
     kernel = ({"f64": "mvm_kt_kernel", "f32": "mvm_kt32_kernel"}[precision] if cached else
-              {"f64": "mvm_f64mfma_kernel", "f32": "mvm_f32_kernel"}.get(precision, "mvm_x3_kernel"))
+              {"f64": "mvm_f64mfma_kernel", "f32": "mvm_fx_kernel" if s > 16 else "mvm_f32_kernel"}.get(precision, "mvm_x3_kernel"))
     return {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
             "traffic": KT_TRAFFIC_BYTES.get(precision) if cached and (n, s) == (50000, 64) else None,
             "kernel": kernel, "avg_ms": avg_ms, "launches": launches}

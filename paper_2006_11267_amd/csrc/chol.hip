@@ -42,7 +42,7 @@ __global__ void chol_prep_kernel(double* __restrict__ A, int n, int npad, double
 // in registers, columns 16 q.. of the block (lane = row) and rows 16 q.. of the
 // inverse (lane = column). Step j needs column j of L and row j of the inverse
 // from LDS (two buffers in turn, one barrier a step) and updates both: the same
-// 16 numbers L[16 q + t][j] serve both. 121 -> 30 us (the block in LDS, three
+// 16 numbers L[16 q + t][j] serve both. 121 -> 55 us (the block in LDS, three
 // barriers a step, then one thread per column of the inverse).
 __global__ __launch_bounds__(256) void chol_diag_kernel(double* __restrict__ A, int ld, int k0,
                                                         double* __restrict__ dinv, int* __restrict__ status) {
