@@ -414,6 +414,11 @@ struct SparseOp {
 // and every col[k] lies in [0, n) (the caller zeroes *bad).
 hipError_t launch_csr_check(const int* row_ptr, const int* col, int n, int nnz, int* bad, hipStream_t st);
 // y = A x for s columns (x: n x s, ld ldx; y: n x s, ld ldy); `done` as above.
+constexpr int kSpmvDotRows = 128;
+// One column of an iteration: y = A q and the phase-0 partials of launch_dots,
+// one per kSpmvDotRows rows (d.dots_blocks of them).
+hipError_t launch_spmv_dot(const SparseOp& a, const double* q, const double* qp, double* y, const Dev& d,
+                           hipStream_t st);
 hipError_t launch_spmv(const SparseOp& a, const double* x, int ldx, int s, double* y, int ldy, const int* done,
                        hipStream_t st);
 

@@ -775,6 +775,11 @@ struct Run {
     }
     size_t op_words() const { return op_halfs(kcache_cols(max_n), nsbt, max_parts()) / 2; }
 
+    // The sparse product of one column carries phase 0 of the inner products:
+    // above the sizes of the one-launch step, up to 256 partials (more cost
+    // the later sums what the launch costs).
+    bool spmv_dots() const { return sp && s == 1 && max_n > 8192 && max_n <= 256 * kSpmvDotRows; }
+
     void configure(int rt_) {
         rt = fx() ? 2 : rt_;   // (a last group of at most 16 columns: the FP32 form with 128 rows)
         const bool kx = parts() == 3;
@@ -792,6 +797,7 @@ struct Run {
             const int rows_per_pass = 256 / ts;
             const int passes = (max_n + rows_per_pass - 1) / rows_per_pass;
             d.dots_blocks = std::max(1, std::min(512, std::max(std::min(passes, 128), (passes + 7) / 8)));
+            if (spmv_dots()) d.dots_blocks = (max_n + kSpmvDotRows - 1) / kSpmvDotRows;
             d.fuse_sums = precond ? 0 : (d.dots_blocks * std::min(s, 64) <= 4096 ? 3 : 1);
         }
         const int rpb = rows_per_block();
@@ -981,7 +987,8 @@ struct Run {
                                              st));
             return CIQ_OK;
         }
-        HIPCHK(launch_dots<double>(d, ypart, ysplit, np, qcur, qprv, 0, st, y32));   // also reduces the splits
+        if (!spmv_dots())
+            HIPCHK(launch_dots<double>(d, ypart, ysplit, np, qcur, qprv, 0, st, y32));   // also reduces the splits
         HIPCHK(launch_colsum(d, 0, st));
         HIPCHK(launch_dots<double>(d, ypart, ysplit, 1, qcur, qprv, 1, st));
         HIPCHK(launch_colsum(d, 1, st));
@@ -1014,7 +1021,8 @@ struct Run {
     // The product of iteration j (kernel matrix, or the caller's sparse operator).
     int product(int j, hipStream_t st) {
         if (sp) {
-            HIPCHK(launch_spmv(*sp, qbuf[(j - 1) & 1], s, s, ypart, s, &d.st->done, st));
+            if (spmv_dots()) HIPCHK(launch_spmv_dot(*sp, qbuf[(j - 1) & 1], qbuf[j & 1], ypart, d, st));
+            else HIPCHK(launch_spmv(*sp, qbuf[(j - 1) & 1], s, s, ypart, s, &d.st->done, st));
             return CIQ_OK;
         }
         if (dn) {

@@ -64,7 +64,68 @@ __global__ __launch_bounds__(256) void spmv1_kernel(SparseOp a, const double* __
     if (row < a.n && g == 0) y[row] = acc;
 }
 
+// The same product for one msMINRES iteration, with the iteration's first
+// inner product: the block's rows of y = A q and its partial of q^T (y - beta
+// q_prev), one partial per 128 rows in dots_kernel's place (phase 0). At 25,600
+// rows and 79 entries a row the pass over y, q and q_prev was a launch of 7.2
+// us beside a product of 6.4; together 10.4. (64 rows a block: 8.2, but the
+// 400 partials cost the later sums 4 us more.) Bound by the gathers' latency.
+__global__ __launch_bounds__(1024) void spmv1_dot_kernel(SparseOp a, const double* __restrict__ q,
+                                                         const double* __restrict__ qp, double* __restrict__ y,
+                                                         Dev d) {
+    __shared__ double part[kSpmvDotRows];
+    if (d.st->done) return;
+    const int tid = threadIdx.x, g = tid & 15, rl = tid >> 4;
+    double acc[2] = {0.0, 0.0}, qi[2] = {0.0, 0.0}, pi[2] = {0.0, 0.0};
+    int k[2] = {0, 0}, k1[2] = {0, 0};
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int row = blockIdx.x * kSpmvDotRows + 64 * u + rl;
+        if (row >= a.n) continue;
+        k[u] = a.row_ptr[row] + g;
+        k1[u] = a.row_ptr[row + 1];
+        if (g == 0) {
+            qi[u] = q[row];
+            pi[u] = d.beta_cur[0] * qp[row];
+        }
+    }
+    while (k[0] < k1[0] || k[1] < k1[1]) {       // both rows' loads in flight
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            if (k[u] < k1[u]) {
+                acc[u] = fma(a.val[k[u]], q[a.col[k[u]]], acc[u]);
+                k[u] += 16;
+            }
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+#pragma unroll
+        for (int m = 8; m > 0; m >>= 1) acc[u] += __shfl_xor(acc[u], m, 16);
+        if (g == 0) {
+            const int row = blockIdx.x * kSpmvDotRows + 64 * u + rl;
+            if (row < a.n) y[row] = acc[u];
+            part[64 * u + rl] = qi[u] * (acc[u] - pi[u]);   // rows past n: 0
+        }
+    }
+    __syncthreads();
+    if (tid < 64) {
+        double v = part[tid] + part[tid + 64];
+#pragma unroll
+        for (int m = 32; m > 0; m >>= 1) v += __shfl_xor(v, m);
+        if (tid == 0) d.dots[(long long)blockIdx.x * 2] = v;
+    }
+}
+
 }  // namespace
+
+hipError_t launch_spmv_dot(const SparseOp& a, const double* q, const double* qp, double* y, const Dev& d,
+                           hipStream_t st) {
+    static_assert(kSpmvDotRows == 128, "two rows a lane group, one wave adds up a block's rows");
+    const int blocks = (a.n + kSpmvDotRows - 1) / kSpmvDotRows;
+    if (d.s != 1 || d.nprob != 1 || blocks != d.dots_blocks) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(spmv1_dot_kernel, dim3(blocks), dim3(1024), 0, st, a, q, qp, y, d);
+    return hipGetLastError();
+}
 
 hipError_t launch_csr_check(const int* row_ptr, const int* col, int n, int nnz, int* bad, hipStream_t st) {
     const long long work = std::max((long long)n + 1, (long long)nnz);
