@@ -535,7 +535,7 @@ int pc_build(const ciq_problem& p, const double* xh, int dp, int kernel, int ard
 // (blocked Cholesky of the observation block and the triangular solve for W
 // on the device, chol.hip). Every product with
 // Sigma is the candidate kernel product plus the low-rank correction
-// -W (W^T v), accumulated into the product's first partial.
+// -W (W^T v), as further partials of the product (Run::post_correct).
 struct PostSpec {
     const void* x_obs;   // device, n_obs x d (element type of the candidates' X)
     int n_obs;
