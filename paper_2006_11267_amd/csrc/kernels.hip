@@ -124,8 +124,9 @@ hipError_t launch_mvm(int dtype, const MvmArgs& a, hipStream_t st) {
     // Accumulators hold at most 8 (FP32) / 4 (FP64, split forms) column blocks
     // of 16; wider right-hand sides run as column groups, each regenerating its
     // entries. FP32 with a.fx: groups of more than 16 columns on the BF16 matrix
-    // cores (mvm_fx.hip); at 16 columns splitting V and the entries costs what
-    // the faster contraction saves (0.54 ms of matrix time at N = 50,000).
+    // cores (mvm_fx.hip); up to 16 columns the splits cost more than the faster
+    // contraction saves (N = 50,000, d = 6: 2.04 ms against 2.16 with them; 17
+    // columns, d = 3: 2.86 against 1.94).
     // FP32 partials: the resident FP32 and split-FP16 products only
     if (a.y32 != nullptr && !((dtype == CIQ_F32 || dtype == CIQ_F16X3) && a.kt != nullptr && a.wl == nullptr))
         return hipErrorInvalidValue;

@@ -13,7 +13,8 @@
 // time there; the entries' evaluation and split (about 27 vector instructions,
 // two of them of a quarter of the rate) are the bound. Measured, same size:
 // 4.55 -> 2.9 ms; 32 columns 3.20 -> 2.20, 128 columns 9.33 -> 5.5; N = 20,000,
-// 64 columns 0.82 -> 0.58. At 16 columns the split costs what it saves.
+// 64 columns 0.82 -> 0.58. At 16 columns the FP32 form stays:
+// 2.04 ms against 2.16.
 //
 // FP32 sums: per chunk of 64 columns the cross terms first, then the two
 // Kh Vh, then to FP64. The matrix cores cut a sum of eight products off
