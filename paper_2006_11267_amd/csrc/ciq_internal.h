@@ -109,7 +109,7 @@ constexpr float kOp3Scale = 16384.0f;  // scale of unit-norm vectors there
 constexpr float kKxScale = 16384.0f;   // and of the unit-scale entries
 
 inline size_t op_halfs(size_t rows_pad, int nsbt, int parts) { return rows_pad * (size_t)nsbt * 16 * parts; }
-inline float op_scale_of(int parts) { return parts == 3 ? kOp3Scale : kOp16Scale; }
+inline double op_scale_of(int parts) { return parts == 3 ? kOp3Scale : kOp16Scale; }
 
 // Where the update / start kernels write the split FP16 copy of the next
 // product operand (p == nullptr: none), in two (op16_index) or three
@@ -117,7 +117,7 @@ inline float op_scale_of(int parts) { return parts == 3 ? kOp3Scale : kOp16Scale
 struct Op16 {
     void* p;
     int nsbt;
-    float scale;
+    double scale;
     int parts;
 };
 // column blocks of 16 in a split operand buffer for s columns: 1, 2, 4 or a
@@ -284,7 +284,7 @@ hipError_t launch_step_owner(const Dev& d, const double* y, long long ysplit, in
 template <typename T>
 hipError_t launch_update(const Dev& d, const T* y, long long ysplit, int nsplit, const T* qcur,
                          T* qprev, const T* m_prev, T* m_cur, T* acc, T* solves, float* q32,
-                         int max_n, hipStream_t st, T* pnext = nullptr, Op16 op = Op16{nullptr, 0, 1.0f, 0});
+                         int max_n, hipStream_t st, T* pnext = nullptr, Op16 op = Op16{nullptr, 0, 1.0, 0});
 
 // pvec (nullable): preconditioned start, pvec <- pvec / beta_1 too and q32
 // copies pvec instead of q.
@@ -312,7 +312,7 @@ hipError_t launch_basis_solves(const Dev& d, int iters, double* cq, double* acc,
 
 template <typename T>
 hipError_t launch_init_vectors(const Dev& d, T* q, T* qprev, T* acc, float* q32, int rows,
-                               hipStream_t st, T* pvec = nullptr, Op16 op = Op16{nullptr, 0, 1.0f, 0});
+                               hipStream_t st, T* pvec = nullptr, Op16 op = Op16{nullptr, 0, 1.0, 0});
 
 // Split FP16 operand (two parts in op16_index layout or three in op3_index
 // layout, nsbt column blocks) of the n x s FP64 block x (ld): per-column

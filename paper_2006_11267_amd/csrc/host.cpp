@@ -656,7 +656,7 @@ struct Run {
     // resident products with a split operand (parts() > 0): tiled copy of q_j / p_j
     void* vt16 = nullptr;
     int nsbt = 0;
-    float op_scale = kOp16Scale;
+    double op_scale = kOp16Scale;
     double* opsc = nullptr;      // [s] per-column scales of an arbitrary operand (final product)
     double* opinv = nullptr;
     Dev d{};
@@ -1575,8 +1575,7 @@ int solve(int nprob, const ciq_problem* probs, const ciq_opts* o, const void* co
         bnd.pc = &pc;
         // the operand p_j = P^{-1} z_j has p_j^T z_j = 1 and P >= sigma^2 I, so
         // |p_j| <= 1/sigma: scale it by the power of two at most 256 sigma
-        const float sc =
-            (float)std::ldexp(1.0, (int)std::floor(std::log2(kOp16Scale * std::sqrt(probs[0].noise))));
+        const double sc = std::ldexp(1.0, (int)std::floor(std::log2(kOp16Scale * std::sqrt(probs[0].noise))));
         main.op_scale = sc;
         bnd.op_scale = sc;
     }

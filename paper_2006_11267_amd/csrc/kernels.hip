@@ -855,7 +855,7 @@ hipError_t launch_scalar(const Dev& d, hipStream_t st) {
 // ----------------------------------------------------------------------------
 // Element (i, c) of the split FP16 operand copy (op16_index layout), x scaled
 // by `scale` first (a power of two, so the split is of x itself).
-__device__ inline void put_op16(_Float16* vt, int nsbt, int i, int c, double x, float scale) {
+__device__ inline void put_op16(_Float16* vt, int nsbt, int i, int c, double x, double scale) {
     const double xs = x * (double)scale;
     const _Float16 hi = (_Float16)(float)xs;
     const _Float16 lo = (_Float16)(float)((xs - (double)hi) * 2048.0);
@@ -865,8 +865,8 @@ __device__ inline void put_op16(_Float16* vt, int nsbt, int i, int c, double x, 
 }
 
 // Element (i, c) of the three-part operand copy (op3_index layout).
-__device__ __forceinline__ void split3_f16(double x, float scale, _Float16& h, _Float16& m, _Float16& l) {
-    const double xs = x * (double)scale;
+__device__ __forceinline__ void split3_f16(double x, double scale, _Float16& h, _Float16& m, _Float16& l) {
+    const double xs = x * scale;
     h = (_Float16)(float)xs;
     const double r = xs - (double)h;
     m = (_Float16)(float)r;
@@ -1022,7 +1022,7 @@ __global__ __launch_bounds__(256) void update_split_kernel(Dev d, const double* 
             part[1][m] = mm;
             part[2][m] = l;
         } else {
-            const double xs = qn * (double)op.scale;
+            const double xs = qn * op.scale;
             const _Float16 hi = (_Float16)(float)xs;
             part[0][m] = hi;
             part[1][m] = (_Float16)(float)((xs - (double)hi) * 2048.0);
@@ -1480,7 +1480,8 @@ template hipError_t launch_init_vectors<double>(const Dev&, double*, double*, do
 // Split FP16 operand of an arbitrary FP64 block vector: per column a power of
 // two 2^e with max_i |x[i][c]| 2^e in [half, full) of the parts' scale (256 or
 // 16384; 1 for a zero column), then the split of x[i][c] 2^e. inv[c] = 2^-e
-// undoes it in the product.
+// undoes it in the product. The scale stays in FP64: a column of FP32 numbers
+// below 2^-114 needs one beyond FP32's range.
 // Block: 64 columns x 16 row lanes, fixed combination order.
 // ----------------------------------------------------------------------------
 __global__ __launch_bounds__(1024) void op16_scale_kernel(const double* x, int n, int s, int ld, int full_log2,
@@ -1499,7 +1500,7 @@ __global__ __launch_bounds__(1024) void op16_scale_kernel(const double* x, int n
         if (m > 0.0 && isfinite(m)) {
             int e = 0;
             (void)frexp(m, &e);          // m in [2^(e-1), 2^e)
-            sc = ldexp(1.0, full_log2 - e);
+            sc = ldexp(1.0, min(full_log2 - e, 1000));
         }
         scale[c] = sc;
         inv[c] = 1.0 / sc;
@@ -1510,7 +1511,7 @@ __global__ void op16_split_kernel(const double* x, int n, int s, int ld, const d
     const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= (long long)n * s) return;
     const int i = (int)(e / s), c = (int)(e - (long long)i * s);
-    op.scale = (float)scale[c];
+    op.scale = scale[c];
     put_op(op, i, c, x[(long long)i * ld + c]);
 }
 
@@ -1520,7 +1521,7 @@ hipError_t launch_op16_split(const double* x, int n, int s, int ld, double* scal
                        scale, inv);
     const long long total = (long long)n * s;
     hipLaunchKernelGGL(op16_split_kernel, dim3((int)((total + 255) / 256)), dim3(256), 0, st, x, n, s, ld, scale,
-                       Op16{vt, nsbt, 1.0f, parts});
+                       Op16{vt, nsbt, 1.0, parts});
     return hipGetLastError();
 }
 

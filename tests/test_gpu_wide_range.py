@@ -1,0 +1,62 @@
+"""FP32 products of more than 32 columns against a resident matrix over the
+range of FP32: very small columns, small entries and elements, infinities and
+NaN."""
+import numpy as np
+import pytest
+
+from gpu_util import announce, ciq_module, colwise_rel, torch_cuda
+from oracle import kernels as okern
+
+pytestmark = pytest.mark.gpu
+
+TINY = 2.0 ** -119          # 1.5e-36: a normal FP32 number
+
+
+def _case(torch, ciq, n, s, seed, kind="matern52", d=3, ls=0.4, noise=0.1):
+    rng = np.random.default_rng(seed)
+    x = rng.random((n, d)).astype(np.float32)
+    b = rng.standard_normal((n, s)).astype(np.float32)
+    K = okern.kernel_matrix(kind, x.astype(np.float64), [ls], 1.0, noise)
+    return ciq.Problem(torch.from_numpy(x).cuda(), kind, [ls], 1.0, noise), b, K
+
+
+@pytest.mark.parametrize("prec", ["f32", "f16x3"])
+def test_tiny_column_product(prec):
+    """A column scaled by 2^-119 is the unscaled column's product scaled: the
+    operand's scale is a power of two per column (FP32 results of 2^-119 keep
+    their 24 bits)."""
+    torch = torch_cuda()
+    ciq = ciq_module()
+    prob, b, _ = _case(torch, ciq, 500, 40, 1)
+    tiny = b.copy()
+    tiny[:, 1] *= np.float32(TINY)
+    b[:, 1] = tiny[:, 1] / TINY          # the same numbers: subnormal ones have lost bits
+    announce(f"tiny column: resident product {prec}")
+    y = ciq.ciq_kernel_mvm_resident(prob, torch.from_numpy(b).cuda(), precision=prec).cpu().numpy()
+    yt = ciq.ciq_kernel_mvm_resident(prob, torch.from_numpy(tiny).cuda(), precision=prec).cpu().numpy()
+    y[:, 1] *= np.float32(TINY)
+    # elements below 2^-126 come out rounded to FP32's subnormal step
+    assert np.all(np.abs(yt.astype(np.float64) - y) <= 2.0 ** -149)
+
+
+@pytest.mark.parametrize("prec", ["f32", "f16x3"])
+def test_tiny_column_roots(prec):
+    """K^{1/2} B with a column of 2^-119 (its last product is with a vector that
+    is not normalised), and the square root's backward (FP32; its first one is):
+    against the dense FP64 result, 2e-5 per column in FP32 as in the other wide
+    roots of this size, 1e-4 in split FP16."""
+    torch = torch_cuda()
+    ciq = ciq_module()
+    prob, b, K = _case(torch, ciq, 300, 40, 2)
+    b[:, 1] *= np.float32(TINY)
+    lam, U = np.linalg.eigh(K)
+    root = lambda m: U @ (np.sqrt(lam)[:, None] * (U.T @ m.astype(np.float64)))  # noqa: E731
+    kw = dict(max_iter=600, tol=1e-7)
+    announce(f"tiny column: square root and backward {prec}")
+    bt = torch.from_numpy(b).cuda()
+    out, info, _ = ciq.ciq_sqrt_mvm(prob, bt, q=12, precision=prec, kernel_cache="on", **kw)
+    assert colwise_rel(out.cpu().numpy(), root(b)).max() < (2e-5 if prec == "f32" else 1e-4)
+    if prec == "f32":
+        _, info, solves = ciq.ciq_sqrt_mvm(prob, bt, q=12, keep_solves=True, **kw)
+        dB, *_ = ciq.ciq_backward(prob, bt, info["t"], info["w"], solves, mode="sqrt", **kw)
+        assert colwise_rel(dB.cpu().numpy(), root(b)).max() < 2e-5
