@@ -95,18 +95,23 @@ __host__ __device__ inline size_t op16_index(int i, int c, int nsbt) {
 }
 constexpr float kOp16Scale = 256.0f;   // scale of unit-norm Lanczos vectors (entries <= 1)
 
-// Three-part FP16 operand of the wide resident FP32 product (mvm_kx.hip): the
-// scaled element is hi + mid + lo, each the FP16 rounding of what the earlier
-// ones leave. Per k-step and column block 64 lanes x 8 halfs of each part;
-// row r of the k-step is lane (c % 16) + 16 (r % 4), half r / 4 (the order in
-// which the FP32 matrix holds its columns).
+// Three-part BF16 operand of the wide resident FP32 product (mvm_kx.hip): the
+// scaled element is hi + mid + lo, each the BF16 rounding of what the earlier
+// ones leave (bf16_parts.h). Per k-step and column block 64 lanes x 8 numbers of
+// each part; row r of the k-step is lane (c % 16) + 16 (r % 4), number r / 4 (the
+// order in which the FP32 matrix holds its columns).
 __host__ __device__ inline size_t op3_index(int i, int c, int nsbt) {
     const int ks = i >> 5, r = i & 31;
     const int lane = (c & 15) + 16 * (r & 3);
     return ((((size_t)ks * nsbt + (c >> 4)) * 3) * 64 + lane) * 8 + (r >> 2);
 }
-constexpr float kOp3Scale = 16384.0f;  // scale of unit-norm vectors there
-constexpr float kKxScale = 16384.0f;   // and of the unit-scale entries
+// Scales there. The parts hold all 24 bits of a number of 2^-109 and more, FP32
+// sums of 64 products of at most 2^(24 + 96) stay below 2^126: entries of FP32's
+// smallest normal size keep all their bits, and so do elements of 2^-205 of
+// their column's largest.
+constexpr float kKxScale = 0x1p24f;      // unit-scale entries
+constexpr float kOp3Scale = 0x1p60f;     // unit-norm vectors
+constexpr int kOp3ScaleLog2 = 96;        // others: their largest element, per column
 
 inline size_t op_halfs(size_t rows_pad, int nsbt, int parts) { return rows_pad * (size_t)nsbt * 16 * parts; }
 inline double op_scale_of(int parts) { return parts == 3 ? kOp3Scale : kOp16Scale; }
@@ -195,7 +200,7 @@ struct KBuildArgs {
     long long njs;           // padded columns / 4
     int elem;                // 0: FP64, 1: FP32 (entries evaluated in FP64, rounded
                              // once), 2: split FP16 hi + 2^-11 lo (4 bytes per entry)
-    float mult;              // FP32: power of two the stored entries are multiplied by
+    double mult;             // FP32: power of two the entries are multiplied by before their rounding
     void* kt;                // kcache_rows(n) x kcache_cols(n) entries
 };
 size_t kcache_rows(int n);

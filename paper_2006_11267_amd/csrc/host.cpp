@@ -1363,7 +1363,7 @@ int kcache_build(Run<T>& r, const KCache& kc, hipStream_t st) {
             ka.nchunk = (int)(kcache_cols(ka.n) / 64);
             ka.njs = (long long)(kcache_cols(ka.n) / 4);
             ka.elem = 1;
-            ka.mult = 1.0f;
+            ka.mult = 1.0;
             ka.kt = static_cast<float*>(kc.ptr) + r.h_pkt[p];
             HIPCHK(launch_kbuild(ka, st));
         }
@@ -1380,11 +1380,11 @@ int kcache_build(Run<T>& r, const KCache& kc, hipStream_t st) {
     ka.nchunk = (int)(kcache_cols(ka.n) / 64);
     ka.njs = (long long)(kcache_cols(ka.n) / 4);
     ka.elem = (r.dtype == CIQ_F16X3) ? 2 : (kc.elem == 4 ? 1 : 0);
-    ka.mult = (r.max_parts() == 3) ? kKxScale : 1.0f;
+    ka.mult = (r.max_parts() == 3) ? kKxScale : 1.0;
     ka.kt = kc.ptr;
     HIPCHK(launch_kbuild(ka, st));
     r.kt = kc.ptr;
-    r.kt_inv = 1.0 / (double)ka.mult;
+    r.kt_inv = 1.0 / ka.mult;
     r.njs = ka.njs;
     return CIQ_OK;
 }

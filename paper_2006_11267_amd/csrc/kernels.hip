@@ -8,6 +8,7 @@
 //    stage (Lanczos alpha/beta, per-shift Givens QR, stopping rule), and one
 //    fused vector update (next Lanczos vector, per-shift search directions,
 //    quadrature-weighted solution accumulation).
+#include "bf16_parts.h"
 #include "ciq_internal.h"
 
 #include <algorithm>
@@ -864,23 +865,15 @@ __device__ inline void put_op16(_Float16* vt, int nsbt, int i, int c, double x, 
     vt[k + 512] = lo;
 }
 
-// Element (i, c) of the three-part operand copy (op3_index layout).
-__device__ __forceinline__ void split3_f16(double x, double scale, _Float16& h, _Float16& m, _Float16& l) {
-    const double xs = x * scale;
-    h = (_Float16)(float)xs;
-    const double r = xs - (double)h;
-    m = (_Float16)(float)r;
-    l = (_Float16)(float)(r - (double)m);
-}
-
+// Element (i, c) of the split operand copy, in two or three (op3_index layout) parts.
 __device__ inline void put_op(const Op16& op, int i, int c, double x) {
-    _Float16* vt = static_cast<_Float16*>(op.p);
     if (op.parts == 2) {
-        put_op16(vt, op.nsbt, i, c, x, op.scale);
+        put_op16(static_cast<_Float16*>(op.p), op.nsbt, i, c, x, op.scale);
         return;
     }
-    _Float16 h, m, l;
-    split3_f16(x, op.scale, h, m, l);
+    __bf16* vt = static_cast<__bf16*>(op.p);
+    __bf16 h, m, l;
+    bf16::split3(x * op.scale, h, m, l);
     const size_t k = op3_index(i, c, op.nsbt);
     vt[k] = h;
     vt[k + 512] = m;
@@ -980,7 +973,6 @@ template <int PARTS>
 __global__ __launch_bounds__(256) void update_split_kernel(Dev d, const double* __restrict__ y,
                                                            const double* __restrict__ qcur, double* __restrict__ qprev,
                                                            Op16 op) {
-    typedef _Float16 half8 __attribute__((ext_vector_type(8)));
     if (!d.st->live) return;
     const int s = d.s, n = d.n[0];
     const int slot = d.st->iter;
@@ -1003,7 +995,8 @@ __global__ __launch_bounds__(256) void update_split_kernel(Dev d, const double* 
         qv[m] = (i < n) ? qcur[idx] : 0.0;
         pv[m] = (i < n) ? qprev[idx] : 0.0;
     }
-    half8 part[PARTS];
+    typedef unsigned short part8 __attribute__((ext_vector_type(8)));
+    part8 part[PARTS];
 #pragma unroll
     for (int m = 0; m < 8; ++m) {
         const int i = i0 + RS * m;
@@ -1016,19 +1009,19 @@ __global__ __launch_bounds__(256) void update_split_kernel(Dev d, const double* 
             if (bq) bq[idx] = qn;
         }
         if constexpr (PARTS == 3) {
-            _Float16 h, mm, l;
-            split3_f16(qn, op.scale, h, mm, l);
-            part[0][m] = h;
-            part[1][m] = mm;
-            part[2][m] = l;
+            __bf16 h, mm, l;
+            bf16::split3(qn * op.scale, h, mm, l);
+            part[0][m] = __builtin_bit_cast(unsigned short, h);
+            part[1][m] = __builtin_bit_cast(unsigned short, mm);
+            part[2][m] = __builtin_bit_cast(unsigned short, l);
         } else {
             const double xs = qn * op.scale;
             const _Float16 hi = (_Float16)(float)xs;
-            part[0][m] = hi;
-            part[1][m] = (_Float16)(float)((xs - (double)hi) * 2048.0);
+            part[0][m] = __builtin_bit_cast(unsigned short, hi);
+            part[1][m] = __builtin_bit_cast(unsigned short, (_Float16)(float)((xs - (double)hi) * 2048.0));
         }
     }
-    half8* out = static_cast<half8*>(op.p) + ((size_t)ks * op.nsbt + (c >> 4)) * 64 * PARTS + (c & 15) + 16 * g;
+    part8* out = static_cast<part8*>(op.p) + ((size_t)ks * op.nsbt + (c >> 4)) * 64 * PARTS + (c & 15) + 16 * g;
 #pragma unroll
     for (int k = 0; k < PARTS; ++k) out[64 * k] = part[k];
 }
@@ -1477,11 +1470,11 @@ template hipError_t launch_init_vectors<double>(const Dev&, double*, double*, do
                                                 double*, Op16);
 
 // ----------------------------------------------------------------------------
-// Split FP16 operand of an arbitrary FP64 block vector: per column a power of
-// two 2^e with max_i |x[i][c]| 2^e in [half, full) of the parts' scale (256 or
-// 16384; 1 for a zero column), then the split of x[i][c] 2^e. inv[c] = 2^-e
-// undoes it in the product. The scale stays in FP64: a column of FP32 numbers
-// below 2^-114 needs one beyond FP32's range.
+// Split operand of an arbitrary FP64 block vector: per column a power of two 2^e
+// with max_i |x[i][c]| 2^e in [half, full), full 256 for two FP16 parts and
+// 2^kOp3ScaleLog2 for three BF16 ones (1 for a zero column), then the split of
+// x[i][c] 2^e. inv[c] = 2^-e undoes it in the product. The scale stays in FP64:
+// a column of small FP32 numbers needs one beyond FP32's range.
 // Block: 64 columns x 16 row lanes, fixed combination order.
 // ----------------------------------------------------------------------------
 __global__ __launch_bounds__(1024) void op16_scale_kernel(const double* x, int n, int s, int ld, int full_log2,
@@ -1517,8 +1510,8 @@ __global__ void op16_split_kernel(const double* x, int n, int s, int ld, const d
 
 hipError_t launch_op16_split(const double* x, int n, int s, int ld, double* scale, double* inv, void* vt,
                              int nsbt, int parts, hipStream_t st) {
-    hipLaunchKernelGGL(op16_scale_kernel, dim3((s + 63) / 64), dim3(1024), 0, st, x, n, s, ld, parts == 3 ? 14 : 8,
-                       scale, inv);
+    hipLaunchKernelGGL(op16_scale_kernel, dim3((s + 63) / 64), dim3(1024), 0, st, x, n, s, ld,
+                       parts == 3 ? kOp3ScaleLog2 : 8, scale, inv);
     const long long total = (long long)n * s;
     hipLaunchKernelGGL(op16_split_kernel, dim3((int)((total + 255) / 256)), dim3(256), 0, st, x, n, s, ld, scale,
                        Op16{vt, nsbt, 1.0, parts});

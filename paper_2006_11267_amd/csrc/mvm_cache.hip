@@ -119,7 +119,7 @@ __global__ __launch_bounds__(256) void kbuild_kernel(KBuildArgs a) {
             for (int p = 0; p < 4; ++p) {
                 floatx4 kv;
 #pragma unroll
-                for (int h = 0; h < 4; ++h) kv[h] = (float)entry(16 * p + 4 * h + (lane >> 4)) * a.mult;
+                for (int h = 0; h < 4; ++h) kv[h] = (float)(entry(16 * p + 4 * h + (lane >> 4)) * a.mult);
                 __builtin_nontemporal_store(kv, out32 + (size_t)(c * 4 + p) * 64);
             }
         } else {

@@ -38,51 +38,15 @@
 // launches of 64 (5.5 against 5.8 ms: entries are evaluated once).
 #include <algorithm>
 
+#include "bf16_parts.h"
 #include "mvm_mfma.h"
 
 namespace ciq {
 namespace {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef float floatx2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
-
-constexpr float kBf16Max = 0x1.fep127f;
-
-__device__ __forceinline__ unsigned int pk_bf16(float a, float b) {
-    return __builtin_bit_cast(unsigned int, __builtin_convertvector((floatx2{a, b}), bf16x2));
-}
-__device__ __forceinline__ float bf_lo(unsigned int p) { return __builtin_bit_cast(float, p << 16); }
-__device__ __forceinline__ float bf_hi(unsigned int p) { return __builtin_bit_cast(float, p & 0xffff0000u); }
-
-// eight values as three BF16 parts whose sum is the value (8 bits each, the
-// remainders of a rounding to nearest are exact). CLAMP: values that round to
-// infinity, and infinities, leave a finite first part; an infinity ends up in
-// the last part alone, so that it meets only the first part of an entry, as
-// the FP32 product would have multiplied it.
-template <bool CLAMP>
-__device__ __forceinline__ void split3(const float* e, bf16x8& h, bf16x8& m, bf16x8& l) {
-    uintx4 hb, mb, lb;
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        float x0 = e[2 * p], x1 = e[2 * p + 1];
-        auto cl = [](float x) { return CLAMP ? __builtin_amdgcn_fmed3f(x, -kBf16Max, kBf16Max) : x; };
-        const unsigned int hp = pk_bf16(cl(x0), cl(x1));
-        x0 -= bf_lo(hp);
-        x1 -= bf_hi(hp);
-        const unsigned int mp = pk_bf16(cl(x0), cl(x1));
-        x0 -= bf_lo(mp);
-        x1 -= bf_hi(mp);
-        hb[p] = hp;
-        mb[p] = mp;
-        lb[p] = pk_bf16(x0, x1);
-    }
-    h = __builtin_bit_cast(bf16x8, hb);
-    m = __builtin_bit_cast(bf16x8, mb);
-    l = __builtin_bit_cast(bf16x8, lb);
-}
+using bf16::bf16x8;
+using bf16::split3;
 
 // a value that is the same in every lane, kept in a scalar register
 __device__ __forceinline__ float uniform(float x) {

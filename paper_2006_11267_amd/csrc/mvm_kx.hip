@@ -1,23 +1,23 @@
-// Resident FP32 kernel matrix times more than 32 columns (CIQ_F32) on the FP16
+// Resident FP32 kernel matrix times more than 32 columns (CIQ_F32) on the BF16
 // matrix cores.
 //
 // v_mfma_f32_16x16x4_f32 runs at 157 TFLOP/s, so at 64 columns the FP32
 // contraction, not the stream of K, bounds a product (2.84 ms at N = 50,000,
 // S = 64, where reading the 10 GB matrix takes 1.6 ms). Here every FP32 entry
-// is split in registers into three FP16 parts, 11 + 11 + 2 significant bits,
-// whose sum is the entry exactly, and the operand vector (written split by
-// the update kernel, op3_index layout) likewise carries 33 bits, so that
-//     K V ~ Kh Vh + (Kh Vm + Km Vh + Km Vm + Kh Vl + Kl Vh)
-// drops only terms below 2^-33 of Kh Vh: six v_mfma_f32_16x16x32_f16 cost 0.9
-// ms of matrix time at that size and the stream of K becomes the bound. Both
-// operands are kept scaled by 2^14 (K in [0, 1] by the build pass, |V| <= 1 by
-// the kernels that write it), which keeps the low
-// parts above FP16's subnormal quantum; the matrix cores take subnormal FP16
-// inputs as they are (checked on gfx950 with an in-bounds probe).
+// is split in registers into three BF16 parts of 8 bits whose sum it is, the
+// operand vector (written split by the update kernel, op3_index layout) likewise,
+// and
+//     K V ~ Kh Vh + (Kh Vm + Km Vh) + (Km Vm + Kh Vl + Kl Vh)
+// drops terms of 2^-26 of Kh Vh and less: six v_mfma_f32_16x16x32_bf16 cost 0.9
+// ms of matrix time at that size and the stream of K becomes the bound. BF16
+// has FP32's range, so the parts keep all 24 bits of small entries and elements
+// as well (FP16 parts take 3.5 instead of 5.5 vector instructions an entry, but
+// end at 2^-38 of the outputscale: entries below 2^-15 lost bits and those below
+// 2^-38 vanished); the scales that keep their lowest parts above 2^-133 are in
+// ciq_internal.h.
 //
-// Kh Vh is summed in FP32 over one 64-column chunk (two MFMAs) and then taken
-// to FP64; the five cross terms are 2^-11 of it and stay in one FP32
-// accumulator over the block's column range.
+// FP32 sums: per chunk of 64 columns the cross terms first, then the two Kh Vh,
+// then to FP64.
 //
 // K is read in the layout of the FP32 form (mvm_cache.hip): lane l of a
 // 16-row tile holds K[l % 16][4 st + l / 16], st = 0..15 of the chunk. The
@@ -29,48 +29,26 @@
 // split operand (NSB column blocks x 2 k-steps x three parts, 1 KB each) in one
 // of two LDS buffers, one barrier per chunk (see kt32_item). Sixteen waves
 // halve the operand's L2 reads (24 KB per block and chunk against 64 KB of K)
-// and fit 128 registers a wave. Measured at N = 50,000, S = 64: 2.13 ms with
-// sixteen waves, 2.20 with eight (the FP32 MFMA form: 2.86 with FP32 sums of
-// 64 columns, 3.72 with sums of 16); 12 waves with two chunks of K in flight
-// 2.23, two tiles a wave 2.31, 128 columns a launch 4.35 (no better than two
-// groups of 64). More than 64 columns run as groups of one launch, the groups
+// and fit 128 registers a wave. Measured at N = 50,000, S = 64 (the FP32 MFMA
+// form: 2.86 ms with FP32 sums of 64 columns, 3.72 with sums of 16): 2.16 ms with
+// sixteen waves, 4.7 TB/s of K (FP16 parts in turn with them: 2.15). With FP16
+// parts, of 2.13 in that run: eight waves 2.20, 12 waves with two chunks of K in
+// flight 2.23, two tiles a wave 2.31, 128 columns a launch 4.35 (no better than
+// two groups of 64). More than 64 columns run as groups of one launch, the groups
 // of a row block next to each other on one XCD so that its L2 serves K to the
-// later ones. Relative error of one product against 64 bits: 7e-8 (FP32 MFMA:
-// 1.5e-7), half of it the rounding of the entries.
+// later ones.
 #include <algorithm>
 #include <cmath>
 
+#include "bf16_parts.h"
 #include "ciq_internal.h"
 
 namespace ciq {
 namespace {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
-
-// eight (scaled) entries as three FP16 parts, rounded towards zero so that
-// every remainder is exact. minus1 is -1 in a register the compiler cannot see
-// through: it keeps each remainder one v_fma_mix_f32 (an FP16 operand read as
-// FP32) instead of a conversion and a subtraction.
-__device__ __forceinline__ void split3(const float* k, float minus1, f16x8& h, f16x8& m, f16x8& l) {
-    uintx4 hb, mb, lb;
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        const float x0 = k[2 * p], x1 = k[2 * p + 1];
-        const auto hp = __builtin_amdgcn_cvt_pkrtz(x0, x1);
-        const float r0 = __builtin_fmaf((float)hp[0], minus1, x0), r1 = __builtin_fmaf((float)hp[1], minus1, x1);
-        const auto mp = __builtin_amdgcn_cvt_pkrtz(r0, r1);
-        const auto lp = __builtin_amdgcn_cvt_pkrtz(__builtin_fmaf((float)mp[0], minus1, r0),
-                                                   __builtin_fmaf((float)mp[1], minus1, r1));
-        hb[p] = __builtin_bit_cast(unsigned int, hp);
-        mb[p] = __builtin_bit_cast(unsigned int, mp);
-        lb[p] = __builtin_bit_cast(unsigned int, lp);
-    }
-    h = __builtin_bit_cast(f16x8, hb);
-    m = __builtin_bit_cast(f16x8, mb);
-    l = __builtin_bit_cast(f16x8, lb);
-}
+using bf16::bf16x8;
+using bf16::split3;
 
 template <int NSB, int WAVES>
 __global__ __launch_bounds__(64 * WAVES, 4) void mvm_kx_kernel(MvmArgs a, int groups) {
@@ -78,7 +56,7 @@ __global__ __launch_bounds__(64 * WAVES, 4) void mvm_kx_kernel(MvmArgs a, int gr
     constexpr int VB = NSB * 192;                // 16-byte operand units per k-step
     constexpr int VU = 2 * VB;                   // per chunk
     constexpr int UPT = (VU + NT - 1) / NT;
-    __shared__ f16x8 vs[2 * VU];
+    __shared__ bf16x8 vs[2 * VU];
 
     if (a.done != nullptr && *a.done != 0) return;
     const int nsplit = a.nsplit;
@@ -86,7 +64,7 @@ __global__ __launch_bounds__(64 * WAVES, 4) void mvm_kx_kernel(MvmArgs a, int gr
     const int x = (int)(blockIdx.x / (unsigned)nsplit);
     const int rb = x / groups, grp = x - rb * groups;
     const int n = a.n;
-    const f16x8* __restrict__ vt = static_cast<const f16x8*>(a.vt) + grp * VB;
+    const bf16x8* __restrict__ vt = static_cast<const bf16x8*>(a.vt) + grp * VB;
     const int kstride = a.nsbt * 192;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -98,18 +76,16 @@ __global__ __launch_bounds__(64 * WAVES, 4) void mvm_kx_kernel(MvmArgs a, int gr
     const int c0 = (int)(((long long)split * nchunk) / nsplit);
     const int c1 = (int)(((long long)(split + 1) * nchunk) / nsplit);
 
-    floatx4 ah[NSB], ax[NSB];
+    floatx4 acc[NSB];
     double accd[NSB][4];
 #pragma unroll
-    for (int sb = 0; sb < NSB; ++sb) {
-        ax[sb] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int sb = 0; sb < NSB; ++sb)
 #pragma unroll
         for (int r = 0; r < 4; ++r) accd[sb][r] = 0.0;
-    }
 
     // operand staging: thread offsets within a chunk are fixed, the chunk's
     // base is uniform
-    f16x8 vreg[UPT];
+    bf16x8 vreg[UPT];
     int voff[UPT];
 #pragma unroll
     for (int u = 0; u < UPT; ++u) {
@@ -117,15 +93,13 @@ __global__ __launch_bounds__(64 * WAVES, 4) void mvm_kx_kernel(MvmArgs a, int gr
         voff[u] = e + (e >= VB ? kstride - VB : 0);
     }
     auto fetch_v = [&](int c) {
-        const f16x8* base = vt + (long long)c * 2 * kstride;
+        const bf16x8* base = vt + (long long)c * 2 * kstride;
 #pragma unroll
         for (int u = 0; u < UPT; ++u) {
             if (VU % NT != 0 && tid + NT * u >= VU) break;
             vreg[u] = base[(unsigned)voff[u]];
         }
     };
-    float minus1 = -1.0f;
-    asm volatile("" : "+s"(minus1));
     const float* kb = static_cast<const float*>(a.kt) + (size_t)min(tile, tmax) * a.njs * 64;
     // one chunk of K in flight per wave; half a chunk (k-step kk) of the next
     // one is requested as soon as the registers of this one's half are free
@@ -140,7 +114,7 @@ __global__ __launch_bounds__(64 * WAVES, 4) void mvm_kx_kernel(MvmArgs a, int gr
         }
     };
     auto chunk = [&](int c) {
-        f16x8* vb = vs + (c & 1) * VU;
+        bf16x8* vb = vs + (c & 1) * VU;
 #pragma unroll
         for (int u = 0; u < UPT; ++u) {
             const int e = tid + NT * u;
@@ -149,28 +123,33 @@ __global__ __launch_bounds__(64 * WAVES, 4) void mvm_kx_kernel(MvmArgs a, int gr
         }
         __syncthreads();
         if (c + 1 < c1) fetch_v(c + 1);
+        bf16x8 kh[2];
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) {
-            f16x8 kh, km, kl;
-            split3(kq + 8 * kk, minus1, kh, km, kl);
+            bf16x8 km, kl;
+            split3<false>(kq + 8 * kk, kh[kk], km, kl);
             if (c + 1 < c1) fetch_k(c + 1, kk);
-            const f16x8* bp = vb + kk * VB + lane;
+            const bf16x8* bp = vb + kk * VB + lane;
 #pragma unroll
             for (int sb = 0; sb < NSB; ++sb) {
-                const f16x8 bh = bp[sb * 192], bm = bp[sb * 192 + 64], bl = bp[sb * 192 + 128];
-                ah[sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-                    kh, bh, kk == 0 ? floatx4{0.f, 0.f, 0.f, 0.f} : ah[sb], 0, 0, 0);
-                ax[sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(km, bh, ax[sb], 0, 0, 0);
-                ax[sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kl, bh, ax[sb], 0, 0, 0);
-                ax[sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kh, bm, ax[sb], 0, 0, 0);
-                ax[sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(km, bm, ax[sb], 0, 0, 0);
-                ax[sb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kh, bl, ax[sb], 0, 0, 0);
+                const bf16x8 bh = bp[sb * 192], bm = bp[sb * 192 + 64], bl = bp[sb * 192 + 128];
+                floatx4 t = kk == 0 ? floatx4{0.f, 0.f, 0.f, 0.f} : acc[sb];
+                t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kl, bh, t, 0, 0, 0);
+                t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kh[kk], bl, t, 0, 0, 0);
+                t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(km, bm, t, 0, 0, 0);
+                t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(km, bh, t, 0, 0, 0);
+                t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kh[kk], bm, t, 0, 0, 0);
+                if (kk == 1) {
+                    t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kh[0], vb[sb * 192 + lane], t, 0, 0, 0);
+                    t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kh[1], bh, t, 0, 0, 0);
+                }
+                acc[sb] = t;
             }
         }
 #pragma unroll
         for (int sb = 0; sb < NSB; ++sb)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) accd[sb][r] += (double)ah[sb][r];
+            for (int r = 0; r < 4; ++r) accd[sb][r] += (double)acc[sb][r];
     };
     if (c0 < c1) {
         fetch_v(c0);
@@ -193,7 +172,7 @@ __global__ __launch_bounds__(64 * WAVES, 4) void mvm_kx_kernel(MvmArgs a, int gr
         for (int r = 0; r < 4; ++r) {
             const int i = tile * 16 + 4 * (lane >> 4) + r;   // 16x16 accumulator layout
             if (i < n) {
-                double val = o2 * ((accd[sb][r] + (double)ax[sb][r]) * vi);
+                double val = o2 * (accd[sb][r] * vi);
                 if (split == 0) val = fma(s2, v[(long long)i * ldv + cc], val);
                 if (y32) y32[(long long)i * ldy + cc] = (float)val;
                 else y[(long long)i * ldy + cc] = val;

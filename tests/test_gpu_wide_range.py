@@ -60,3 +60,38 @@ def test_tiny_column_roots(prec):
         _, info, solves = ciq.ciq_sqrt_mvm(prob, bt, q=12, keep_solves=True, **kw)
         dB, *_ = ciq.ciq_backward(prob, bt, info["t"], info["w"], solves, mode="sqrt", **kw)
         assert colwise_rel(dB.cpu().numpy(), root(b)).max() < 2e-5
+
+
+@pytest.mark.parametrize("kind,ls", [("rbf", 0.1), ("matern52", 0.02)])
+def test_small_entries(kind, ls):
+    """Right-hand sides on four points only, short lengthscales: rows see them
+    through entries down to FP32's smallest. Every entry is rounded once (2^-24),
+    the operand to 2^-26, the dropped part products are 2^-25, four terms are cut
+    off at 2^-23 at most and the result is rounded: 11 x 2^-24 of |K||V| bounds
+    each element."""
+    torch = torch_cuda()
+    ciq = ciq_module()
+    prob, v, K = _case(torch, ciq, 300, 40, 3, kind, d=5, ls=ls)
+    v[4:] = 0.0
+    announce(f"small entries {kind} ls={ls}")
+    y = ciq.ciq_kernel_mvm_resident(prob, torch.from_numpy(v).cuda()).cpu().numpy().astype(np.float64)
+    v = v.astype(np.float64)
+    bound = 11 * 2.0 ** -24 * (np.abs(K) @ np.abs(v)) + 2.0 ** -148 * (1.0 + np.abs(v).sum(axis=0))
+    worst = (np.abs(y - K @ v) / bound).max()
+    print(f"worst element at {worst:.3f} of its bound", flush=True)
+    assert worst < 1.0
+
+
+def test_small_elements():
+    """Next to the identity a row's result is its own element, however small
+    beside the column's largest: elements from 1 to 2^-100, the bound as above
+    (one term that counts)."""
+    torch = torch_cuda()
+    ciq = ciq_module()
+    prob, v, K = _case(torch, ciq, 300, 40, 4, "rbf", d=5, ls=0.004)
+    v = (np.sign(v) * 2.0 ** -np.minimum(np.arange(300) % 101, 100)[:, None] * (1.0 + np.abs(v) % 1.0)).astype(np.float32)
+    announce("small elements")
+    y = ciq.ciq_kernel_mvm_resident(prob, torch.from_numpy(v).cuda()).cpu().numpy().astype(np.float64)
+    v = v.astype(np.float64)
+    bound = 11 * 2.0 ** -24 * (np.abs(K) @ np.abs(v))
+    assert (np.abs(y - K @ v) / bound).max() < 1.0
