@@ -99,12 +99,14 @@ constexpr float kOp16Scale = 256.0f;   // scale of unit-norm Lanczos vectors (en
 // scaled element is hi + mid + lo, each the BF16 rounding of what the earlier
 // ones leave (bf16_parts.h). Per k-step and column block 64 lanes x 8 numbers of
 // each part; row r of the k-step is lane (c % 16) + 16 (r % 4), number r / 4 (the
-// order in which the FP32 matrix holds its columns).
+// order in which the FP32 matrix holds its columns). Rows of odd 64-row chunks
+// are negated (op3_sign; the product undoes it).
 __host__ __device__ inline size_t op3_index(int i, int c, int nsbt) {
     const int ks = i >> 5, r = i & 31;
     const int lane = (c & 15) + 16 * (r & 3);
     return ((((size_t)ks * nsbt + (c >> 4)) * 3) * 64 + lane) * 8 + (r >> 2);
 }
+__host__ __device__ inline double op3_sign(int i) { return (i & 64) ? -1.0 : 1.0; }
 // Scales there. The parts hold all 24 bits of a number of 2^-109 and more, FP32
 // sums of 64 products of at most 2^(24 + 96) stay below 2^126: entries of FP32's
 // smallest normal size keep all their bits, and so do elements of 2^-205 of

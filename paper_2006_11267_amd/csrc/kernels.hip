@@ -873,7 +873,7 @@ __device__ inline void put_op(const Op16& op, int i, int c, double x) {
     }
     __bf16* vt = static_cast<__bf16*>(op.p);
     __bf16 h, m, l;
-    bf16::split3(x * op.scale, h, m, l);
+    bf16::split3(x * op3_sign(i) * op.scale, h, m, l);
     const size_t k = op3_index(i, c, op.nsbt);
     vt[k] = h;
     vt[k + 512] = m;
@@ -995,6 +995,7 @@ __global__ __launch_bounds__(256) void update_split_kernel(Dev d, const double* 
         qv[m] = (i < n) ? qcur[idx] : 0.0;
         pv[m] = (i < n) ? qprev[idx] : 0.0;
     }
+    const double sc = PARTS == 3 ? op.scale * op3_sign(i0) : op.scale;   // (a k-step lies in one chunk)
     typedef unsigned short part8 __attribute__((ext_vector_type(8)));
     part8 part[PARTS];
 #pragma unroll
@@ -1010,12 +1011,12 @@ __global__ __launch_bounds__(256) void update_split_kernel(Dev d, const double* 
         }
         if constexpr (PARTS == 3) {
             __bf16 h, mm, l;
-            bf16::split3(qn * op.scale, h, mm, l);
+            bf16::split3(qn * sc, h, mm, l);
             part[0][m] = __builtin_bit_cast(unsigned short, h);
             part[1][m] = __builtin_bit_cast(unsigned short, mm);
             part[2][m] = __builtin_bit_cast(unsigned short, l);
         } else {
-            const double xs = qn * op.scale;
+            const double xs = qn * sc;
             const _Float16 hi = (_Float16)(float)xs;
             part[0][m] = __builtin_bit_cast(unsigned short, hi);
             part[1][m] = __builtin_bit_cast(unsigned short, (_Float16)(float)((xs - (double)hi) * 2048.0));

@@ -17,7 +17,14 @@
 // ciq_internal.h.
 //
 // FP32 sums: per chunk of 64 columns the cross terms first, then the two Kh Vh,
-// then to FP64.
+// then to FP64. As in mvm_fx.hip the operand changes its sign from chunk to
+// chunk, because the matrix cores cut sums off downwards, and the diagonal entry
+// stays out of the matrix product: 2^-60 takes its place (an infinite V[i] must
+// still reach row i) and the epilogue adds V[i] itself, in FP64. Error of one
+// product against 64 bits (norms, in 2^-24; eight kernels, N = 3,000 to 20,000, d =
+// 2 to 10, lengthscales 0.05 to 1): Gaussian right-hand sides 0.4 to 1.1 (0.5 to 1.7
+// without the two measures and with FP16 parts, 0.5 to 2.5 on the FP32 matrix cores),
+// positive ones 0.43 to 0.54 (0.45 to 0.82; 0.43 to 0.54).
 //
 // K is read in the layout of the FP32 form (mvm_cache.hip): lane l of a
 // 16-row tile holds K[l % 16][4 st + l / 16], st = 0..15 of the chunk. The
@@ -123,10 +130,18 @@ __global__ __launch_bounds__(64 * WAVES, 4) void mvm_kx_kernel(MvmArgs a, int gr
         }
         __syncthreads();
         if (c + 1 < c1) fetch_v(c + 1);
+        const bool diag = c == (tile >> 2);         // the chunk holds the tile's diagonal
         bf16x8 kh[2];
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) {
             bf16x8 km, kl;
+            if (diag && kk == ((tile >> 1) & 1)) {  // row r's entry: column 16 (tile % 4) + r of the chunk
+                const int r = lane & 15, step = 4 * (tile & 3) + (r >> 2);
+#pragma unroll
+                for (int m = 0; m < 8; ++m)
+                    if (8 * kk + m == step && (r & 3) == (lane >> 4))
+                        kq[8 * kk + m] = (kq[8 * kk + m] - kKxScale) + kKxScale * 0x1p-60f;
+            }
             split3<false>(kq + 8 * kk, kh[kk], km, kl);
             if (c + 1 < c1) fetch_k(c + 1, kk);
             const bf16x8* bp = vb + kk * VB + lane;
@@ -149,7 +164,7 @@ __global__ __launch_bounds__(64 * WAVES, 4) void mvm_kx_kernel(MvmArgs a, int gr
 #pragma unroll
         for (int sb = 0; sb < NSB; ++sb)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) accd[sb][r] += (double)acc[sb][r];
+            for (int r = 0; r < 4; ++r) accd[sb][r] = fma((double)acc[sb][r], (c & 1) ? -1.0 : 1.0, accd[sb][r]);
     };
     if (c0 < c1) {
         fetch_v(c0);
@@ -158,7 +173,7 @@ __global__ __launch_bounds__(64 * WAVES, 4) void mvm_kx_kernel(MvmArgs a, int gr
     }
     for (int c = c0; c < c1; ++c) chunk(c);
 
-    const double o2 = a.o2, s2 = a.s2;
+    const double o2 = a.o2, dd = a.o2 * kKxScale + a.s2;   // the diagonal: entry and noise
     const double* __restrict__ v = static_cast<const double*>(a.v);
     double* __restrict__ y = static_cast<double*>(a.y) + (long long)split * a.ysplit;
     float* __restrict__ y32 = a.y32 ? a.y32 + (long long)split * a.ysplit : nullptr;
@@ -173,7 +188,7 @@ __global__ __launch_bounds__(64 * WAVES, 4) void mvm_kx_kernel(MvmArgs a, int gr
             const int i = tile * 16 + 4 * (lane >> 4) + r;   // 16x16 accumulator layout
             if (i < n) {
                 double val = o2 * (accd[sb][r] * vi);
-                if (split == 0) val = fma(s2, v[(long long)i * ldv + cc], val);
+                if (split == 0) val = fma(dd, v[(long long)i * ldv + cc], val);
                 if (y32) y32[(long long)i * ldy + cc] = (float)val;
                 else y[(long long)i * ldy + cc] = val;
             }

@@ -95,3 +95,21 @@ def test_small_elements():
     v = v.astype(np.float64)
     bound = 11 * 2.0 ** -24 * (np.abs(K) @ np.abs(v))
     assert (np.abs(y - K @ v) / bound).max() < 1.0
+
+
+def test_sums_are_not_biased():
+    """The matrix cores cut off downwards what an FP32 sum of eight products
+    cannot hold, always with the same sign; signs that alternate from chunk to
+    chunk cancel that. All positive sums: entries and results are rounded to
+    nearest, 2^-25 each that averages out over 4,096 rows, so a mean signed
+    relative error of 2^-26 would be the sums'."""
+    torch = torch_cuda()
+    ciq = ciq_module()
+    prob, v, K = _case(torch, ciq, 4096, 40, 8, "matern52", d=6, ls=0.3, noise=1e-2)
+    v = np.abs(v)
+    announce("bias of the sums")
+    y = ciq.ciq_kernel_mvm_resident(prob, torch.from_numpy(v).cuda()).cpu().numpy().astype(np.float64)
+    ref = K @ v.astype(np.float64)
+    bias = ((y - ref) / ref).mean() * 2.0 ** 26
+    print(f"mean signed relative error {bias:.3f} x 2^-26", flush=True)
+    assert abs(bias) < 1.0
