@@ -51,13 +51,15 @@ __device__ __forceinline__ void split3(const float* e, bf16x8& h, bf16x8& m, bf1
     l = __builtin_bit_cast(bf16x8, lb);
 }
 
-// One FP64 value, kept to 2^-27 of itself; infinities and NaN as above.
+// One FP64 value, kept to 2^-27 of itself; an infinity or NaN is the last part
+// (the others 0: products of scaled entries with a largest number would overflow).
 __device__ __forceinline__ void split3(double x, __bf16& h, __bf16& m, __bf16& l) {
-    h = (__bf16)clamp((float)x);
-    x -= (double)(float)h;
-    m = (__bf16)clamp((float)x);
-    x -= (double)(float)m;
-    l = (__bf16)(float)x;
+    const double f = fabs(x) < INFINITY ? x : 0.0;
+    h = (__bf16)(float)f;
+    double r = f - (double)(float)h;
+    m = (__bf16)(float)r;
+    r -= (double)(float)m;
+    l = (__bf16)(float)(f == x ? r : x);
 }
 
 }  // namespace bf16

@@ -1472,8 +1472,8 @@ template hipError_t launch_init_vectors<double>(const Dev&, double*, double*, do
 
 // ----------------------------------------------------------------------------
 // Split operand of an arbitrary FP64 block vector: per column a power of two 2^e
-// with max_i |x[i][c]| 2^e in [half, full), full 256 for two FP16 parts and
-// 2^kOp3ScaleLog2 for three BF16 ones (1 for a zero column), then the split of
+// with max_i |x[i][c]| 2^e in [half, full) over the finite elements, full 256 for
+// two FP16 parts and 2^kOp3ScaleLog2 for three BF16 ones (1 for a zero column), then the split of
 // x[i][c] 2^e. inv[c] = 2^-e undoes it in the product. The scale stays in FP64:
 // a column of small FP32 numbers needs one beyond FP32's range.
 // Block: 64 columns x 16 row lanes, fixed combination order.
@@ -1485,13 +1485,16 @@ __global__ __launch_bounds__(1024) void op16_scale_kernel(const double* x, int n
     const int c = blockIdx.x * 64 + cl;
     double m = 0.0;
     if (c < s)
-        for (int i = lane; i < n; i += 16) m = fmax(m, fabs(x[(long long)i * ld + c]));
+        for (int i = lane; i < n; i += 16) {
+            const double v = fabs(x[(long long)i * ld + c]);
+            if (v < INFINITY) m = fmax(m, v);
+        }
     sh[threadIdx.x] = m;
     __syncthreads();
     if (lane == 0 && c < s) {
         for (int r = 1; r < 16; ++r) m = fmax(m, sh[r * 64 + cl]);
         double sc = 1.0;
-        if (m > 0.0 && isfinite(m)) {
+        if (m > 0.0) {
             int e = 0;
             (void)frexp(m, &e);          // m in [2^(e-1), 2^e)
             sc = ldexp(1.0, min(full_log2 - e, 1000));

@@ -113,3 +113,29 @@ def test_sums_are_not_biased():
     bias = ((y - ref) / ref).mean() * 2.0 ** 26
     print(f"mean signed relative error {bias:.3f} x 2^-26", flush=True)
     assert abs(bias) < 1.0
+
+
+def test_infinities_and_nan():
+    """An infinite element reaches every row of its column with its sign, two of
+    opposite sign and a NaN make the column NaN, a column with one element at
+    FP32's end stays finite elsewhere, the other columns stay as they were."""
+    torch = torch_cuda()
+    ciq = ciq_module()
+    n = 200
+    prob, v, _ = _case(torch, ciq, n, 40, 5, ls=2.0)
+    v = torch.from_numpy(v).cuda()
+    announce("wide resident product: infinities")
+    base = ciq.ciq_kernel_mvm_resident(prob, v)
+    w = v.clone()
+    w[70, 0] = float("inf")
+    w[3, 1] = float("-inf")
+    w[5, 2], w[130, 2] = float("inf"), float("-inf")
+    w[199, 3] = float("nan")
+    w[:, 4] = 0.0
+    w[64, 4] = torch.finfo(torch.float32).max
+    y = ciq.ciq_kernel_mvm_resident(prob, w)
+    assert bool((y[:, 0] == float("inf")).all()) and bool((y[:, 1] == float("-inf")).all())
+    assert bool(torch.isnan(y[:, 2]).all()) and bool(torch.isnan(y[:, 3]).all())
+    other = torch.arange(n, device=y.device) != 64        # row 64: (1 + noise) max overflows
+    assert bool(torch.isfinite(y[other, 4]).all()) and float(y[other, 4].min()) > 0.0
+    assert torch.equal(y[:, 5:], base[:, 5:])
