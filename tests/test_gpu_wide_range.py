@@ -139,3 +139,30 @@ def test_infinities_and_nan():
     other = torch.arange(n, device=y.device) != 64        # row 64: (1 + noise) max overflows
     assert bool(torch.isfinite(y[other, 4]).all()) and float(y[other, 4].min()) > 0.0
     assert torch.equal(y[:, 5:], base[:, 5:])
+
+
+@pytest.mark.parametrize("mode", ["sqrt", "invsqrt"])
+@pytest.mark.parametrize("basis", ["auto", "off"])
+def test_wide_solve_basis_and_graph(mode, basis):
+    """Wide resident solves with and without the Krylov basis (the operand is
+    written by the update kernel of either) against the dense root, 1e-4 as for
+    the other FP32 solves of this conditioning; graph replays (host polls between
+    them) give the eager loop's bits."""
+    torch = torch_cuda()
+    ciq = ciq_module()
+    prob, b, K = _case(torch, ciq, 1501, 41, 6, d=4, ls=0.3)
+    lam, U = np.linalg.eigh(K)
+    p = 0.5 if mode == "sqrt" else -0.5
+    ref = U @ ((lam ** p)[:, None] * (U.T @ b.astype(np.float64)))
+    fn = ciq.ciq_sqrt_mvm if mode == "sqrt" else ciq.ciq_invsqrt_mvm
+    kw = dict(q=12, max_iter=800, tol=5e-6, bounds=(lam[0], lam[-1]), kernel_cache="on", krylov_basis=basis)
+    announce(f"wide solve {mode} basis={basis}")
+    bt = torch.from_numpy(b).cuda()
+    out, info, _ = fn(prob, bt, **kw)
+    assert info["converged"] and info["kernel_cached"] and info["krylov_basis"] == (basis == "auto")
+    err = colwise_rel(out.cpu().numpy(), ref).max()
+    print(f"{mode} basis={basis}: {err:.2e}, {info['iters']} iterations", flush=True)
+    assert err < 1e-4
+    for _ in range(2):
+        g, ginfo, _ = fn(prob, bt, graph=True, **kw)
+        assert ginfo["iters"] == info["iters"] and torch.equal(g, out)
