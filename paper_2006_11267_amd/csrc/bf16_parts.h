@@ -16,30 +16,22 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
 
-constexpr float kMax = 0x1.fep127f;
-
 __device__ __forceinline__ unsigned int pk(float a, float b) {
     return __builtin_bit_cast(unsigned int, __builtin_convertvector((floatx2{a, b}), bf16x2));
 }
 __device__ __forceinline__ float lo(unsigned int p) { return __builtin_bit_cast(float, p << 16); }
 __device__ __forceinline__ float hi(unsigned int p) { return __builtin_bit_cast(float, p & 0xffff0000u); }
-__device__ __forceinline__ float clamp(float x) { return __builtin_amdgcn_fmed3f(x, -kMax, kMax); }
 
-// Eight values. CLAMP: values that round to infinity, and infinities, leave a
-// finite first part; an infinity ends up in the last part alone, so that it
-// meets only the first part of an entry, as the FP32 product would have
-// multiplied it (a NaN ends up there too).
-template <bool CLAMP>
+// Eight values that do not round to infinity.
 __device__ __forceinline__ void split3(const float* e, bf16x8& h, bf16x8& m, bf16x8& l) {
     uintx4 hb, mb, lb;
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
         float x0 = e[2 * p], x1 = e[2 * p + 1];
-        auto cl = [](float x) { return CLAMP ? clamp(x) : x; };
-        const unsigned int hp = pk(cl(x0), cl(x1));
+        const unsigned int hp = pk(x0, x1);
         x0 -= lo(hp);
         x1 -= hi(hp);
-        const unsigned int mp = pk(cl(x0), cl(x1));
+        const unsigned int mp = pk(x0, x1);
         x0 -= lo(mp);
         x1 -= hi(mp);
         hb[p] = hp;
@@ -51,8 +43,18 @@ __device__ __forceinline__ void split3(const float* e, bf16x8& h, bf16x8& m, bf1
     l = __builtin_bit_cast(bf16x8, lb);
 }
 
-// One FP64 value, kept to 2^-27 of itself; an infinity or NaN is the last part
-// (the others 0: products of scaled entries with a largest number would overflow).
+// Infinities and NaN among them: the last part alone, so that an infinity meets
+// only the first part of an entry, as the FP32 product would have multiplied it.
+__device__ __forceinline__ void only_last(const float* e, bf16x8& h, bf16x8& m, bf16x8& l) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+        if (!(fabsf(e[q]) < INFINITY)) {
+            h[q] = m[q] = (__bf16)0.0f;
+            l[q] = (__bf16)e[q];
+        }
+}
+
+// One FP64 value, kept to 2^-27 of itself; infinities and NaN as above.
 __device__ __forceinline__ void split3(double x, __bf16& h, __bf16& m, __bf16& l) {
     const double f = fabs(x) < INFINITY ? x : 0.0;
     h = (__bf16)(float)f;

@@ -16,12 +16,20 @@
 // 64 columns 0.82 -> 0.58. At 16 columns the FP32 form stays:
 // 2.04 ms against 2.16.
 //
+// Range: BF16 parts hold all 24 bits of numbers of 2^-109 and more, so entries
+// are scaled by 2^24 and V by 2^40: FP32's smallest normal entries and all its
+// elements keep their bits. What the sums could then overflow by, elements of
+// 2^56 and more, infinities among them, is left out of a chunk's pass; a chunk
+// that had any takes a second pass with them alone, scaled by 2^-40. The scaling
+// costs up to 2 % (Matern) and, one more instruction an entry, 3 to 5 % (RBF:
+// 2.54 -> 2.62 ms at 64 columns, 1.87 -> 1.98 at 32).
+//
 // FP32 sums: per chunk of 64 columns the cross terms first, then the two
 // Kh Vh, then to FP64. The matrix cores cut a sum of eight products off
 // downwards (towards minus infinity), which adds up over the chunks (0.7 of
 // the whole error at N = 50,000), so V changes its sign from chunk to chunk.
 // The diagonal entry, which outweighs the rest of its chunk where lengthscales
-// are short, stays out of the matrix product: 2^-60 takes its place (an
+// are short, stays out of the matrix product: 2^-60 of it takes its place (an
 // infinite V[i] must still reach row i) and the epilogue adds V[i] itself.
 // The lengthscale and log2(e) are one factor, rounded once, of the exponent.
 // Error against 64 bits at d = 2 to 16, lengthscales 0.02 to 2, N = 300 to
@@ -52,6 +60,11 @@ using bf16::split3;
 __device__ __forceinline__ float uniform(float x) {
     return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x)));
 }
+
+// Entries of FP32's smallest normal size and elements below kVLarge keep all 24
+// bits in their parts (2^-109 and more after the scaling), sums of 64 products
+// stay below 2^126; larger elements take a pass of their own (below).
+constexpr float kKScale = 0x1p24f, kVScale = 0x1p40f, kVLarge = 0x1p56f;
 
 template <int KERNEL, int DP, int NSB, bool ARD>
 __global__ __launch_bounds__(512, NSB > 4 ? 2 : 4) void mvm_fx_kernel(MvmArgs a) {
@@ -129,10 +142,14 @@ __global__ __launch_bounds__(512, NSB > 4 ? 2 : 4) void mvm_fx_kernel(MvmArgs a)
     };
     if (c0 < c1) fetch(c0);
 
-    for (int c = c0; c < c1; ++c) {
+    __shared__ int large[NBUF];                    // the last chunk that had large elements
+    if (tid < NBUF) large[tid] = -1;
+    if (NBUF == 2) __syncthreads();
+    bool again = false;                            // this chunk's large elements
+    for (int c = c0; c < c1;) {
         const int buf = NBUF == 2 ? (c & 1) : 0;
-        const float sign = (c & 1) ? -1.0f : 1.0f;
-        if (NBUF == 1) __syncthreads();
+        const float scale = ((c & 1) ? -1.0f : 1.0f) * (again ? 1.0f / kVScale : kVScale);
+        if (NBUF == 1 || again) __syncthreads();
 #pragma unroll
         for (int k = 0; k < XPT; ++k) {
             const int e = tid + NT * k;
@@ -145,8 +162,22 @@ __global__ __launch_bounds__(512, NSB > 4 ? 2 : 4) void mvm_fx_kernel(MvmArgs a)
             const int cc = e % S16, g = e / S16;      // column, group of eight rows of V
             bf16x8 h, m, l;
 #pragma unroll
-            for (int q = 0; q < 8; ++q) vreg[u][q] *= sign;
-            split3<true>(vreg[u], h, m, l);
+            for (int q = 0; q < 8; ++q) vreg[u][q] *= scale;
+            float top = 0.0f;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) top = fmaxf(top, fabsf(vreg[u][q]));
+            if (again) {
+#pragma unroll
+                for (int q = 0; q < 8; ++q)
+                    if (fabsf(vreg[u][q]) < kVLarge / kVScale) vreg[u][q] = 0.0f;
+            } else if (top >= kVLarge * kVScale) {
+                large[buf] = c;
+#pragma unroll
+                for (int q = 0; q < 8; ++q)
+                    if (fabsf(vreg[u][q]) >= kVLarge * kVScale) vreg[u][q] = 0.0f;   // (not a NaN)
+            }
+            split3(vreg[u], h, m, l);
+            if (again) bf16::only_last(vreg[u], h, m, l);
             const int at = (g >> 2) * VB + (cc >> 4) * 64 + (g & 3) * 16 + (cc & 15);
             vs[buf][at] = h;
             vs[buf][VU + at] = m;
@@ -173,12 +204,12 @@ __global__ __launch_bounds__(512, NSB > 4 ? 2 : 4) void mvm_fx_kernel(MvmArgs a)
                     }
                 }
                 if constexpr (KERNEL == CIQ_KERNEL_RBF) {
-                    kv[u] = __builtin_amdgcn_exp2f(r2 * ec);
+                    kv[u] = __builtin_amdgcn_exp2f(r2 * ec) * kKScale;
                 } else {
                     // t = -rho log2(e); 1 + rho + rho^2 / 3 in t
                     constexpr double ln2 = 0.69314718055994530942;
                     const float t = __builtin_amdgcn_sqrtf(r2) * ec;
-                    kv[u] = fmaf(t, fmaf(t, (float)(ln2 * ln2 / 3.0), (float)-ln2), 1.0f) *
+                    kv[u] = fmaf(t, fmaf(t, (float)(ln2 * ln2 / 3.0) * kKScale, (float)-ln2 * kKScale), kKScale) *
                             __builtin_amdgcn_exp2f(t);
                 }
             }
@@ -186,10 +217,10 @@ __global__ __launch_bounds__(512, NSB > 4 ? 2 : 4) void mvm_fx_kernel(MvmArgs a)
             if (j0 <= row0 + 15 && row0 <= j0 + 31) {     // the diagonal (see above)
 #pragma unroll
                 for (int u = 0; u < 8; ++u)
-                    if (j0 + 8 * (lane >> 4) + u == row0 + (lane & 15)) kv[u] = (kv[u] - 1.0f) + 0x1p-60f;
+                    if (j0 + 8 * (lane >> 4) + u == row0 + (lane & 15)) kv[u] = (kv[u] - kKScale) + kKScale * 0x1p-60f;
             }
             bf16x8 km, kl;
-            split3<false>(kv, kh[kk], km, kl);
+            split3(kv, kh[kk], km, kl);
             const bf16x8* bp = &vs[buf][kk * VB + lane];
 #pragma unroll
             for (int sb = 0; sb < NSB; ++sb) {
@@ -210,7 +241,10 @@ __global__ __launch_bounds__(512, NSB > 4 ? 2 : 4) void mvm_fx_kernel(MvmArgs a)
 #pragma unroll
         for (int sb = 0; sb < NSB; ++sb)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) accd[sb][r] = fma((double)acc[sb][r], (double)sign, accd[sb][r]);
+            for (int r = 0; r < 4; ++r) accd[sb][r] = fma((double)acc[sb][r], (double)(1.0f / scale), accd[sb][r]);
+        again = !again && large[buf] == c;
+        if (again) fetch(c);
+        else ++c;
     }
 
     const double o2 = a.o2, s2 = a.s2;
@@ -221,7 +255,7 @@ __global__ __launch_bounds__(512, NSB > 4 ? 2 : 4) void mvm_fx_kernel(MvmArgs a)
         for (int r = 0; r < 4; ++r) {
             const int i = row0 + 4 * (lane >> 4) + r;
             if (i < n && cc < s) {
-                double val = o2 * accd[sb][r];
+                double val = o2 * (1.0 / kKScale) * accd[sb][r];
                 if (split == 0) val = fma(o2 + s2, (double)v[(long long)i * ldv + cc], val);
                 y[(long long)i * ldy + cc] = val;
             }

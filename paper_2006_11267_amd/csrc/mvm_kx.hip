@@ -142,7 +142,7 @@ __global__ __launch_bounds__(64 * WAVES, 4) void mvm_kx_kernel(MvmArgs a, int gr
                     if (8 * kk + m == step && (r & 3) == (lane >> 4))
                         kq[8 * kk + m] = (kq[8 * kk + m] - kKxScale) + kKxScale * 0x1p-60f;
             }
-            split3<false>(kq + 8 * kk, kh[kk], km, kl);
+            split3(kq + 8 * kk, kh[kk], km, kl);
             if (c + 1 < c1) fetch_k(c + 1, kk);
             const bf16x8* bp = vb + kk * VB + lane;
 #pragma unroll
