@@ -623,8 +623,7 @@ struct Run {
     int fine_acc = 0;      // FP32 resident products: the finer FP64 accumulation (inverse root)
     bool cached = false;   // products stream a resident kernel matrix (kt)
     bool with_post = false;      // products carry a posterior's correction
-    bool wide_allowed = false;   // the wide FP32 form may be chosen
-    bool wide = false;           // and is
+    bool wide = false;           // FP32 products of many columns from BF16 parts (see parts)
     bool precond = false;  // preconditioned run (single problem): Lanczos in the P^{-1} inner product
     const Precond* pc = nullptr;
     BasisSlots* bslots = nullptr;   // resident Krylov basis of this run (d.basis is its table)
@@ -689,14 +688,14 @@ struct Run {
         }
         acc = a.template take<double>(vec);
         if (keep_solves) solves = a.template take<double>(vec * Q);
-        if (max_parts() > 0) {
+        if (parts() > 0) {
             nsbt = op16_nsbt(s);
-            op_scale = op_scale_of(max_parts());
-            vt16 = a.template take<_Float16>(op_halfs(kcache_cols(max_n), nsbt, max_parts()));
+            op_scale = op_scale_of(parts());
+            vt16 = a.template take<_Float16>(op_halfs(kcache_cols(max_n), nsbt, parts()));
             opsc = a.template take<double>(s);
             opinv = a.template take<double>(s);
         }
-        if (sizeof(T) == 4 && max_parts() != 2) q32 = a.template take<float>(vec);
+        if (sizeof(T) == 4 && parts() == 0) q32 = a.template take<float>(vec);
         if (precond) {
             pbuf[0] = a.template take<double>(vec);
             pbuf[1] = a.template take<double>(vec);
@@ -741,39 +740,19 @@ struct Run {
     int rows_per_block() const {
         return parts() == 3 ? kx_rows_per_block(rt) : fx() ? kFxRows : cached ? 64 * rt : mvm_rows_per_block(dtype, s, rt);
     }
-    // parts of the split operand the products read: two for CIQ_F16X3, three
-    // for the wide CIQ_F32 form; max_parts: what the layout has room for (the
-    // wide form is decided once the bounds are known, choose_wide)
-    int max_parts() const {
+    // Parts of the split operand the products read: two for CIQ_F16X3, three for
+    // the wide CIQ_F32 form. Inverse roots pass the FP32 noise of their products
+    // on multiplied by about kappa / sqrt(N); the wide form has the less of it:
+    // its roots are 0.77 to 0.92 times as far from the FP64 ones as those of the
+    // FP32 matrix cores with sums of 16 columns (tolerance 2e-7; 47 problems, N =
+    // 1,000 to 50,000, kappa 500 to 1e7, resident and not), at any conditioning.
+    int parts() const {
         if (sp || dn || !cached || nprob != 1) return 0;
-        return dtype == CIQ_F16X3 ? 2 : (wide_allowed && kx_columns(dtype, cached, nprob, s)) ? 3 : 0;
+        return dtype == CIQ_F16X3 ? 2 : (wide && kx_columns(dtype, cached, nprob, s)) ? 3 : 0;
     }
-    int parts() const { return max_parts() == 3 ? (wide ? 3 : 0) : max_parts(); }
-    // the same choice where entries are evaluated in the product (mvm_fx.hip)
-    bool fx_form() const {
-        return wide_allowed && !sp && !dn && !cached && nprob == 1 && dtype == CIQ_F32 && s > 16;
-    }
-    bool fx() const { return wide && fx_form(); }
-    // The inverse root passes FP32 noise of the products on multiplied by about
-    // kappa / sqrt(N). The FP32 matrix cores with sums of 16 columns and the
-    // wide form differ in that noise (the wide form has half of it): up to
-    // kappa / sqrt(N) = 125 their results lie within 1.2e-5 of each other,
-    // beyond that they drift apart with it (1.5e-4 at 3,000; 64 problems, N =
-    // 800 to 20,000, kappa 20 to 4.5e5), although both are as far from the
-    // exact root. So the inverse root takes the wide form where results keep to
-    // what the FP32 matrix cores gave, and from 32,768 rows on, where the
-    // product is most of a solve (3.7 -> 2.2 ms). The square root's FP32 path
-    // had sums of 64 columns, whose own noise is as large as any difference.
-    void choose_wide(bool sqrt_mode, double kappa) {
-        wide = (max_parts() == 3 || fx_form()) &&
-               (sqrt_mode || max_n >= 32768 || kappa <= 125.0 * std::sqrt((double)max_n));
-        use_operand();
-    }
-    void use_operand() {      // the operand copy that is not read is not written
-        if (parts() > 0) q32 = nullptr;
-        else vt16 = nullptr;
-    }
-    size_t op_words() const { return op_halfs(kcache_cols(max_n), nsbt, max_parts()) / 2; }
+    // the same where entries are evaluated in the product (mvm_fx.hip)
+    bool fx() const { return wide && !sp && !dn && !cached && nprob == 1 && dtype == CIQ_F32 && s > 16; }
+    size_t op_words() const { return op_halfs(kcache_cols(max_n), nsbt, parts()) / 2; }
 
     // The sparse product of one column carries phase 0 of the inner products:
     // above the sizes of the one-launch step, up to 256 partials (more cost
@@ -847,16 +826,11 @@ struct Run {
     void plan(int rt_) {
         nsplit_alloc = 1;
         nrb_alloc = 1;
-        const bool w0 = wide;
-        for (int form = 0; form < 2; ++form) {   // with and without the wide form
-            wide = (form == 1);
-            for (int r = 1; r <= 2; ++r) {
-                configure(r);
-                nsplit_alloc = std::max(nsplit_alloc, nsplit);
-                nrb_alloc = std::max(nrb_alloc, nrb);
-            }
+        for (int r = 1; r <= 2; ++r) {
+            configure(r);
+            nsplit_alloc = std::max(nsplit_alloc, nsplit);
+            nrb_alloc = std::max(nrb_alloc, nrb);
         }
-        wide = w0;
         if (nprob > 1) nsplit_alloc = std::max(nsplit_alloc, 4);   // the tuner's batched candidates
         if (with_post) nsplit_alloc += 4;                          // the correction's partials
         configure(rt_);
@@ -1380,7 +1354,7 @@ int kcache_build(Run<T>& r, const KCache& kc, hipStream_t st) {
     ka.nchunk = (int)(kcache_cols(ka.n) / 64);
     ka.njs = (long long)(kcache_cols(ka.n) / 4);
     ka.elem = (r.dtype == CIQ_F16X3) ? 2 : (kc.elem == 4 ? 1 : 0);
-    ka.mult = (r.max_parts() == 3) ? kKxScale : 1.0;
+    ka.mult = (r.parts() == 3) ? kKxScale : 1.0;
     ka.kt = kc.ptr;
     HIPCHK(launch_kbuild(ka, st));
     r.kt = kc.ptr;
@@ -1517,9 +1491,10 @@ int solve(int nprob, const ciq_problem* probs, const ciq_opts* o, const void* co
     // the inverse root keeps FP64 partials
     main.part32 = (mode == CIQ_SQRT) && nprob == 1 && main.cached && (dtype == CIQ_F32 || dtype == CIQ_F16X3) &&
                   !precond && post_spec == nullptr && sparse == nullptr && dense == nullptr;
-    // (inverse roots: kept solves feed gradients, whose sums cancel, and a
-    // posterior's products carry noise of the prior's size, see choose_wide)
-    main.wide_allowed = !precond && (mode == CIQ_SQRT || (post_spec == nullptr && solves_out == nullptr));
+    // (inverse roots with kept solves, which feed gradients, and of posteriors,
+    // whose products carry noise of the prior's size, subtract sums of that noise,
+    // so that any other form moves their results: they keep the FP32 matrix cores)
+    main.wide = !precond && (mode == CIQ_SQRT || (post_spec == nullptr && solves_out == nullptr));
     main.with_post = post_spec != nullptr;
     main.plan(2);
 
@@ -1656,8 +1631,6 @@ int solve(int nprob, const ciq_problem* probs, const ciq_opts* o, const void* co
     }
     HIPCHK(hipMemcpyAsync(main.t, th.data(), th.size() * sizeof(double), hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(main.w, wh.data(), wh.size() * sizeof(double), hipMemcpyHostToDevice, st));
-
-    main.choose_wide(mode == CIQ_SQRT, dense ? 1.0 : lmax[0] / lmin[0]);
 
     // ---- right-hand sides --------------------------------------------------
     for (int p = 0; p < nprob; ++p)
@@ -1825,7 +1798,7 @@ int backward_impl(const ciq_problem* p, const ciq_opts* o, int mode, const doubl
     r.keep_solves = true;
     r.fine_acc = sqrt_mode ? 0 : 1;
     r.cached = (kc.ptr != nullptr);
-    r.wide_allowed = sqrt_mode;
+    r.wide = sqrt_mode;
     r.plan(2);
 
     const int kpad = grad_k_pad((Q + (sqrt_mode ? 1 : 0)) * s);
@@ -1849,8 +1822,6 @@ int backward_impl(const ciq_problem* p, const ciq_opts* o, int mode, const doubl
     Carver c(base);
     r.layout(c, true);
     extra(c, &U, &V, &pts, &xd, &part);
-    r.choose_wide(sqrt_mode, 1.0);
-    r.configure(2);
     r.fill_dev();
     STCHK(r.upload_tables(st));
     STCHK(setup_points(r, p, dtype, st));
@@ -2171,7 +2142,7 @@ int ciq_kernel_mvm_resident(const ciq_problem* p, int dtype, const void* v, int 
         r.Q = 0;
         r.max_iter = 1;
         r.cached = true;
-        r.wide_allowed = true;
+        r.wide = true;
         r.plan(2);
         Sizer sz;
         r.layout(sz, true);
@@ -2179,7 +2150,6 @@ int ciq_kernel_mvm_resident(const ciq_problem* p, int dtype, const void* v, int 
         STCHK(scratch_reserve(dev, sz.off + 4096, &base));
         Carver c(base);
         r.layout(c, true);
-        r.choose_wide(true, 1.0);
         r.fill_dev();
         STCHK(r.upload_tables(stream));
         STCHK(setup_points(r, p, dtype, stream));

@@ -12,11 +12,11 @@ pytestmark = pytest.mark.gpu
 TINY = 2.0 ** -119          # 1.5e-36: a normal FP32 number
 
 
-def _case(torch, ciq, n, s, seed, kind="matern52", d=3, ls=0.4, noise=0.1):
+def _case(torch, ciq, n, s, seed, kind="matern52", d=3, ls=0.4, noise=0.1, dense=True):
     rng = np.random.default_rng(seed)
     x = rng.random((n, d)).astype(np.float32)
     b = rng.standard_normal((n, s)).astype(np.float32)
-    K = okern.kernel_matrix(kind, x.astype(np.float64), [ls], 1.0, noise)
+    K = okern.kernel_matrix(kind, x.astype(np.float64), [ls], 1.0, noise) if dense else None
     return ciq.Problem(torch.from_numpy(x).cuda(), kind, [ls], 1.0, noise), b, K
 
 
@@ -166,3 +166,37 @@ def test_wide_solve_basis_and_graph(mode, basis):
     for _ in range(2):
         g, ginfo, _ = fn(prob, bt, graph=True, **kw)
         assert ginfo["iters"] == info["iters"] and torch.equal(g, out)
+
+
+def _fp64_inverse_root(torch, ciq, prob, b):
+    """The same quadrature (its bounds returned) with FP64 products, converged."""
+    p64 = ciq.Problem(prob.x.double(), prob.kernel, prob.lengthscale, prob.outputscale, prob.noise)
+    ref, info, _ = ciq.ciq_invsqrt_mvm(p64, b.double(), q=15, max_iter=12000, tol=1e-10)
+    assert info["converged"]
+    return ref.cpu().numpy(), (info["lambda_min"], info["lambda_max"])
+
+
+@pytest.mark.parametrize("cache", ["on", "off"])
+@pytest.mark.parametrize("kind,n,d,ls,noise", [
+    ("rbf", 4000, 3, 0.2, 1e-3),             # kappa 3e5
+    ("rbf", 4000, 3, 0.2, 1e-2),
+    ("matern52", 33000, 6, 0.3, 1e-2),       # 1.6e5
+    ("matern52", 32700, 6, 0.3, 1e-1),
+])
+def test_wide_inverse_root_noise(kind, n, d, ls, noise, cache):
+    """K^{-1/2} B of 40 columns: FP32 rounding of the products reaches the root
+    multiplied by about kappa / sqrt(N). A resident product is off by at most 1.2
+    x 2^-24 of its norm, one that evaluates FP32 entries by 2.5 x 2^-24 (their
+    own rounding), at any conditioning and size; the solver's tolerance adds 1e-6."""
+    torch = torch_cuda()
+    ciq = ciq_module()
+    prob, b, _ = _case(torch, ciq, n, 40, 9, kind, d=d, ls=ls, noise=noise, dense=False)
+    bt = torch.from_numpy(b).cuda()
+    announce(f"wide inverse root {kind} n={n} noise={noise} cache={cache}")
+    ref, bounds = _fp64_inverse_root(torch, ciq, prob, bt)
+    out, info, _ = ciq.ciq_invsqrt_mvm(prob, bt, q=15, max_iter=12000, tol=2e-7, bounds=bounds, kernel_cache=cache)
+    err = colwise_rel(out.cpu().numpy(), ref).mean()
+    unit = 2.0 ** -24 * bounds[1] / bounds[0] / np.sqrt(n)
+    print(f"{kind} n={n} kappa={bounds[1] / bounds[0]:.2g} cache={cache}: {err:.2e} = {err / unit:.2f} units",
+          flush=True)
+    assert err < (1.2 if cache == "on" else 2.5) * unit + 1e-6
