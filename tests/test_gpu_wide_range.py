@@ -200,3 +200,36 @@ def test_wide_inverse_root_noise(kind, n, d, ls, noise, cache):
     print(f"{kind} n={n} kappa={bounds[1] / bounds[0]:.2g} cache={cache}: {err:.2e} = {err / unit:.2f} units",
           flush=True)
     assert err < (1.2 if cache == "on" else 2.5) * unit + 1e-6
+
+
+@pytest.mark.parametrize("kind,d,ls", [("rbf", 4, 0.35), ("matern52", 6, 0.3)])
+def test_wide_sqrt_scalar_gradients(kind, d, ls):
+    """Gradients of <G, K^{1/2} B> for the hyperparameters, whose sums cancel:
+    against the same with FP64 products on the same quadrature, over six seeds, in
+    units of the values' own size. The products' noise (2^-24) reaches the solves
+    multiplied by kappa / sqrt(N) = 30; gradients for the lengthscale and the
+    outputscale average it over N S terms, the noise's (a trace) is the smallest
+    difference: 1e-5 of the first two, 1e-4 of the last."""
+    torch = torch_cuda()
+    ciq = ciq_module()
+    n, s = 1000, 64
+    errs, vals = [], []
+    for seed in range(6):
+        prob, b, _ = _case(torch, ciq, n, s, 100 + seed, kind, d=d, ls=ls, noise=5e-2, dense=False)
+        bt = torch.from_numpy(b).cuda()
+        g = torch.from_numpy(np.random.default_rng(seed).standard_normal((n, s)).astype(np.float32)).cuda()
+        p64 = ciq.Problem(prob.x.double(), kind, [ls], 1.0, 5e-2)
+        announce(f"scalar gradients {kind} seed={seed}")
+        kw = dict(max_iter=2000)
+        _, info, sol = ciq.ciq_sqrt_mvm(p64, bt.double(), q=15, tol=1e-11, keep_solves=True, **kw)
+        ref = ciq.ciq_backward(p64, g.double(), info["t"], info["w"], sol, mode="sqrt", tol=1e-11, **kw)
+        _, i32, sol = ciq.ciq_sqrt_mvm(prob, bt, q=15, tol=1e-7, keep_solves=True,
+                                       bounds=(info["lambda_min"], info["lambda_max"]), **kw)
+        got = ciq.ciq_backward(prob, g, i32["t"], i32["w"], sol, mode="sqrt", tol=1e-7, **kw)
+        vals.append([float(np.ravel(ref[k])[0]) for k in (1, 2, 3)])
+        errs.append([float(np.ravel(got[k])[0]) - vals[-1][k - 1] for k in (1, 2, 3)])
+        assert colwise_rel(got[0].cpu().numpy(), ref[0].cpu().numpy()).max() < 1e-5
+    rms = lambda a: np.sqrt((np.array(a) ** 2).mean(axis=0))  # noqa: E731
+    rel = rms(errs) / rms(vals)
+    print(f"{kind}: lengthscale {rel[0]:.1e}, outputscale {rel[1]:.1e}, noise {rel[2]:.1e}", flush=True)
+    assert rel[0] < 1e-5 and rel[1] < 1e-5 and rel[2] < 1e-4
