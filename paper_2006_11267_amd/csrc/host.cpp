@@ -1367,7 +1367,7 @@ int kcache_build(Run<T>& r, const KCache& kc, hipStream_t st) {
 // padded with zero columns (which never start: a zero column of B has a zero
 // result) to a multiple of four, so the vector passes move 16 bytes a lane
 // whatever s is; the padding is within the 16-column blocks that the products
-// compute anyway.
+// compute anyway. Where the scratch has no room for it, a run goes without.
 int run_cols(int s) { return s <= 2 ? s : (s + 3) / 4 * 4; }
 
 struct ScratchLock {
@@ -1476,8 +1476,6 @@ int solve(int nprob, const ciq_problem* probs, const ciq_opts* o, const void* co
     main.sp = sparse;
     main.dn = dense;
     main.dtype = dtype;
-    const int sr = run_cols(s);
-    main.s = sr;
     main.Q = o->q;
     main.max_iter = o->max_iter;
     main.tol = o->tol;
@@ -1496,7 +1494,6 @@ int solve(int nprob, const ciq_problem* probs, const ciq_opts* o, const void* co
     // so that any other form moves their results: they keep the FP32 matrix cores)
     main.wide = !precond && (mode == CIQ_SQRT || (post_spec == nullptr && solves_out == nullptr));
     main.with_post = post_spec != nullptr;
-    main.plan(2);
 
     Run<T> bnd;
     fill_problem_tables(bnd, probs, nprob, dtype);
@@ -1513,16 +1510,21 @@ int solve(int nprob, const ciq_problem* probs, const ciq_opts* o, const void* co
     bnd.with_post = main.with_post;
     bnd.plan(2);
 
-    Sizer sz;
-    main.layout(sz, true);
-    const size_t off_after_xh = 0;
-    (void)off_after_xh;
     Sizer szb;
     szb.take<double>((size_t)main.rows_total * main.dp);
     bnd.layout(szb, false);
-    const size_t need = std::max(sz.off, szb.off) + 4096;
     void* base = nullptr;
-    STCHK(scratch_reserve(dev, need, &base));
+    int sr = run_cols(s);
+    for (;;) {
+        main.s = sr;
+        main.plan(2);
+        Sizer sz;
+        main.layout(sz, true);
+        const int rc = scratch_reserve(dev, std::max(sz.off, szb.off) + 4096, &base);
+        if (rc == CIQ_OK) break;
+        if (rc != CIQ_ENOMEM || sr == s) return rc;
+        sr = s;                           // no room for the padding columns
+    }
     IterState* pinned = g_scratch[dev].pinned;
 
     Carver cm(base);
@@ -1790,8 +1792,6 @@ int backward_impl(const ciq_problem* p, const ciq_opts* o, int mode, const doubl
     Run<T> r;
     fill_problem_tables(r, p, 1, dtype);
     r.dtype = dtype;
-    const int sr = run_cols(s);
-    r.s = sr;
     r.Q = Q;
     r.max_iter = o->max_iter;
     r.tol = o->tol;
@@ -1799,7 +1799,6 @@ int backward_impl(const ciq_problem* p, const ciq_opts* o, int mode, const doubl
     r.fine_acc = sqrt_mode ? 0 : 1;
     r.cached = (kc.ptr != nullptr);
     r.wide = sqrt_mode;
-    r.plan(2);
 
     const int kpad = grad_k_pad((Q + (sqrt_mode ? 1 : 0)) * s);
     const int rows_pad = grad_rows_pad(n);
@@ -1813,11 +1812,19 @@ int backward_impl(const ciq_problem* p, const ciq_opts* o, int mode, const doubl
         *part = a.template take<double>((size_t)nb * nb * (dpg + 2));
     };
     double *U, *V, *pts, *xd, *part;
-    Sizer sz;
-    r.layout(sz, true);
-    extra(sz, &U, &V, &pts, &xd, &part);
     void* base = nullptr;
-    STCHK(scratch_reserve(dev, sz.off + 4096, &base));
+    int sr = run_cols(s);
+    for (;;) {
+        r.s = sr;
+        r.plan(2);
+        Sizer sz;
+        r.layout(sz, true);
+        extra(sz, &U, &V, &pts, &xd, &part);
+        const int rc = scratch_reserve(dev, sz.off + 4096, &base);
+        if (rc == CIQ_OK) break;
+        if (rc != CIQ_ENOMEM || sr == s) return rc;
+        sr = s;                           // as in solve
+    }
     IterState* pinned = g_scratch[dev].pinned;
     Carver c(base);
     r.layout(c, true);
