@@ -274,10 +274,15 @@ int ciq_kernel_mvm(const ciq_problem* p, int dtype, const void* v, int s, int ld
  * without ordering) race and give wrong results; calls on one stream are
  * ordered. The caller still supplies v and y.
  * Asynchronous on `stream`. Errors: as for ciq_kernel_mvm, and CIQ_EINVAL when
- * n * d_pad * 8 (rounded up to 256) + nsplit * n * s * 8 bytes exceed
- * CIQ_NOALLOC_SCRATCH_BYTES (d_pad: d padded to 4/6/8/10/12/16; nsplit <= 8,
- * the split of the column range the kernel uses; CIQ_F64 with one split and
- * s <= 64 needs no partials); CIQ_EHIP if the array's address cannot be taken.
+ * n * d_pad * 8 (rounded up to 256) + ranges * n * s * 8 bytes exceed
+ * CIQ_NOALLOC_SCRATCH_BYTES (d_pad: d padded to 4/6/8/10/12/16); CIQ_EHIP if
+ * the array's address cannot be taken. `ranges` is a nominal number of column
+ * ranges: that of 1..min(8, ceil(n / 64)) which leaves the least of the last
+ * round of blocks idle (less 2 % for each further range) when blocks of 64
+ * rows (128 for CIQ_F64, and for CIQ_F32 of at most 64 columns) fill 1,024
+ * slots (512 beyond 32 columns); CIQ_F64 with ranges = 1 and s <= 64 counts no
+ * partials. The launch itself may use up to 16 ranges, as many as the array
+ * holds.
  */
 int ciq_kernel_mvm_noalloc(const ciq_problem* p, int dtype, const void* v, int s, int ldv,
                            void* y, int ldy, hipStream_t stream);
