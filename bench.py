@@ -21,7 +21,7 @@ its columns/s, accuracy and HBM roofline are reported beside the FP32 line
 
 Default path: the kernel matrix is evaluated once per call in FP64, rounded
 to FP32 and kept resident in HBM (10 GB); every product streams it, splits each
-FP32 entry exactly into three FP16 parts and contracts them on the FP16 MFMA
+FP32 entry into three BF16 parts (24 bits) and contracts them on the BF16 MFMA
 with FP64 sums across 64-column chunks; Lanczos and search-direction vectors and
 all scalars are FP64 (dtype "f32" names the product arithmetic).
 
@@ -94,7 +94,7 @@ def roofline(precision: str, cached: bool, n: int, s: int, avg_ms: float, launch
     """Roofline of the kernel product from its live HIP-event timing. The FP64
     products and the narrow FP32 ones are reported against the dense MFMA peak
     of their precision: 2 N^2 S flops per launch. The resident split FP16
-    product and the resident FP32 one of more than 32 columns (exact FP16 parts)
+    product and the resident FP32 one of more than 32 columns (BF16 parts)
     are HBM-bound: their algorithmic bytes per launch are the matrix (4 bytes
     per entry, N^2 entries), the split operand (4 or 6 N S) and the FP64 result
     (8 N S), against 8 TB/s."""

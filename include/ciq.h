@@ -70,15 +70,15 @@ extern "C" {
                            (no FP32 sums: the result is the rounded matrix's),
                            K^{1/2}B solves of at most 32 columns keep FP32 sums
                            of 16 columns. Wider single-problem K^{1/2}B solves
-                           contract three-part BF16 splits of the FP32 entries
-                           and of the vectors (24 bits each) on the BF16 MFMA with
-                           FP32 sums of 64 columns, and so do wider K^{-1/2}B solves
-                           that keep no per-shift solves and have no
-                           preconditioner and no posterior (the others: FP32 MFMA,
-                           sums of 16 columns). Where entries are evaluated in the
-                           product, the same rule from 17 columns on, and
-                           ciq_kernel_mvm from 17 columns on, take such splits
-                           too                                                  */
+                           without a preconditioner contract three-part BF16
+                           splits of the FP32 entries and of the vectors (24 bits
+                           each) on the BF16 MFMA with FP32 sums of 64 columns,
+                           and so do wider K^{-1/2}B solves that moreover keep no
+                           per-shift solves and have no posterior (the others:
+                           FP32 MFMA, sums of 16 columns, 64 for K^{1/2}B). Where
+                           entries are evaluated in the product, the same rule
+                           from 17 columns on, and ciq_kernel_mvm from 17 columns
+                           on, take such splits too                             */
 #define CIQ_BF16X3  2   /* as CIQ_F32, but the entries and V are split into BF16
                            hi + scaled lo parts: K V ~ Kh Vh + 2^-8 (Kh Vl + Kl Vh)
                            on bf16 MFMA, FP32 accumulation (~1e-5 per product)   */

@@ -118,7 +118,7 @@ constexpr int kOp3ScaleLog2 = 96;        // others: their largest element, per c
 inline size_t op_halfs(size_t rows_pad, int nsbt, int parts) { return rows_pad * (size_t)nsbt * 16 * parts; }
 inline double op_scale_of(int parts) { return parts == 3 ? kOp3Scale : kOp16Scale; }
 
-// Where the update / start kernels write the split FP16 copy of the next
+// Where the update / start kernels write the split copy of the next
 // product operand (p == nullptr: none), in two (op16_index) or three
 // (op3_index) parts.
 struct Op16 {
@@ -229,7 +229,7 @@ inline int product_cap(int dtype, bool cached) {
     return ((dtype == CIQ_F32 && !cached) || (dtype == CIQ_F16X3 && cached)) ? 128 : 64;
 }
 // More than 32 columns of a single resident CIQ_F32 problem can run on the
-// FP16 matrix cores (three-part operand, mvm_kx.hip); at most 32 are HBM-bound
+// BF16 matrix cores (three-part operand, mvm_kx.hip); at most 32 are HBM-bound
 // as they are (see kt32_item).
 inline bool kx_columns(int dtype, bool cached, int nprob, int s) {
     return cached && nprob == 1 && dtype == CIQ_F32 && s > 32;
@@ -321,7 +321,7 @@ template <typename T>
 hipError_t launch_init_vectors(const Dev& d, T* q, T* qprev, T* acc, float* q32, int rows,
                                hipStream_t st, T* pvec = nullptr, Op16 op = Op16{nullptr, 0, 1.0, 0});
 
-// Split FP16 operand (two parts in op16_index layout or three in op3_index
+// Split operand (two FP16 parts in op16_index layout or three BF16 ones in op3_index
 // layout, nsbt column blocks) of the n x s FP64 block x (ld): per-column
 // power-of-two scales (scale, inv: device [s]).
 hipError_t launch_op16_split(const double* x, int n, int s, int ld, double* scale, double* inv, void* vt,

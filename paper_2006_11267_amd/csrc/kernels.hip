@@ -1473,9 +1473,10 @@ template hipError_t launch_init_vectors<double>(const Dev&, double*, double*, do
 // ----------------------------------------------------------------------------
 // Split operand of an arbitrary FP64 block vector: per column a power of two 2^e
 // with max_i |x[i][c]| 2^e in [half, full) over the finite elements, full 256 for
-// two FP16 parts and 2^kOp3ScaleLog2 for three BF16 ones (1 for a zero column), then the split of
-// x[i][c] 2^e. inv[c] = 2^-e undoes it in the product. The scale stays in FP64:
-// a column of small FP32 numbers needs one beyond FP32's range.
+// two FP16 parts and 2^kOp3ScaleLog2 for three BF16 ones (1 for a zero column),
+// then the split of x[i][c] 2^e. inv[c] = 2^-e undoes it in the product. The
+// scale stays in FP64: a column of small FP32 numbers needs one beyond FP32's
+// range.
 // Block: 64 columns x 16 row lanes, fixed combination order.
 // ----------------------------------------------------------------------------
 __global__ __launch_bounds__(1024) void op16_scale_kernel(const double* x, int n, int s, int ld, int full_log2,

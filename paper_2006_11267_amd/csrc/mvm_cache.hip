@@ -323,10 +323,10 @@ __global__ __launch_bounds__(64 * WAVES) void mvm_kt_kernel(MvmArgs a) {
 // stream K at HBM speed with the matrix cores less than half busy. Those
 // launches use B = 4, or the FP64 MFMA for the inverse root (a.acc); the
 // 64-column launch is MFMA-bound and uses B = 16, or B = 4 for the inverse
-// root (plain solves of more than 32 columns run on the FP16 matrix cores
-// where their conditioning allows, mvm_kx.hip). A single problem's column
-// groups of 64 run in one launch (grid.y): at N = 5,000, S = 256 one group
-// leaves the chip's last round of blocks mostly idle (206 against 140 us).
+// root (plain solves and products of more than 32 columns run on the BF16
+// matrix cores, mvm_kx.hip). A single problem's column groups of 64 run in one
+// launch (grid.y): at N = 5,000, S = 256 one group leaves the chip's last round
+// of blocks mostly idle (four launches of 50 us against one of 172).
 // Batched runs (a.wl set) keep one such matrix per problem (a.pkt: its
 // element offset, a.pnjs: its padded columns / 4) and run persistently: a
 // grid of the resident blocks takes (problem, row block, column range) items
