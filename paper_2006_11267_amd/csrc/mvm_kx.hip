@@ -37,13 +37,13 @@
 // of two LDS buffers, one barrier per chunk (see kt32_item). Sixteen waves
 // halve the operand's L2 reads (24 KB per block and chunk against 64 KB of K)
 // and fit 128 registers a wave. Measured at N = 50,000, S = 64 (the FP32 MFMA
-// form: 2.86 ms with FP32 sums of 64 columns, 3.72 with sums of 16): 2.16 ms with
-// sixteen waves, 4.7 TB/s of K (FP16 parts in turn with them: 2.15). With FP16
-// parts, of 2.13 in that run: eight waves 2.20, 12 waves with two chunks of K in
-// flight 2.23, two tiles a wave 2.31, 128 columns a launch 4.35 (no better than
-// two groups of 64). More than 64 columns run as groups of one launch, the groups
-// of a row block next to each other on one XCD so that its L2 serves K to the
-// later ones.
+// form: 2.86 ms with FP32 sums of 64 columns, 3.72 with sums of 16): 2.18 ms with
+// sixteen waves, 4.6 TB/s of K (FP16 parts with neither alternating signs nor the
+// diagonal outside, in turn with it: 2.15). Tried with those, where sixteen waves
+// took 2.13: eight waves 2.20, 12 waves with two chunks of K in flight 2.23, two
+// tiles a wave 2.31, 128 columns a launch 4.35 (no better than two groups of 64).
+// More than 64 columns run as groups of one launch, the groups of a row block next
+// to each other on one XCD so that its L2 serves K to the later ones.
 #include <algorithm>
 #include <cmath>
 
